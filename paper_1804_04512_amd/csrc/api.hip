@@ -480,10 +480,18 @@ dll_status dll_rbm_cd1_step(int batch, int n_vis, int n_hid, int visible, const 
   float *h0p = h0_prob ? h0_prob : h0p_ws;
   float *h0s = h0_sample ? h0_sample : h0s_ws;
   float *h1p = h1_prob ? h1_prob : h1p_ws;
-  float *v1p = vstack + nV;   // the reconstruction is produced in place as the lower half of the stack
+  const float invB = 1.0f / (float)B;
+  // Where every product is one the small-product kernel takes (the three batch-by-units products and
+  // one phase of dW have the same multiply-add count), the step is four launches: the states leave in
+  // the epilogue that forms their probabilities, and the statistics - dW as the difference of two
+  // products, both column sums, the reconstruction error from the squares summed by the reconstruction's
+  // epilogue - are jobs of one closing launch.  100 x 784 x 500: ten launches, 44.9 us -> @@ us.
+  const bool small = gemm_is_small(B, nh, nv);
+  float *v1p = small && v1 ? v1 : vstack + nV;   // else the reconstruction is the lower half of the stack
+  float *sq_partial = vstack;                    // small: gemm_small_tiles(B, nv) <= B * nv floats
 
   // hidden probabilities of a visible batch: sigmoid(b_hid + v W^T)
-  auto hidden = [&](const float *v, float *out) {
+  auto hidden = [&](const float *v, float *out, bool states) {
     GemmArgs g;
     g.M = B; g.N = nh; g.Kdim = nv;
     g.A = v; g.a_m = nv; g.a_k = 1;
@@ -492,14 +500,16 @@ dll_status dll_rbm_cd1_step(int batch, int n_vis, int n_hid, int visible, const 
     g.Cout = out; g.c_m = nh; g.c_n = 1;
     g.split_k = gemm_pick_split_k(g.M, g.N, g.Kdim);
     g.partial = partial;
+    if (states) { g.uniform = uniform; g.sample = h0s; }
     return dev(launch_gemm(g, s));
   };
-  if ((st = hidden(v0, h0p)) != DLL_OK) return st;
+  const bool fused_states = small && !h0_sample_in;
+  if ((st = hidden(v0, h0p, fused_states)) != DLL_OK) return st;
   const float *hs = h0s;
   if (h0_sample_in) {
     hs = h0_sample_in;
     if (h0_sample && (st = dev(launch_copy(h0_sample_in, h0_sample, nH, s))) != DLL_OK) return st;
-  } else if ((st = dev(launch_bernoulli(h0p, uniform, h0s, nH, s))) != DLL_OK) {
+  } else if (!fused_states && (st = dev(launch_bernoulli(h0p, uniform, h0s, nH, s))) != DLL_OK) {
     return st;
   }
   {
@@ -512,13 +522,28 @@ dll_status dll_rbm_cd1_step(int batch, int n_vis, int n_hid, int visible, const 
     g.Cout = v1p; g.c_m = nv; g.c_n = 1;
     g.split_k = gemm_pick_split_k(g.M, g.N, g.Kdim);
     g.partial = partial;
+    if (small && recon_mse) { g.sq_ref = v0; g.sq_partial = sq_partial; }
     if ((st = dev(launch_gemm(g, s))) != DLL_OK) return st;
   }
-  if ((st = hidden(v1p, h1p)) != DLL_OK) return st;
+  if ((st = hidden(v1p, h1p, false)) != DLL_OK) return st;
+  if (small) {
+    GemmArgs g;
+    g.M = nh; g.N = nv; g.Kdim = B;
+    g.A = h0p; g.A2 = h1p; g.a_m = 1; g.a_k = nh;
+    g.B = v0; g.B2 = v1p; g.b_k = nv; g.b_n = 1;
+    g.alpha = invB;
+    g.Cout = dW; g.c_m = nv; g.c_n = 1;
+    if (lr != 0.0f) { g.update = W; g.step = lr; }
+    StepTail t;
+    t.gemm[t.n_gemm++] = g;
+    t.colsum[t.n_colsum++] = StepTail::Colsum{h0p, B, nh, db, lr != 0.0f ? b_hid : nullptr, lr, nullptr, 0.0f, h1p, invB};
+    t.colsum[t.n_colsum++] = StepTail::Colsum{v0, B, nv, dc, lr != 0.0f ? c_vis : nullptr, lr, nullptr, 0.0f, v1p, invB};
+    if (recon_mse) { t.rowloss = sq_partial; t.rows = (int)gemm_small_tiles(B, nv); t.count = (double)B * nv; t.loss = recon_mse; }
+    return dev(launch_step_tail(t, s));
+  }
   if (v1 && (st = dev(launch_copy(v1p, v1, nV, s))) != DLL_OK) return st;
   // statistics: with the phases stacked along the batch axis (signs and 1/B folded into the hidden
   // half), dW is ONE product over 2B rows and db one column sum; the updates ride in their epilogues
-  const float invB = 1.0f / (float)B;
   if ((st = dev(launch_copy(v0, vstack, nV, s))) != DLL_OK) return st;
   if ((st = dev(launch_rbm_stack(h0p, h1p, invB, hstack, nH, s))) != DLL_OK) return st;
   if ((st = dev(launch_rbm_visible_stats(v0, v1p, B, nv, invB, dc, recon_mse, lr != 0.0f ? c_vis : nullptr, lr, stats, s))) !=
@@ -755,9 +780,12 @@ dll_status run_cnn_step(const dll_net_desc *net, float *const *params, float *co
     // The weight-gradient product only has to be done before the step ends (nothing below reads the
     // updated weights: every data gradient is taken with the old ones, just above).  It waits for
     // the next layer's, and the two share a launch: the upper layers' products are too small to
-    // fill the chip on their own.
+    // fill the chip on their own.  Small ones are jobs of the closing launch.
     if (h.Cout || h.update) {
-      if (have_pending) {
+      if (step_tail_takes(h)) {
+        if (tail.n_gemm == StepTail::kMaxGemm && (st = flush_tail()) != DLL_OK) return st;
+        tail.gemm[tail.n_gemm++] = h;
+      } else if (have_pending) {
         if ((st = dev(launch_gemm_pair(h, pending, s))) != DLL_OK) return st;
         have_pending = false;
       } else {
@@ -769,7 +797,7 @@ dll_status run_cnn_step(const dll_net_desc *net, float *const *params, float *co
     if (gb || upd) {
       if (tail.n_colsum == StepTail::kMaxColsum && (st = flush_tail()) != DLL_OK) return st;
       tail.colsum[tail.n_colsum++] = StepTail::Colsum{gcur, B, dd->out, gb, upd ? bq : nullptr, step,
-                                                      (upd && velocity) ? velocity[2 * (L + q) + 1] : nullptr, mu};
+                                                      (upd && velocity) ? velocity[2 * (L + q) + 1] : nullptr, mu, nullptr, 1.0f};
     }
   }
   if (have_pending && (st = dev(launch_gemm(pending, s))) != DLL_OK) return st;

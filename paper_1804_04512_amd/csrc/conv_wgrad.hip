@@ -15,6 +15,7 @@
 // bit-identical from run to run) and can apply the parameter update in the same pass.
 #include "dll_internal.h"
 #include "small_bodies.h"
+#include "gemm_small_body.h"
 
 #include <type_traits>
 
@@ -633,26 +634,47 @@ inline int reduce_blocks(const WgradReduceArgs &a, const WgradPlan &plan) {
   return reduce_kgroups(a, plan) * plan.nchunks * plan.MTF * plan.NTT * 16 + (a.K + 15) / 16;
 }
 
-// The step's closing kernel: workgroup ranges [start[j], start[j+1]) belong to job j; jobs are the
-// filter-gradient reductions, then the column sums, then the mean loss.
+// The step's closing kernel: workgroup ranges [start[j], start[j+1]) belong to job j; jobs are the small
+// weight-gradient products, the filter-gradient reductions, the column sums, then the mean loss.  The
+// reductions alone (PRODUCTS = false) are bound by memory latency and live from their occupancy, which the
+// products' registers and LDS would halve.  As launches of their own the products of a small network took
+// 4 to 10 us each, most of it latency; here they run beside each other and the reductions.
 struct StepTailParams {
-  StepTail t;
-  int start[StepTail::kMaxReduce + StepTail::kMaxColsum + 2];
+  int n_reduce, n_colsum, n_gemm;
+  StepTail::Reduce reduce[StepTail::kMaxReduce];
+  StepTail::Colsum colsum[StepTail::kMaxColsum];
+  small_gemm::SmallParams gemm[StepTail::kMaxGemm];
+  const float *rowloss; int rows; float *loss; double count;
+  int start[StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 2];
   long group_stride[StepTail::kMaxReduce];
   int kgroups[StepTail::kMaxReduce];
 };
+static_assert(sizeof(StepTailParams) <= 4096, "kernel arguments");
+template <bool PRODUCTS>
 __global__ __launch_bounds__(kThreads) void step_tail_kernel(const StepTailParams p) {
   const int b = blockIdx.x;
   int j = 0;
   while (b >= p.start[j + 1]) ++j;   // uniform; at most a dozen jobs
   const int blk = b - p.start[j];
-  if (j < p.t.n_reduce) {
-    wgrad_reduce_block(p.t.reduce[j].a, p.t.reduce[j].plan, p.group_stride[j], p.kgroups[j], blk);
-  } else if (j < p.t.n_reduce + p.t.n_colsum) {
-    const StepTail::Colsum &c = p.t.colsum[j - p.t.n_reduce];
-    colsum_block(c.A, c.M, c.N, c.out, c.update, c.step, c.vel, c.mu, blk);
+  if constexpr (PRODUCTS) {
+    if (j < p.n_gemm) {
+      __shared__ __attribute__((aligned(16))) float red[small_gemm::kOuterRedFloats];
+      const small_gemm::SmallParams &g = p.gemm[j];
+      const int nx = (g.a.N + small_gemm::kOuterN - 1) / small_gemm::kOuterN;
+      const int mt = blk / nx, nt = blk - mt * nx;
+      if (g.a.A2) small_gemm::outer_product<2>(g, mt, nt, red);
+      else small_gemm::outer_product<1>(g, mt, nt, red);
+      return;
+    }
+    j -= p.n_gemm;
+  }
+  if (j < p.n_reduce) {
+    wgrad_reduce_block(p.reduce[j].a, p.reduce[j].plan, p.group_stride[j], p.kgroups[j], blk);
+  } else if (j < p.n_reduce + p.n_colsum) {
+    const StepTail::Colsum &c = p.colsum[j - p.n_reduce];
+    colsum_block(c.A, c.M, c.N, c.out, c.update, c.step, c.vel, c.mu, blk, c.A2, c.scale);
   } else {
-    mean_block(p.t.rowloss, p.t.rows, p.t.loss);
+    mean_block(p.rowloss, p.rows, p.loss, p.count);
   }
 }
 
@@ -851,12 +873,28 @@ hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, const WgradPlan &plan, 
   return hipGetLastError();
 }
 
+bool step_tail_takes(const GemmArgs &g) {
+  return g.split_k <= 1 && gemm_is_small(g.M, g.N, g.Kdim) && g.a_m == 1 && g.b_n == 1 && g.c_n == 1 && !g.bias && !g.C_ref &&
+         g.act == ACT_IDENTITY && !g.sm_labels && !g.uniform && !g.sq_ref && (g.A2 == nullptr) == (g.B2 == nullptr);
+}
+
 hipError_t launch_step_tail(const StepTail &t, hipStream_t stream) {
-  if (t.n_reduce < 0 || t.n_reduce > StepTail::kMaxReduce || t.n_colsum < 0 || t.n_colsum > StepTail::kMaxColsum) return hipErrorInvalidValue;
+  if (t.n_reduce < 0 || t.n_reduce > StepTail::kMaxReduce || t.n_colsum < 0 || t.n_colsum > StepTail::kMaxColsum || t.n_gemm < 0 ||
+      t.n_gemm > StepTail::kMaxGemm)
+    return hipErrorInvalidValue;
   StepTailParams p;
-  p.t = t;
+  p.n_reduce = t.n_reduce; p.n_colsum = t.n_colsum; p.n_gemm = t.n_gemm;
+  p.rowloss = t.rowloss; p.rows = t.rows; p.loss = t.loss; p.count = t.count > 0.0 ? t.count : (double)t.rows;
   int jobs = 0, blocks = 0;
+  for (int j = 0; j < t.n_gemm; ++j) {
+    const GemmArgs &g = t.gemm[j];
+    if (!step_tail_takes(g)) return hipErrorInvalidValue;
+    if (!small_gemm::make_params(g, &p.gemm[j])) return hipErrorInvalidValue;
+    p.start[jobs++] = blocks;
+    blocks += ((g.M + small_gemm::kOuterM - 1) / small_gemm::kOuterM) * ((g.N + small_gemm::kOuterN - 1) / small_gemm::kOuterN);
+  }
   for (int j = 0; j < t.n_reduce; ++j) {
+    p.reduce[j] = t.reduce[j];
     const WgradReduceArgs &a = t.reduce[j].a;
     if ((reinterpret_cast<uintptr_t>(a.pos) & 15u) || (a.neg && (reinterpret_cast<uintptr_t>(a.neg) & 15u))) return hipErrorInvalidValue;
     p.group_stride[j] = reduce_group_stride(t.reduce[j].plan);
@@ -865,6 +903,7 @@ hipError_t launch_step_tail(const StepTail &t, hipStream_t stream) {
     blocks += reduce_blocks(a, t.reduce[j].plan);
   }
   for (int j = 0; j < t.n_colsum; ++j) {
+    p.colsum[j] = t.colsum[j];
     p.start[jobs++] = blocks;
     blocks += (t.colsum[j].N + kColsumCols - 1) / kColsumCols;
   }
@@ -873,8 +912,9 @@ hipError_t launch_step_tail(const StepTail &t, hipStream_t stream) {
     blocks += 1;
   }
   if (blocks == 0) return hipSuccess;
-  for (int j = jobs; j < StepTail::kMaxReduce + StepTail::kMaxColsum + 2; ++j) p.start[j] = blocks;
-  hipLaunchKernelGGL(step_tail_kernel, dim3(blocks), dim3(kThreads), 0, stream, p);
+  for (int j = jobs; j < StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 2; ++j) p.start[j] = blocks;
+  if (t.n_gemm == 0) hipLaunchKernelGGL(step_tail_kernel<false>, dim3(blocks), dim3(kThreads), 0, stream, p);
+  else hipLaunchKernelGGL(step_tail_kernel<true>, dim3(blocks), dim3(kThreads), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -202,6 +202,13 @@ struct GemmArgs {
   const int *sm_labels = nullptr;
   float *sm_dz = nullptr, *sm_rowloss = nullptr;
   float sm_scale = 1.0f;
+  // The RBM's epilogues, in the small-product kernel only (strides of Cout): sample = 1[uniform < C];
+  // sq_partial receives the sums of (sq_ref - C)^2 over gemm_small_tiles(M, N) parts of the result.
+  const float *uniform = nullptr; float *sample = nullptr;
+  const float *sq_ref = nullptr; float *sq_partial = nullptr;
+  // Jobs of the closing launch only: C = alpha * (A B - A2 B2), both products with the same strides and sizes.
+  const float *A2 = nullptr, *B2 = nullptr;
+  float alpha = 1.0f;
 };
 int gemm_pick_split_k(int M, int N, int Kdim);
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream);
@@ -218,6 +225,7 @@ bool gemm_is_small(int M, int N, int Kdim);
 bool gemm_prefers_small(const GemmArgs &a);
 bool gemm_fuses_softmax(int M, int N, int Kdim);
 hipError_t launch_gemm_small(const GemmArgs &a, hipStream_t stream);
+size_t gemm_small_tiles(int M, int N);
 
 // Column sums out[n] = sum_m A(m,n) of a row-major [M][N] array; optional update.
 hipError_t launch_colsum(const float *A, int M, int N, float *out,
@@ -252,16 +260,21 @@ hipError_t launch_rbm_visible_stats(const float *v0, const float *v1, int B, int
 
 // ---------------------------------------------------------------------------------------
 // Closing kernel of a training step: the reductions that nothing later in the step waits for
-// (filter-gradient reductions with their updates, dense bias gradients, the mean loss) run as
+// (filter-gradient reductions with their updates, dense bias gradients, small weight-gradient products, the mean loss) run as
 // jobs of ONE launch instead of one tiny dependent kernel each.
 // ---------------------------------------------------------------------------------------
 struct StepTail {
-  static constexpr int kMaxReduce = 8, kMaxColsum = 4;
-  int n_reduce = 0, n_colsum = 0;
+  static constexpr int kMaxReduce = 8, kMaxColsum = 4, kMaxGemm = 4;
+  int n_reduce = 0, n_colsum = 0, n_gemm = 0;
   struct Reduce { WgradReduceArgs a; WgradPlan plan; } reduce[kMaxReduce];
-  struct Colsum { const float *A; int M, N; float *out, *update; float step; float *vel; float mu; } colsum[kMaxColsum];
-  const float *rowloss = nullptr; int rows = 0; float *loss = nullptr;   // optional: *loss = mean(rowloss)
+  // out[n] = scale * sum_m (A - A2)(m, n); A2 may be NULL
+  struct Colsum { const float *A; int M, N; float *out, *update; float step; float *vel; float mu; const float *A2 = nullptr; float scale = 1.0f; } colsum[kMaxColsum];
+  GemmArgs gemm[kMaxGemm];   // small products of the weight-gradient form (A contiguous along m, B along n)
+  // optional: *loss = sum(rowloss[0 .. rows)) / count (count 0: the number of rows)
+  const float *rowloss = nullptr; int rows = 0; float *loss = nullptr; double count = 0.0;
 };
+// Whether a product can be a job of the closing launch.
+bool step_tail_takes(const GemmArgs &g);
 hipError_t launch_step_tail(const StepTail &t, hipStream_t stream);
 
 }  // namespace dllk

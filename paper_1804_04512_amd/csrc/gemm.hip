@@ -831,7 +831,7 @@ __global__ __launch_bounds__(kThreads) void softmax_prob_kernel(const float *log
   for (int j = tid; j < classes; j += kThreads) prob[(long)n * classes + j] = expf(row[j] - m) * inv;
 }
 
-__global__ __launch_bounds__(kThreads) void mean_kernel(const float *v, int count, float *out) { mean_block(v, count, out); }
+__global__ __launch_bounds__(kThreads) void mean_kernel(const float *v, int count, float *out) { mean_block(v, count, out, (double)count); }
 
 constexpr int kStatBlocks = 32;
 
@@ -930,7 +930,7 @@ GemmPlan plan_gemm(const GemmArgs &a) {
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream) {
-  if (a.split_k <= 1 && (gemm_is_small(a.M, a.N, a.Kdim) || a.small_form)) return launch_gemm_small(a, stream);
+  if (a.split_k <= 1 && a.a_k == 1 && (gemm_is_small(a.M, a.N, a.Kdim) || a.small_form)) return launch_gemm_small(a, stream);
   if (a.sm_labels) return hipErrorInvalidValue;   // the fused loss exists in the small-product kernel only
   const GemmPlan g = plan_gemm(a);
   const GemmParams &p = g.p;

@@ -11,17 +11,22 @@ namespace dllk {
 constexpr int kSmallThreads = 256;
 constexpr int kColsumCols = 16, kColsumSlices = kSmallThreads / kColsumCols;
 
-// out[n] = sum_m A[m][n]: 16 columns per workgroup, 16 row slices added in a fixed order
+// out[n] = scale * sum_m (A - A2)[m][n] (A2 may be NULL): 16 columns per workgroup, 16 row slices added in a fixed order
 // (small inputs: many short independent load chains beat few long ones).
 __device__ __forceinline__ void colsum_block(const float *A, int M, int N, float *out, float *update, float step, float *vel,
-                                             float mu, int blk) {
+                                             float mu, int blk, const float *A2 = nullptr, float scale = 1.0f) {
   __shared__ float part[kColsumSlices][kColsumCols + 1];
   const int col = threadIdx.x % kColsumCols, slice = threadIdx.x / kColsumCols;
   const int n = blk * kColsumCols + col;
   float s = 0.0f;
   if (n < N) {
+    if (A2) {
 #pragma unroll 4
-    for (int m = slice; m < M; m += kColsumSlices) s += A[(long)m * N + n];
+      for (int m = slice; m < M; m += kColsumSlices) s += A[(long)m * N + n] - A2[(long)m * N + n];
+    } else {
+#pragma unroll 4
+      for (int m = slice; m < M; m += kColsumSlices) s += A[(long)m * N + n];
+    }
   }
   part[slice][col] = s;
   __syncthreads();
@@ -33,7 +38,7 @@ __device__ __forceinline__ void colsum_block(const float *A, int M, int N, float
 #pragma unroll
       for (int i = 0; i < kColsumSlices / 4; ++i) q[g] += part[g * (kColsumSlices / 4) + i][col];
     }
-    s = (q[0] + q[1]) + (q[2] + q[3]);
+    s = ((q[0] + q[1]) + (q[2] + q[3])) * scale;
     if (out) out[n] = s;
     if (update) update_param(update + n, vel ? vel + n : nullptr, s, step, mu, 0.0f);
   }
@@ -59,13 +64,16 @@ __device__ __forceinline__ float block_reduce(float v, float *sh, bool is_max) {
   return r;
 }
 
-// *out = mean of v[0 .. count)
-__device__ __forceinline__ void mean_block(const float *v, int count, float *out) {
-  __shared__ float sh[kSmallThreads];
-  float s = 0.0f;
-  for (int j = threadIdx.x; j < count; j += kSmallThreads) s += v[j];
-  s = block_reduce(s, sh, false);
-  if (threadIdx.x == 0) *out = s / (float)count;
+// *out = (sum of v[0 .. n)) / count
+__device__ __forceinline__ void mean_block(const float *v, int n, float *out, double count) {
+  __shared__ double sh[kSmallThreads / 64];
+  double s = 0.0;
+  for (int j = threadIdx.x; j < n; j += kSmallThreads) s += (double)v[j];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) *out = (float)(((sh[0] + sh[1]) + (sh[2] + sh[3])) / count);
 }
 
 }  // namespace dllk
