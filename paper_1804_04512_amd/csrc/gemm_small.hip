@@ -34,9 +34,22 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_small_kernel(const SmallParam
 
 }  // namespace
 
-// Products below this many multiply-adds run here; above it the chip can be filled and the
-// persistent kernel's rate matters more than the latency chain.
-bool gemm_is_small(int M, int N, int Kdim) { return (long)M * N * Kdim <= (1L << 27); }
+// Where a product runs here rather than on the persistent kernel (128 x 64 tiles, split-K partials and a
+// reduction launch for products of few tiles).  Up to 1.5 x 2^27 multiply-adds in any case (129 x 1024 x
+// 1024 RBM step: 87 us there, 55 here; but the 128 x 1000 x 2048 logits: 15 + 7 us with the loss behind
+// them there, 27 here).  Up to 2^28 where the shortest extent leaves the persistent kernel's tiles half
+// empty (large-image step at batch 16: 274 against 259 us).  Up to 2^29 where all three are at least 256, i.e.
+// where several rows of its tiles re-read operands (512 x 1000 x 1000 RBM step 184 against 117; but with the
+// 128 x 2048 x 2000 products of a large-image step 370 against 379 in all).  Up to 2^30 where an extent is no
+// multiple of four, which the persistent kernel's 16-byte loads need (500 x 1600 x 1001 RBM step 267
+// against 192).
+bool gemm_is_small(int M, int N, int Kdim) {
+  const long macs = (long)M * N * Kdim;
+  const int least = M < N ? (M < Kdim ? M : Kdim) : (N < Kdim ? N : Kdim);
+  if (((M | N | Kdim) & 3) != 0) return macs <= (1L << 30);
+  if (least >= 256) return macs <= (1L << 29);
+  return macs <= (least <= 64 ? 1L << 28 : 3L << 26);
+}
 
 bool gemm_prefers_small(const GemmArgs &a) {
   if (gemm_is_small(a.M, a.N, a.Kdim)) return true;

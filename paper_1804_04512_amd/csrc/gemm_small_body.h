@@ -251,7 +251,7 @@ __device__ __forceinline__ void tile_product(const SmallParams &p, int mt, int n
 // row tiles and its 8 bytes of B columns n0 + 2 i16 + j of two column tiles (which row of the tile a lane
 // stands for is free as long as the stores know it), so two loads feed eight MFMAs.  64 x 32 outputs per workgroup,
 // the four wavefronts split k in batches of 16; PHASES = 2: the batches of A2 B2, taken off, follow.
-// 784 x 500 over 2 x 100 rows: 15.6 -> @@ us, with the step's column sums beside it.  Bound by the latency of its
+// 784 x 500 over 2 x 100 rows: 15.6 -> 10.4 us, with the step's column sums beside it.  Bound by the latency of its
 // two or three dependent round trips (operands, parameters, store), not by the matrix pipe.
 constexpr int kOuterM = 64, kOuterN = 32;
 constexpr int kOuterRedFloats = 4 * 8 * 64 * 4;
