@@ -215,15 +215,33 @@ dll_status dll_conv_full_bwd(const dll_conv_desc *d, const float *dy, const floa
   return dev(launch_conv_engine(bwd_args(d, dy, y, pool_idx, w, dx), static_cast<hipStream_t>(stream)));
 }
 
+}  // extern "C"
+
+namespace {
+// The Fourier route's scratch: the spectra of the image pairs and filters, then those of their products.
+// Returns the bytes without the last part, which the route can do without (at the old speed).
+size_t carve_fft(const dll_conv_desc *d, void *ws, int lph, int lpw, ConvFftArgs *a, size_t *all) {
+  const size_t F = (size_t)1 << (lph + lpw), pairs = (size_t)((d->N + 1) / 2);   // two batch images per complex image
+  Carver c(ws, 0);
+  a->xf = static_cast<float2 *>(c.take(pairs * d->K * F * sizeof(float2)));
+  a->wf = static_cast<float2 *>(c.take((size_t)d->K * d->C * F * sizeof(float2)));
+  const size_t least = c.used;
+  a->yf = static_cast<float2 *>(c.take(pairs * d->C * F * sizeof(float2)));
+  *all = c.used;
+  return least;
+}
+}  // namespace
+
+extern "C" {
+
 size_t dll_conv_full_fft_workspace_bytes(const dll_conv_desc *d) {
   if (check_desc(d, true, false) != DLL_OK) return 0;
   int lph, lpw;
   if (!conv_fft_plan(out_h(d), out_w(d), d->R, d->S, &lph, &lpw)) return 0;
-  const size_t F = (size_t)1 << (lph + lpw);
-  Carver c(nullptr, 0);
-  c.take((size_t)((d->N + 1) / 2) * d->K * F * sizeof(float2));   // two batch images per complex image
-  c.take((size_t)d->K * d->C * F * sizeof(float2));
-  return c.used;
+  ConvFftArgs a;
+  size_t all;
+  carve_fft(d, nullptr, lph, lpw, &a, &all);
+  return all;
 }
 
 dll_status dll_conv_full_bwd_fft(const dll_conv_desc *d, const float *dy, const float *y, const unsigned char *pool_idx,
@@ -234,18 +252,16 @@ dll_status dll_conv_full_bwd_fft(const dll_conv_desc *d, const float *dy, const 
   if ((const float *)dx == dy || (const float *)dx == y || (const float *)dx == w) return DLL_ERR_SHAPE;
   int lph, lpw;
   if (!conv_fft_plan(out_h(d), out_w(d), d->R, d->S, &lph, &lpw)) return DLL_ERR_UNSUPPORTED;
-  st = check_ws(ws, ws_bytes, dll_conv_full_fft_workspace_bytes(d));
-  if (st != DLL_OK) return st;
-  const size_t F = (size_t)1 << (lph + lpw);
-  Carver c(ws, ws_bytes);
   ConvFftArgs a;
+  size_t all;
+  st = check_ws(ws, ws_bytes, carve_fft(d, ws, lph, lpw, &a, &all));
+  if (st != DLL_OK) return st;
+  if (ws_bytes < all) a.yf = nullptr;
   a.dy = dy; a.y = y; a.idx = pool_idx;
   a.act = flagged_relu(d, y) ? ACT_RELU_FLAGGED : d->act; a.pool = d->pool;
   a.N = d->N; a.K = d->K; a.C = d->C; a.Ho = out_h(d); a.Wo = out_w(d); a.R = d->R; a.S = d->S;
   a.H = d->H; a.W = d->W; a.pad = d->pad;
   a.w = w; a.dx = dx;
-  a.xf = static_cast<float2 *>(c.take((size_t)((d->N + 1) / 2) * d->K * F * sizeof(float2)));
-  a.wf = static_cast<float2 *>(c.take((size_t)d->K * d->C * F * sizeof(float2)));
   return dev(launch_conv_full_fft(a, static_cast<hipStream_t>(stream)));
 }
 

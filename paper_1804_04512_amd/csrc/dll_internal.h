@@ -107,6 +107,7 @@ struct ConvFftArgs {
   const float *w = nullptr;               // [K][C][R][S]
   float *dx = nullptr;                    // [N][C][H][W]
   float2 *xf = nullptr, *wf = nullptr;
+  float2 *yf = nullptr;                   // product spectra, ceil(N/2)*C images (NULL: product and inverse in one kernel)
 };
 bool conv_fft_plan(int Ho, int Wo, int R, int S, int *lph, int *lpw);
 hipError_t launch_conv_full_fft(const ConvFftArgs &a, hipStream_t stream);
