@@ -182,20 +182,24 @@ __device__ __forceinline__ float fft_src_value(const FftFwdArgs &a, int img, int
   return g;
 }
 
-__global__ __launch_bounds__(kFftThreads) void fft2_forward_kernel(const FftFwdArgs a) {
+// Both operands' transforms in one launch: the first `split` workgroups take `x`, the others `w`.
+__global__ __launch_bounds__(kFftThreads) void fft2_forward_kernel(const FftFwdArgs x, const FftFwdArgs w, int split) {
+  const bool second = (int)blockIdx.x >= split;
+  const FftFwdArgs &a = second ? w : x;
+  const int block = second ? (int)blockIdx.x - split : (int)blockIdx.x;
   extern __shared__ float2 fbuf[];   // [PH * PW] + twiddles
   const int F = 1 << (a.lph + a.lpw);
   float2 *tw = fbuf + F;
   // packed: workgroup (pair p, plane k) takes images (2p, k) and (2p + 1, k) of [N][planes]
-  int img = blockIdx.x, img2 = -1;
+  int img = block, img2 = -1;
   if (a.pair_stride > 0) {
-    const int p = blockIdx.x / a.planes, k = blockIdx.x - p * a.planes;
+    const int p = block / a.planes, k = block - p * a.planes;
     img = 2 * p * a.planes + k;
     img2 = img + a.pair_stride < a.count ? img + a.pair_stride : -1;
   }
   make_twiddles(tw);
   const int lph = a.lph, lpw = a.lpw;
-  float2 *dst = a.out + (long)blockIdx.x * F;
+  float2 *dst = a.out + (long)block * F;
   auto from_image = [&](int i, int c) {
     const bool in = c < a.W;
     return make_float2(in ? fft_src_value(a, img, i, c) : 0.0f, in && img2 >= 0 ? fft_src_value(a, img2, i, c) : 0.0f);
@@ -271,7 +275,7 @@ __device__ __forceinline__ void inverse_image(const FftInvArgs &a, float2 *fbuf,
 // every load is 512 contiguous bytes.  The four wavefronts of a workgroup take neighbouring channel tiles of the same
 // pairs and meet in the L1 cache.  Inside the inverse kernel, with a whole spectrum per workgroup, registers
 // allowed tiles of 2 x 2 and the stage was bound by re-reading spectra from L2 (1 GB for 32 pairs x 32
-// channels x 32 maps at 64 x 64; 8 x 8 tiles read 168 MB).  Bound by vector arithmetic now.
+// channels x 32 maps at 64 x 64; 4 x 8 tiles read a third of that).  Product and inverse 128 -> 35 + 16 us.
 template <int PT, int CT>
 __global__ __launch_bounds__(kFftThreads) void fft2_product_kernel(const FftInvArgs a, int ctiles, int tiles) {
   const int F = 1 << (a.lph + a.lpw), lane = threadIdx.x & 63;
@@ -436,26 +440,26 @@ hipError_t launch_conv_full_fft(const ConvFftArgs &g, hipStream_t stream) {
   x.pair_stride = g.K; x.planes = g.K;
   x.out = g.xf;
   const int pairs = (g.N + 1) / 2;
-  hipLaunchKernelGGL(fft2_forward_kernel, dim3(pairs * g.K), dim3(kFftThreads), lds, stream, x);
   FftFwdArgs f;
   f.src = g.w; f.src_y = nullptr; f.src_idx = nullptr;
   f.src_dz = 0; f.src_act = ACT_IDENTITY; f.src_pool = 1;
   f.count = g.K * g.C; f.H = g.R; f.W = g.S; f.lph = lph; f.lpw = lpw;
   f.pair_stride = 0; f.planes = 1;
   f.out = g.wf;
-  hipLaunchKernelGGL(fft2_forward_kernel, dim3(f.count), dim3(kFftThreads), lds, stream, f);
+  hipLaunchKernelGGL(fft2_forward_kernel, dim3(pairs * g.K + f.count), dim3(kFftThreads), lds, stream, x, f, pairs * g.K);
   FftInvArgs v;
   v.xf = g.xf; v.wf = g.wf; v.N = g.N; v.K = g.K; v.C = g.C; v.lph = lph; v.lpw = lpw;
   v.H = g.H; v.W = g.W; v.off = g.pad; v.out = g.dx;
   v.yf = g.yf;
   if (g.yf) {
-    // 8 x 8 tiles once they give every SIMD of the chip a wavefront, 4 x 4 ones below
-    const int chunks = (F + 63) / 64;
-    const int c8 = (g.C + 7) / 8, t8 = c8 * ((pairs + 7) / 8), c4 = (g.C + 3) / 4, t4 = c4 * ((pairs + 3) / 4);
-    if ((long)t8 * chunks >= 4L * chip().cus)
-      hipLaunchKernelGGL((fft2_product_kernel<8, 8>), dim3(chunks, (t8 + 3) / 4), dim3(kFftThreads), 0, stream, v, c8, t8);
+    // 4 x 8 tiles once they give every SIMD of the chip two wavefronts (one wavefront of 8 x 8 tiles moves
+    // less but waits out every k's loads: 38 against 35 us at 32 x 32 x 32 maps), 4 x 4 ones below
+    const int chunks = (F + 63) / 64, prows = (pairs + 3) / 4;
+    const int c8 = (g.C + 7) / 8, c4 = (g.C + 3) / 4;
+    if ((long)c8 * prows * chunks >= 8L * chip().cus)
+      hipLaunchKernelGGL((fft2_product_kernel<4, 8>), dim3(chunks, (c8 * prows + 3) / 4), dim3(kFftThreads), 0, stream, v, c8, c8 * prows);
     else
-      hipLaunchKernelGGL((fft2_product_kernel<4, 4>), dim3(chunks, (t4 + 3) / 4), dim3(kFftThreads), 0, stream, v, c4, t4);
+      hipLaunchKernelGGL((fft2_product_kernel<4, 4>), dim3(chunks, (c4 * prows + 3) / 4), dim3(kFftThreads), 0, stream, v, c4, c4 * prows);
     hipLaunchKernelGGL(fft2_inverse_kernel, dim3(pairs * g.C), dim3(kFftThreads), lds, stream, v);
     return hipGetLastError();
   }

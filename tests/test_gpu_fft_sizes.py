@@ -1,5 +1,5 @@
 """The Fourier route of the full convolution over its padded sides (every power of two from 2 to 64, equal and
-not), the edges of the product kernel's 8 x 8 and 4 x 4 tiles of image pairs and channels, odd batches, a
+not), the edges of the product kernel's 4 x 8 and 4 x 4 tiles of image pairs and channels, odd batches, a
 single map, and a workspace that holds no product spectra (the route in two launches instead of three)."""
 import numpy as np
 import pytest
