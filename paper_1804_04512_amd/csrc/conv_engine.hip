@@ -1011,9 +1011,13 @@ hipError_t launch_conv_engine(const ConvEngineArgs &a, hipStream_t stream) {
   const int nt = a.Kout <= 16 ? 1 : (a.Kout <= 32 ? 2 : 3);
   const long tiles16 = (long)a.N * ((a.Wout + kTileW - 1) / kTileW) * ((a.Hout + 15) / 16) * ((a.Kout + nt * 16 - 1) / (nt * 16));
   const bool small = a.Hout <= 8 || tiles16 < 512;
-  // very few output channels: the banded-filter kernel wins when its share of real products,
-  // S of every 4*ceil((16+S-1)/4) window columns, clearly beats Kout of 16 channel columns
-  if (a.Kout <= 3 && a.Kout * (4 * ((16 + a.S - 1 + 3) / 4)) * 3 < 16 * a.S * 2 && conv_fewout_applies(a))
+  // very few output channels: the banded-filter kernel takes Kout * ceil((16 + S - 1) / 4) MFMA steps per
+  // channel and filter row for 256 pixels where the channel columns of the engine take 4 * S (one to three
+  // of whose 16 columns are real): 16 x 2 x 45 x 45 behind 20 maps, 3x3: both backward passes 38 -> 20 us; but three channels, 3x3,
+  // 64 x 64 maps: 32 -> 43.  Two or three channels of a layer the 3x3 instance takes stay with it until the filter
+  // rows are long.
+  const int few_steps = a.Kout * ((16 + a.S - 1 + 3) / 4);
+  if (a.Kout <= 3 && few_steps < 4 * a.S && conv_fewout_applies(a) && (few_steps * 3 < 8 * a.S || conv3x3c16_pick(a).NT == 0))
     return launch_conv_fewout(a, stream);
   if (conv_fwd_fewch_applies(a)) return launch_conv_fwd_fewch(a, stream);
   if (conv_wino_stream_applies(a) || conv_wino_stream_bwd_applies(a)) return launch_conv_wino_stream(a, stream);

@@ -12,9 +12,13 @@
 // the compact filter rows in LDS (each row padded with zeros on both sides), so the banded matrix
 // is never stored.
 //
-// One workgroup = one 16x16 output tile of one image, all (<= 3) output channels.  Source
-// channels are staged in rounds of kRch; inside a round each of the four wavefronts multiplies
-// its own kRch/4 channels, and the four partial tiles are added in a fixed order at the end.
+// One workgroup = one 16x16 output tile of one image, all (<= 3) output channels.  The wavefronts split the
+// source channels: each stages one channel's window and filter rows in LDS of its own, so nothing in the loop
+// waits for a workgroup, and has the next channel's values on their way while it multiplies.  The
+// partial tiles are added in wavefront order at the end.  Which element of a plane a lane moves, and to where, is
+// the same for every channel and worked out once.  (The form before staged eight channels at a time for
+// the whole workgroup, three divisions by run-time sizes per element and nothing in flight during the
+// products: 64 x 40 maps of 20 x 20 back through 9 x 9 filters 45 -> 20 us, of which the products are 7.)
 #include "dll_internal.h"
 
 namespace dllk {
@@ -22,12 +26,12 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-constexpr int kThreads = 256;
-constexpr int kRch = 8;            // source channels per staging round
 constexpr int kRsx = 34;           // LDS row stride of the window: 2 mod 32 -> conflict-free A reads
 constexpr int kSteps = 8;          // MFMA steps a window row can have (window <= 32 columns: S <= 17)
 constexpr int kRoww = 15 + 4 * kSteps + 1;   // filter row: 15 zeros, the taps, zeros up to the last column a lane reads
-constexpr int kStage = 4;          // staging loads per thread and batch
+constexpr int kTapSlots = 7;       // filter values per lane and channel: at most 3 x 144
+constexpr int kPlaneSlots = 32;    // window values per lane and channel at most
+constexpr unsigned kOob = 0x80000000u;   // byte offset past any plane: the range check returns zero
 
 struct FewoutParams {
   ConvEngineArgs a;
@@ -35,7 +39,7 @@ struct FewoutParams {
   int rows;        // window rows = 16 + R - 1
   int winp;        // window columns staged = 4 * wsteps >= 16 + S - 1
   int wsteps;
-  int rounds;
+  int inv_winp;    // ceil(65536 / winp): exact division of a plane's element numbers
 };
 
 __device__ __forceinline__ float act_apply(int act, float z) {
@@ -44,112 +48,122 @@ __device__ __forceinline__ float act_apply(int act, float z) {
   return z;
 }
 
-template <int KO>
-__global__ __launch_bounds__(kThreads) void conv_fewout_kernel(const FewoutParams p) {
+// NS: window values per lane and channel; POOL: the source is dz behind 2x2 pooling
+template <int KO, int NS, int WAVES, bool POOL>
+__global__ __launch_bounds__(WAVES * 64) void conv_fewout_kernel(const FewoutParams p) {
   extern __shared__ float lds[];
   const ConvEngineArgs &a = p.a;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, kq = lane >> 4;
-  const int psx = p.rows * kRsx;
-  float *xs = lds;                    // [kRch][rows][kRsx]
-  float *wf = xs + kRch * psx;        // [KO][kRch][R][kRoww]
+  const int psx = p.rows * kRsx, wrows = KO * a.R * kRoww;
+  float *xs = lds + wave * (psx + wrows);   // [rows][kRsx], this wavefront's
+  float *wf = xs + psx;                     // [KO][R][kRoww]
   const int bid = blockIdx.x;
   const int tx = bid % p.tiles_x, ty = (bid / p.tiles_x) % p.tiles_y, n = bid / (p.tiles_x * p.tiles_y);
   const int i0 = ty * 16, j0 = tx * 16;
   const int RSf = a.R * a.S;
-  const bool need_y = a.src_dz && a.src_act != ACT_IDENTITY;
+  const int Wsrc = POOL ? a.Win >> 1 : a.Win, HW = (POOL ? a.Hin >> 1 : a.Hin) * Wsrc;   // of a plane as it is stored
+  const bool need_y = a.src_dz && (a.src_act == ACT_SIGMOID || a.src_act == ACT_RELU);
 
-  // the zero borders of the filter rows are written once; the rounds rewrite the taps only
-  for (int e = tid; e < KO * kRch * a.R * kRoww; e += kThreads) wf[e] = 0.0f;
+  // the lane's window elements: byte offset inside a source plane (out of range: padding), LDS offset
+  const int plane = p.rows * p.winp;
+  int voff[NS], dst[NS];
+  unsigned char want[POOL ? NS : 1], fv[POOL ? NS : 1];   // position inside the pooling window; the window's byte
+#pragma unroll
+  for (int u = 0; u < NS; ++u) {
+    const int e = lane + 64 * u;
+    const int y = (e * p.inv_winp) >> 16, x = e - y * p.winp;
+    const int gi = i0 - a.pad_h + y, gj = j0 - a.pad_w + x;
+    voff[u] = (e < plane && gi >= 0 && gi < a.Hin && gj >= 0 && gj < a.Win) ? (POOL ? 4 * ((gi >> 1) * Wsrc + (gj >> 1)) : 4 * (gi * a.Win + gj)) : (int)kOob;
+    dst[u] = e < plane ? y * kRsx + x : -1;
+    if (POOL) want[u] = ((gi & 1) << 1) | (gj & 1);
+  }
+  // the lane's filter taps: byte offset from the channel's first, LDS offset
+  int woff[kTapSlots], wdst[kTapSlots];
+  const int taps = KO * RSf;
+  for (int e = lane; e < wrows; e += 64) wf[e] = 0.0f;   // the zero borders stay, the taps are rewritten
+#pragma unroll
+  for (int u = 0; u < kTapSlots; ++u) {
+    const int e = lane + 64 * u;
+    woff[u] = (int)kOob;
+    wdst[u] = -1;
+    if (64 * u >= taps || e >= taps) continue;
+    const int c = e / RSf, rs = e - c * RSf, r = rs / a.S, s = rs - r * a.S;
+    woff[u] = 4 * (a.w_flip ? c * RSf + (a.R - 1 - r) * a.S + (a.S - 1 - s) : c * a.Cin * RSf + rs);
+    wdst[u] = (c * a.R + r) * kRoww + 15 + s;
+  }
+
+  float gv[NS], yv[NS], tv[kTapSlots];
+  auto load_channel = [&](int ci) __attribute__((always_inline)) {
+    const long base = (long)(n * a.Cin + ci) * HW;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.src + base), 0, 4 * HW, 0x00020000);
+#pragma unroll
+    for (int u = 0; u < NS; ++u) gv[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff[u], 0, 0));
+    if (need_y) {
+      const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.src_y + base), 0, 4 * HW, 0x00020000);
+#pragma unroll
+      for (int u = 0; u < NS; ++u) yv[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ry, voff[u], 0, 0));
+    }
+    if constexpr (POOL) {
+      const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(a.src_idx + base), 0, HW, 0x00020000);
+#pragma unroll
+      for (int u = 0; u < NS; ++u) fv[u] = __builtin_amdgcn_raw_buffer_load_b8(ri, (int)((unsigned)voff[u] >> 2), 0, 0);
+    }
+    const float *w0 = a.w + (long)ci * (a.w_flip ? KO * RSf : RSf);
+    const int wbytes = a.w_flip ? 4 * taps : 4 * (((KO - 1) * a.Cin + 1) * RSf);   // to the end of the channel's last filter
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(w0), 0, wbytes, 0x00020000);
+#pragma unroll
+    for (int u = 0; u < kTapSlots; ++u)
+      if (64 * u < taps) tv[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rw, woff[u], 0, 0));
+  };
+  auto store_channel = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      float v = gv[u];
+      if (need_y) {   // dz = dy * act'(y), from the layer output
+        if (a.src_act == ACT_SIGMOID) v *= yv[u] * (1.0f - yv[u]);
+        else v = yv[u] > 0.0f ? v : 0.0f;
+      }
+      if constexpr (POOL) {   // the gradient sits at the recorded position
+        const bool off = (fv[u] & kIdxPosMask) != want[u] || (a.src_act == ACT_RELU_FLAGGED && (fv[u] & kIdxInactive));
+        v = off ? 0.0f : v;
+      }
+      if (dst[u] >= 0) xs[dst[u]] = v;
+    }
+#pragma unroll
+    for (int u = 0; u < kTapSlots; ++u)
+      if (64 * u < taps && wdst[u] >= 0) wf[wdst[u]] = tv[u];
+  };
 
   floatx4 acc[KO];
 #pragma unroll
   for (int c = 0; c < KO; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  for (int round = 0; round < p.rounds; ++round) {
-    const int c0 = round * kRch;
-    __syncthreads();   // the previous round's readers are done (first round: the zero fill is complete)
-    // Staging works in batches: all addresses, then all loads, unconditionally and from clamped
-    // addresses (element 0 stands in for padding and for channels that do not exist), then the
-    // selects and the LDS stores; a load behind a per-lane branch would be waited for on its own.
-    // ---- filter taps of the round's channels: wf[c][cl][r][15 + s]
+  if (wave < a.Cin) load_channel(wave);
+  for (int ci = wave; ci < a.Cin; ci += WAVES) {
+    store_channel();
+    if (ci + WAVES < a.Cin) load_channel(ci + WAVES);   // in flight during the products
+    // LDS of one wavefront: its accesses are served in order, only the compiler must keep them so
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // ---- MFMA over the channel's filter rows; the fragments of the next row are read from LDS while the
+    // current one is multiplied.  A: lane (row i16, k = kq) reads window column 4*step + kq of row
+    // i16 + r; B: lane (column i16, k = kq) reads tap 4*step + kq - i16 of the padded filter row (zero
+    // outside the S taps).
     {
-      const int total = KO * kRch * RSf;
-      for (int e0 = tid; e0 < total; e0 += kStage * kThreads) {
-        float v[kStage];
-        bool ok[kStage];
-        int dst[kStage];
-#pragma unroll
-        for (int u = 0; u < kStage; ++u) {
-          const int e = min(e0 + u * kThreads, total - 1);
-          const int s = e % a.S, q = e / a.S;
-          const int r = q % a.R, q2 = q / a.R;
-          const int cl = q2 % kRch, c = q2 / kRch;
-          const int ci = c0 + cl;
-          ok[u] = ci < a.Cin;
-          const int o = a.w_flip ? ((ci * a.Kout + c) * a.R + (a.R - 1 - r)) * a.S + (a.S - 1 - s)
-                                 : ((c * a.Cin + ci) * a.R + r) * a.S + s;
-          v[u] = a.w[ok[u] ? o : 0];
-          dst[u] = ((c * kRch + cl) * a.R + r) * kRoww + 15 + s;
-        }
-#pragma unroll
-        for (int u = 0; u < kStage; ++u)
-          if (e0 + u * kThreads < total) wf[dst[u]] = ok[u] ? v[u] : 0.0f;
-      }
-    }
-    // ---- source window of the round's channels: xs[cl][y][x] = srcpad(c0 + cl, i0 - pad + y, j0 - pad + x)
-    {
-      const int total = kRch * p.rows * p.winp;
-      for (int e0 = tid; e0 < total; e0 += kStage * kThreads) {
-        float gv[kStage], yv[kStage];
-        bool ok[kStage];
-        int dst[kStage];
-#pragma unroll
-        for (int u = 0; u < kStage; ++u) {
-          const int e = min(e0 + u * kThreads, total - 1);
-          const int x = e % p.winp, q = e / p.winp;
-          const int y = q % p.rows, cl = q / p.rows;
-          const int gi = i0 - a.pad_h + y, gj = j0 - a.pad_w + x, ci = c0 + cl;
-          ok[u] = ci < a.Cin && gi >= 0 && gi < a.Hin && gj >= 0 && gj < a.Win;
-          const int o = ok[u] ? ((n * a.Cin + ci) * a.Hin + gi) * a.Win + gj : 0;
-          gv[u] = a.src[o];
-          yv[u] = need_y ? a.src_y[o] : 0.0f;
-          dst[u] = cl * psx + y * kRsx + x;
-        }
-#pragma unroll
-        for (int u = 0; u < kStage; ++u) {
-          if (e0 + u * kThreads >= total) continue;
-          float v = gv[u];
-          if (need_y) {   // dz = dy * act'(y), from the layer output
-            if (a.src_act == ACT_SIGMOID) v *= yv[u] * (1.0f - yv[u]);
-            else v = yv[u] > 0.0f ? v : 0.0f;
-          }
-          xs[dst[u]] = ok[u] ? v : 0.0f;
-        }
-      }
-    }
-    __syncthreads();
-    // ---- MFMA over (channel, filter row) pairs of this wavefront's channels; the fragments of the
-    // next pair are read from LDS while the current pair is multiplied.  A: lane (row i16, k = kq)
-    // reads window column 4*step + kq of row i16 + r; B: lane (column i16, k = kq) reads tap
-    // 4*step + kq - i16 of the padded filter row (zero outside the S taps).
-    {
-      constexpr int CPW = kRch / 4;   // channels per wavefront
-      const int npairs = CPW * a.R;
       float afA[kSteps], afB[kSteps], bfA[KO][kSteps], bfB[KO][kSteps];
-      auto load_pair = [&](int cc, int r, float (&af)[kSteps], float (&bf)[KO][kSteps]) __attribute__((always_inline)) {
-        const int cl = wave * CPW + cc;
-        const float *ap = xs + cl * psx + (i16 + r) * kRsx + kq;
+      auto load_row = [&](int r, float (&af)[kSteps], float (&bf)[KO][kSteps]) __attribute__((always_inline)) {
+        const float *ap = xs + (i16 + r) * kRsx + kq;
 #pragma unroll
         for (int st = 0; st < kSteps; ++st) af[st] = ap[4 * st];
 #pragma unroll
         for (int c = 0; c < KO; ++c) {
-          const float *bp = wf + ((c * kRch + cl) * a.R + r) * kRoww + 15 + kq - i16;
+          const float *bp = wf + (c * a.R + r) * kRoww + 15 + kq - i16;
 #pragma unroll
           for (int st = 0; st < kSteps; ++st) bf[c][st] = bp[4 * st];
         }
       };
-      auto mfma_pair = [&](const float (&af)[kSteps], const float (&bf)[KO][kSteps]) __attribute__((always_inline)) {
+      auto mfma_row = [&](const float (&af)[kSteps], const float (&bf)[KO][kSteps]) __attribute__((always_inline)) {
 #pragma unroll
         for (int st = 0; st < kSteps; ++st) {
           if (st < p.wsteps) {
@@ -158,29 +172,23 @@ __global__ __launch_bounds__(kThreads) void conv_fewout_kernel(const FewoutParam
           }
         }
       };
-      int cc = 0, r = 0;   // the pair whose fragments are loaded next
-      auto advance = [&]() __attribute__((always_inline)) {
-        if (++r == a.R) { r = 0; ++cc; }
-        if (cc == CPW) { cc = CPW - 1; r = a.R - 1; }   // past the end: re-read the last pair (not multiplied)
-      };
-      load_pair(cc, r, afA, bfA);
-      advance();
-      for (int t = 0; t < npairs; t += 2) {
-        load_pair(cc, r, afB, bfB);
-        advance();
+      load_row(0, afA, bfA);
+      for (int r = 0; r < a.R; r += 2) {   // a row past the last re-reads it and is not multiplied
+        load_row(min(r + 1, a.R - 1), afB, bfB);
         __builtin_amdgcn_sched_barrier(0);
-        mfma_pair(afA, bfA);
+        mfma_row(afA, bfA);
         __builtin_amdgcn_sched_barrier(0);
-        load_pair(cc, r, afA, bfA);
-        advance();
+        load_row(min(r + 2, a.R - 1), afA, bfA);
         __builtin_amdgcn_sched_barrier(0);
-        if (t + 1 < npairs) mfma_pair(afB, bfB);
+        if (r + 1 < a.R) mfma_row(afB, bfB);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 
-  // ---- the four wavefronts' partial tiles, added in wavefront order, then bias, activation, store.
+  // ---- the wavefronts' partial tiles, added in wavefront order, then bias, activation, store.
   // Lane holds D[row 4*kq + v][column i16].
   __syncthreads();
   float *red = lds;   // [wave][KO][lane][4]
@@ -193,7 +201,7 @@ __global__ __launch_bounds__(kThreads) void conv_fewout_kernel(const FewoutParam
     for (int c = 0; c < KO; ++c) {
       float4 s = *reinterpret_cast<const float4 *>(red + ((0 * KO + c) * 64 + lane) * 4);
 #pragma unroll
-      for (int w = 1; w < 4; ++w) {
+      for (int w = 1; w < WAVES; ++w) {
         const float4 t = *reinterpret_cast<const float4 *>(red + ((w * KO + c) * 64 + lane) * 4);
         s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
       }
@@ -209,10 +217,34 @@ __global__ __launch_bounds__(kThreads) void conv_fewout_kernel(const FewoutParam
   }
 }
 
-size_t fewout_lds_bytes(const ConvEngineArgs &a, int rows) {
-  const size_t stage = sizeof(float) * ((size_t)kRch * rows * kRsx + (size_t)a.Kout * kRch * a.R * kRoww);
-  const size_t red = sizeof(float) * 4 * (size_t)a.Kout * 64 * 4;
+size_t fewout_lds_bytes(const ConvEngineArgs &a, int waves) {
+  const size_t stage = sizeof(float) * waves * ((size_t)(16 + a.R - 1) * kRsx + (size_t)a.Kout * a.R * kRoww);
+  const size_t red = sizeof(float) * waves * (size_t)a.Kout * 64 * 4;
   return stage > red ? stage : red;
+}
+inline int fewout_winp(const ConvEngineArgs &a) { return 4 * ((16 + a.S - 1 + 3) / 4); }
+
+template <int KO, int NS>
+hipError_t launch_fewout_t(const FewoutParams &p, unsigned blocks, int waves, hipStream_t stream) {
+  const size_t lds = fewout_lds_bytes(p.a, waves);
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * waves), lds, stream, p);
+    return hipGetLastError();
+  };
+  // (the largest window's pooled form needs more registers than eight wavefronts leave: the launcher asks for four)
+  if constexpr (NS == kPlaneSlots) {
+    if (p.a.src_dz && p.a.src_pool == 2) return launch(conv_fewout_kernel<KO, NS, 4, true>);
+  } else {
+    if (p.a.src_dz && p.a.src_pool == 2) return waves == 8 ? launch(conv_fewout_kernel<KO, NS, 8, true>) : launch(conv_fewout_kernel<KO, NS, 4, true>);
+  }
+  return waves == 8 ? launch(conv_fewout_kernel<KO, NS, 8, false>) : launch(conv_fewout_kernel<KO, NS, 4, false>);
+}
+template <int KO>
+hipError_t launch_fewout_k(const FewoutParams &p, unsigned blocks, int waves, hipStream_t stream) {
+  const int slots = (p.rows * p.winp + 63) / 64;
+  if (slots <= 7) return launch_fewout_t<KO, 7>(p, blocks, waves, stream);    // 5x5 filters and smaller
+  if (slots <= 12) return launch_fewout_t<KO, 12>(p, blocks, waves, stream);
+  return launch_fewout_t<KO, kPlaneSlots>(p, blocks, waves, stream);
 }
 
 }  // namespace
@@ -220,9 +252,11 @@ size_t fewout_lds_bytes(const ConvEngineArgs &a, int rows) {
 bool conv_fewout_applies(const ConvEngineArgs &a) {
   if (a.Kout > 3 || a.pool != 1 || a.sample || a.out_pool) return false;
   if (a.act != ACT_IDENTITY && a.act != ACT_SIGMOID && a.act != ACT_RELU) return false;
-  if (a.src_dz && (a.src_pool != 1 || (a.src_act != ACT_IDENTITY && a.src_act != ACT_SIGMOID && a.src_act != ACT_RELU))) return false;
-  if (16 + a.S - 1 > 4 * kSteps) return false;
-  return fewout_lds_bytes(a, 16 + a.R - 1) <= 64 * 1024;
+  if (a.src_dz && a.src_pool != 2 && a.src_act != ACT_IDENTITY && a.src_act != ACT_SIGMOID && a.src_act != ACT_RELU) return false;
+  if (16 + a.S - 1 > 4 * kSteps || (16 + a.R - 1) * fewout_winp(a) > 64 * kPlaneSlots || a.Kout * a.R * a.S > 64 * kTapSlots) return false;
+  // 32-bit byte offsets inside a plane and a channel's filters
+  if (4L * a.Hin * a.Win >= (long)kOob || 4L * a.Kout * a.Cin * a.R * a.S >= (long)kOob) return false;
+  return fewout_lds_bytes(a, 4) <= 64 * 1024;
 }
 
 hipError_t launch_conv_fewout(const ConvEngineArgs &a, hipStream_t stream) {
@@ -231,20 +265,20 @@ hipError_t launch_conv_fewout(const ConvEngineArgs &a, hipStream_t stream) {
   p.tiles_x = (a.Wout + 15) / 16;
   p.tiles_y = (a.Hout + 15) / 16;
   p.rows = 16 + a.R - 1;
-  p.wsteps = (16 + a.S - 1 + 3) / 4;
-  p.winp = 4 * p.wsteps;
-  p.rounds = (a.Cin + kRch - 1) / kRch;
+  p.winp = fewout_winp(a);
+  p.wsteps = p.winp / 4;
+  p.inv_winp = (65536 + p.winp - 1) / p.winp;
   const long blocks = (long)a.N * p.tiles_x * p.tiles_y;
   if (blocks <= 0 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  const size_t lds = fewout_lds_bytes(a, p.rows);
-  const dim3 grid((unsigned)blocks);
+  // eight wavefronts a tile halve the chain of channels each walks, as long as the tiles alone leave SIMDs idle
+  const bool huge = a.src_dz && a.src_pool == 2 && p.rows * p.winp > 64 * 12;
+  const int waves = !huge && a.Cin > 4 && blocks < 4L * chip().cus && fewout_lds_bytes(a, 8) <= 64 * 1024 ? 8 : 4;
   switch (a.Kout) {
-    case 1: hipLaunchKernelGGL(conv_fewout_kernel<1>, grid, dim3(kThreads), lds, stream, p); break;
-    case 2: hipLaunchKernelGGL(conv_fewout_kernel<2>, grid, dim3(kThreads), lds, stream, p); break;
-    case 3: hipLaunchKernelGGL(conv_fewout_kernel<3>, grid, dim3(kThreads), lds, stream, p); break;
+    case 1: return launch_fewout_k<1>(p, (unsigned)blocks, waves, stream);
+    case 2: return launch_fewout_k<2>(p, (unsigned)blocks, waves, stream);
+    case 3: return launch_fewout_k<3>(p, (unsigned)blocks, waves, stream);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace dllk
