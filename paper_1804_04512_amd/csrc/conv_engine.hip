@@ -36,7 +36,7 @@ struct EngineGeom {
   int KC, KS;        // padded taps per chunk (multiple of 4), MFMA steps per chunk
   int tiles_x, tiles_y;
   int kgroups;       // groups of NT*16 output channels (gridDim.y)
-  int jw_log;        // generic kernel: log2 of the filter columns staged per N-tile (16, or fewer when Kout is small)
+  int cw_log;        // generic kernel: log2 of the next power of two of CC
   unsigned src_bytes; // 3x3 instance: bytes of the source tensor (below 2 GiB)
   int pack3;          // 3x3 instance, three input channels: the 27 taps run as 7 MFMA steps, not 9
 };
@@ -89,9 +89,10 @@ __device__ __forceinline__ void lane_bias(const ConvEngineArgs &a, int ko0, int 
 }
 
 // Epilogue shared by the engine kernels.  Lane owns output channel ko0+16nt+i16, window column
-// 4*kq+mt of the tile, window row wave*RP+rp; acc[..][v] is window position v = 2a+b.
-template <int NT, int RP, int ACT, int POOL>
-__device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floatx4 (&acc)[RP][4][NT], const float (&bias)[NT],
+// MT*kq+mt of the tile, window row wave*RP+rp; acc[..][v] is window position v = 2a+b.
+// AHEAD: the sampling epilogue asks for its uniform numbers before their first use (registers the 3x3 instances lack).
+template <int NT, int RP, int ACT, int POOL, int MT = 4, bool AHEAD = false>
+__device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floatx4 (&acc)[RP][MT][NT], const float (&bias)[NT],
                                                 int n, int ko0, int oy0, int ox0, int wave, int i16, int kq) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -101,14 +102,14 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
 #pragma unroll
     for (int rp = 0; rp < RP; ++rp) {
       const int py = (oy0 >> 1) + wave * RP + rp;   // window row (pre-pool rows 2py, 2py+1)
-      const int px0 = (ox0 >> 1) + 4 * kq;          // first of the lane's 4 window columns
+      const int px0 = (ox0 >> 1) + MT * kq;         // first of the lane's MT window columns
       if (2 * py >= a.Hout) continue;
       if (POOL == 2) {
         const int Hp = a.Hout >> 1, Wp = a.Wout >> 1;
-        float yv[4];
-        unsigned char iv[4];
+        float yv[MT];
+        unsigned char iv[MT];
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
+        for (int mt = 0; mt < MT; ++mt) {
           const floatx4 z = acc[rp][mt][nt];
           float m = z[0];
           int arg = 0;
@@ -119,22 +120,38 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
           iv[mt] = (unsigned char)(arg | ((ACT == ACT_RELU && !(yv[mt] > 0.0f)) ? kIdxInactive : 0));
         }
         const int o = ((n * a.Kout + ko) * Hp + py) * Wp + px0;
-        if (px0 + 3 < Wp && (Wp & 3) == 0) {
-          *reinterpret_cast<float4 *>(a.out + o) = make_float4(yv[0], yv[1], yv[2], yv[3]);
-          if (a.out_idx) *reinterpret_cast<uchar4 *>(a.out_idx + o) = make_uchar4(iv[0], iv[1], iv[2], iv[3]);
-        } else {
+        bool whole = false;
+        if constexpr (MT == 4) {
+          whole = px0 + 3 < Wp && (Wp & 3) == 0;
+          if (whole) {
+            *reinterpret_cast<float4 *>(a.out + o) = make_float4(yv[0], yv[1], yv[2], yv[3]);
+            if (a.out_idx) *reinterpret_cast<uchar4 *>(a.out_idx + o) = make_uchar4(iv[0], iv[1], iv[2], iv[3]);
+          }
+        }
+        if (!whole) {
 #pragma unroll
-          for (int mt = 0; mt < 4; ++mt)
+          for (int mt = 0; mt < MT; ++mt)
             if (px0 + mt < Wp) {
               a.out[o + mt] = yv[mt];
               if (a.out_idx) a.out_idx[o + mt] = iv[mt];
             }
         }
       } else {
-        // the lane's four windows: unit outputs pr[mt][2a+b] and, for the sampling epilogues, their states
-        floatx4 pr[4], sm[4] = {};
+        // the uniform numbers of the lane's windows, all of them ahead of the first use and from clamped addresses
+        // (a load beside its use would be waited for on its own, one row of one channel group after the other)
+        float uh[2][2 * MT];
+        if (AHEAD && a.sample && ACT != ACT_PMP) {
+          const int plane_o = (n * a.Kout + ko) * a.Hout * a.Wout;
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
+          for (int wa2 = 0; wa2 < 2; ++wa2)
+#pragma unroll
+            for (int e = 0; e < 2 * MT; ++e)
+              uh[wa2][e] = a.uniform[plane_o + min(2 * py + wa2, a.Hout - 1) * a.Wout + min(2 * px0 + e, a.Wout - 1)];
+        }
+        // the lane's windows: unit outputs pr[mt][2a+b] and, for the sampling epilogues, their states
+        floatx4 pr[MT], sm[MT] = {};
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
           if (ACT == ACT_PMP) {
             pr[mt] = pmp_block(acc[rp][mt][nt], bv);
           } else {
@@ -147,13 +164,13 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
           // pooling unit's probability is the sum of its block
           const int Hp = a.Hout >> 1, Wp = a.Wout >> 1;
           const int ob = ((n * a.Kout + ko) * Hp + py) * Wp + px0;
-          float ub[4];   // the blocks' uniform numbers, loaded together from clamped addresses
+          float ub[MT];   // the blocks' uniform numbers, loaded together from clamped addresses
           if (a.sample) {
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) ub[mt] = a.uniform[ob - px0 + min(px0 + mt, Wp - 1)];   // stays inside the row
+            for (int mt = 0; mt < MT; ++mt) ub[mt] = a.uniform[ob - px0 + min(px0 + mt, Wp - 1)];   // stays inside the row
           }
 #pragma unroll
-          for (int mt = 0; mt < 4; ++mt) {
+          for (int mt = 0; mt < MT; ++mt) {
             if (px0 + mt >= Wp) continue;
             if (a.out_pool) a.out_pool[ob + mt] = (pr[mt][0] + pr[mt][1]) + (pr[mt][2] + pr[mt][3]);
             if (a.sample) {
@@ -177,41 +194,44 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
           if (oy >= a.Hout) continue;
           const int ox = 2 * px0;
           const int o = ((n * a.Kout + ko) * a.Hout + oy) * a.Wout + ox;
-          float yv[8], sv[8];
+          float yv[2 * MT], sv[2 * MT];
 #pragma unroll
-          for (int mt = 0; mt < 4; ++mt) {
+          for (int mt = 0; mt < MT; ++mt) {
             yv[2 * mt] = pr[mt][2 * wa2];
             yv[2 * mt + 1] = pr[mt][2 * wa2 + 1];
             if (ACT == ACT_PMP) { sv[2 * mt] = sm[mt][2 * wa2]; sv[2 * mt + 1] = sm[mt][2 * wa2 + 1]; }
           }
-          if (ox + 7 < a.Wout && (a.Wout & 3) == 0) {
+          bool whole = false;
+          if constexpr (MT == 4) whole = ox + 7 < a.Wout && (a.Wout & 3) == 0;
+          if (whole) {
+            if constexpr (MT == 4) {
             *reinterpret_cast<float4 *>(a.out + o) = make_float4(yv[0], yv[1], yv[2], yv[3]);
             *reinterpret_cast<float4 *>(a.out + o + 4) = make_float4(yv[4], yv[5], yv[6], yv[7]);
             if (a.sample) {
-              if (ACT != ACT_PMP) {
+              if (!AHEAD && ACT != ACT_PMP) {
                 const float4 u0 = *reinterpret_cast<const float4 *>(a.uniform + o);
                 const float4 u1 = *reinterpret_cast<const float4 *>(a.uniform + o + 4);
-                sv[0] = u0.x < yv[0] ? 1.f : 0.f; sv[1] = u0.y < yv[1] ? 1.f : 0.f;
-                sv[2] = u0.z < yv[2] ? 1.f : 0.f; sv[3] = u0.w < yv[3] ? 1.f : 0.f;
-                sv[4] = u1.x < yv[4] ? 1.f : 0.f; sv[5] = u1.y < yv[5] ? 1.f : 0.f;
-                sv[6] = u1.z < yv[6] ? 1.f : 0.f; sv[7] = u1.w < yv[7] ? 1.f : 0.f;
+                uh[wa2][0] = u0.x; uh[wa2][1] = u0.y; uh[wa2][2] = u0.z; uh[wa2][3] = u0.w;
+                uh[wa2][4] = u1.x; uh[wa2][5] = u1.y; uh[wa2][6] = u1.z; uh[wa2][7] = u1.w;
+              }
+              if (ACT != ACT_PMP) {
+#pragma unroll
+                for (int e = 0; e < 2 * MT; ++e) sv[e] = uh[wa2][e] < yv[e] ? 1.f : 0.f;
               }
               *reinterpret_cast<float4 *>(a.sample + o) = make_float4(sv[0], sv[1], sv[2], sv[3]);
               *reinterpret_cast<float4 *>(a.sample + o + 4) = make_float4(sv[4], sv[5], sv[6], sv[7]);
             }
+            }
           } else {
-            // ragged row end: the uniform numbers first, all of them and from clamped addresses (a
-            // load behind the per-lane range check would be waited for on its own, eight in a row)
-            float uv[8];
-            if (a.sample && ACT != ACT_PMP) {
+            if (!AHEAD && a.sample && ACT != ACT_PMP) {   // from clamped addresses: they stay inside the row
 #pragma unroll
-              for (int e = 0; e < 8; ++e) uv[e] = a.uniform[o - ox + min(ox + e, a.Wout - 1)];   // stays inside the row
+              for (int e = 0; e < 2 * MT; ++e) uh[wa2][e] = a.uniform[o - ox + min(ox + e, a.Wout - 1)];
             }
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < 2 * MT; ++e)
               if (ox + e < a.Wout) {
                 a.out[o + e] = yv[e];
-                if (a.sample) a.sample[o + e] = ACT == ACT_PMP ? sv[e] : (uv[e] < yv[e] ? 1.f : 0.f);
+                if (a.sample) a.sample[o + e] = ACT == ACT_PMP ? sv[e] : (uh[wa2][e] < yv[e] ? 1.f : 0.f);
               }
           }
         }
@@ -222,10 +242,10 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
 
 // The activation and the pooling mode are fixed for a launch: dispatch once, so that the
 // per-element code carries no branches on them.
-template <int NT, int RP>
-__device__ __forceinline__ void engine_epilogue(const ConvEngineArgs &a, floatx4 (&acc)[RP][4][NT], const float (&bias)[NT],
+template <int NT, int RP, int MT = 4, bool AHEAD = false>
+__device__ __forceinline__ void engine_epilogue(const ConvEngineArgs &a, floatx4 (&acc)[RP][MT][NT], const float (&bias)[NT],
                                                 int n, int ko0, int oy0, int ox0, int wave, int i16, int kq) {
-#define DLL_EPI(ACT_, POOL_) engine_epilogue_as<NT, RP, ACT_, POOL_>(a, acc, bias, n, ko0, oy0, ox0, wave, i16, kq)
+#define DLL_EPI(ACT_, POOL_) engine_epilogue_as<NT, RP, ACT_, POOL_, MT, AHEAD>(a, acc, bias, n, ko0, oy0, ox0, wave, i16, kq)
   if (a.pool == 2) {
     if (a.act == ACT_RELU) DLL_EPI(ACT_RELU, 2);
     else if (a.act == ACT_SIGMOID) DLL_EPI(ACT_SIGMOID, 2);
@@ -239,15 +259,26 @@ __device__ __forceinline__ void engine_epilogue(const ConvEngineArgs &a, floatx4
 #undef DLL_EPI
 }
 
-template <int NT, int RP>
-__global__ __launch_bounds__(kThreads) void conv_engine_kernel(const EngineParams p) {
+// The generic instance: any filter, any channel count.  MT: pooling windows per lane and row pair, i.e. the tile is
+// 8 * MT columns wide (narrow maps take 8 or 16: an 8 x 8 map fills a quarter of a 32-wide tile's products).  DZ:
+// the source is dz, formed while staging.
+// Staging walks positions of the halo tile (a thread's row, column and what lies there are worked out once per
+// position) and, inside, channels: one channel further is a uniform step in memory and in LDS, so an
+// element costs its load and its store.  Positions outside the image are cleared once and never written.
+// The first positions of a chunk are on their way during the products of the chunk before.  Before, each
+// element had an address of its own, walked with divergent carries, four at a time:
+// 33 x 40 x 45 x 51 gradients, 24 channels 3x3: 74 -> 67 us; 100 x 8 x 12 x 12, 8 filters 5x5: 14.9 -> 9.5.
+// Bound by the latency of that chain for a few channels, by the matrix pipe for many.
+// kBatch: values of the halo tile in flight per thread: 8 where that is all of them (one to three channels), which
+// leaves registers for twice the wavefronts, else 16, or 12 with everything dz needs.  WIDE: 64-bit offsets, for planes or filter rows of 4 GiB.
+template <int NT, int RP, int MT, bool DZ, int kBatch, bool WIDE = false>
+__global__ __launch_bounds__(kThreads, 2) void conv_engine_kernel(const EngineParams p) {
   extern __shared__ float lds[];
   const ConvEngineArgs &a = p.a;
   const EngineGeom &g = p.g;
   float *xs = lds;                                  // [CC][PS]
   float *wl = xs + g.CC * g.PS;                     // [NT][KC][16]
   int *koff = reinterpret_cast<int *>(wl + NT * g.KC * 16);  // [KC]
-  int2 *wtab = reinterpret_cast<int2 *>(koff + g.KC);        // [KC]: offset of tap kk inside a filter slice (-1: padding), channel
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i16 = lane & 15, kq = lane >> 4;
@@ -256,139 +287,175 @@ __global__ __launch_bounds__(kThreads) void conv_engine_kernel(const EngineParam
   const int ty = (bid / g.tiles_x) % g.tiles_y;
   const int n = bid / (g.tiles_x * g.tiles_y);
   const int ko0 = blockIdx.y * (NT * 16);
-  constexpr int TH = 8 * RP;
-  const int oy0 = ty * TH, ox0 = tx * kTileW;       // pre-pool output origin of the tile
+  constexpr int TH = 8 * RP, TW = 8 * MT;
+  const int oy0 = ty * TH, ox0 = tx * TW;           // pre-pool output origin of the tile
   const int RSf = a.R * a.S;
 
-  // tap offsets inside the halo tile: kk = (r*S + s)*CC + cl  ->  cl*PS + r*RS + s, and inside the
-  // filter tensor relative to the chunk's first channel (rotated and transposed filters: w_flip)
+  // ---- halo tile of the source, zero outside the image (padding) and past Cin.  A thread's work on a chunk is a list
+  // of (position, channel) pairs, channel fastest, kBatch of them in flight together.
+  const int positions = g.rows * g.cols;
+  const bool pooled = DZ && a.src_pool == 2;
+  const bool need_y = DZ && reads_output(a.src_act);
+  const int sh = pooled ? 1 : 0, Ws = a.Win >> sh, plane = (a.Hin >> sh) * Ws;   // a plane as it is stored
+  // one uniform base plus a 32-bit byte offset per lane: the form that costs no address arithmetic per load
+  auto fetch = [](const auto *base, auto offset) __attribute__((always_inline)) {
+    using T = std::remove_cv_t<std::remove_reference_t<decltype(*base)>>;
+    if constexpr (WIDE) return base[offset];
+    else return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + (unsigned)offset * (unsigned)sizeof(T));
+  };
+  // offsets are taken from the tile's first row and column inside the image
+  const int gi0 = max(oy0 - a.pad_h, 0) >> sh, gj0 = max(ox0 - a.pad_w, 0) >> sh;
+  const int drow = kThreads / g.cols, dcol = kThreads - drow * g.cols;
+  const int row0 = tid / g.cols, col0 = tid - row0 * g.cols;
+  int row = row0, col = col0, cl = 0;   // the next pair
+  int o = 0, at = 0;                    // its position's offset in a plane and in LDS
+  bool in = false;
+  unsigned char place = 0;              // its position's place in the pooling window
+  auto look = [&]() __attribute__((always_inline)) {
+    const int gi = oy0 - a.pad_h + row, gj = ox0 - a.pad_w + col;
+    in = row < g.rows && gi >= 0 && gi < a.Hin && gj >= 0 && gj < a.Win;
+    o = in ? ((gi >> sh) - gi0) * Ws + (gj >> sh) - gj0 : 0;
+    at = row * g.RS + col;
+    place = (unsigned char)(((gi & 1) << 1) | (gj & 1));
+  };
+  const int pairs = (positions + kThreads - 1) / kThreads * g.CC;
+  float gv[kBatch], yv[DZ ? kBatch : 1];
+  unsigned char fv[DZ ? kBatch : 1], want[DZ ? kBatch : 1];
+  int dst[kBatch];                      // LDS offset; negative: nothing to store; with kZero: a channel past the last
+  constexpr int kZero = 1 << 30;
+  auto load_halo = [&](int c0, int q0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      if (q0 + u >= pairs) break;
+      // a position outside the image and a channel past the last read an element that exists
+      const long base = (long)(n * a.Cin + min(c0 + cl, a.Cin - 1)) * plane + (long)gi0 * Ws + gj0;
+      gv[u] = fetch(a.src + base, o);
+      dst[u] = in ? (cl * g.PS + at) | (c0 + cl < a.Cin ? 0 : kZero) : -1;
+      if constexpr (DZ) {
+        if (need_y) yv[u] = fetch(a.src_y + base, o);
+        if (pooled) fv[u] = fetch(a.src_idx + base, o);
+        want[u] = place;
+      }
+      if (++cl == g.CC) {
+        cl = 0;
+        row += drow;
+        col += dcol;
+        if (col >= g.cols) { col -= g.cols; ++row; }
+        look();
+      }
+    }
+  };
+  auto store_halo = [&](int q0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      if (q0 + u >= pairs) break;
+      float v = gv[u];
+      if constexpr (DZ) {
+        // dz at a pre-pool position: dy routed to the recorded arg-max, times act'(y)
+        if (pooled && (fv[u] & kIdxPosMask) != want[u]) v = 0.0f;
+        if (a.src_act == ACT_RELU_FLAGGED) v = (fv[u] & kIdxInactive) ? 0.0f : v;
+        else if (a.src_act == ACT_SIGMOID) v *= yv[u] * (1.0f - yv[u]);
+        else if (a.src_act == ACT_RELU) v = yv[u] > 0.0f ? v : 0.0f;
+      }
+      if (dst[u] >= 0) xs[dst[u] & (kZero - 1)] = (dst[u] & kZero) ? 0.0f : v;
+    }
+  };
+
+  // ---- filter slice wl[nt][kk][j] = wgt(ko0 + 16nt + j, c0 + cl, r, s), kk = (r*S + s)*CC + cl: sixteen threads take the
+  // 16 columns j of a (channel, tap); a thread keeps its channel and steps through the taps, `tstep` at a time
+  constexpr int kTaps = NT == 1 ? 9 : (NT == 2 ? 6 : 4);
+  const int fj = tid & 15, fs = tid >> 4;
+  const int fcl = fs & ((1 << g.cw_log) - 1), frs = fs >> g.cw_log, tstep = 16 >> g.cw_log;
+  float tv[NT][kTaps];
+  auto load_taps = [&](int c0, int r0) __attribute__((always_inline)) {
+    const bool chan = fcl < g.CC && c0 + fcl < a.Cin;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const bool ok = chan && ko0 + nt * 16 + fj < a.Kout;
+      const float *base = a.w + (a.w_flip ? ((long)c0 * a.Kout + ko0 + nt * 16) * RSf : ((long)(ko0 + nt * 16) * a.Cin + c0) * RSf);
+      if (ko0 + nt * 16 >= a.Kout) base = a.w;   // a group of columns that does not exist reads the first filter
+      const long lane_o = !ok ? 0 : (a.w_flip ? ((long)fcl * a.Kout + fj) * RSf : ((long)fj * a.Cin + fcl) * RSf);
+#pragma unroll
+      for (int u = 0; u < kTaps; ++u) {
+        if (r0 + u * tstep >= RSf) break;
+        const int rs = min(r0 + u * tstep + frs, RSf - 1), at = a.w_flip ? RSf - 1 - rs : rs;
+        const float v = WIDE ? fetch(base, lane_o + at) : fetch(base, (int)lane_o + at);
+        tv[nt][u] = ok ? v : 0.0f;
+      }
+    }
+  };
+  auto store_taps = [&](int r0) __attribute__((always_inline)) {
+    if (fcl >= g.CC) return;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int u = 0; u < kTaps; ++u) {
+        if (r0 + u * tstep >= RSf) break;
+        const int rs = r0 + u * tstep + frs;
+        if (rs < RSf) wl[(nt * g.KC + rs * g.CC + fcl) * 16 + fj] = tv[nt][u];
+      }
+  };
+  // ---- once: tap offsets inside the halo tile (kk -> cl*PS + r*RS + s), the filter rows that pad KC to whole
+  // MFMA steps, the positions outside the image
   for (int kk = tid; kk < g.KC; kk += kThreads) {
-    const int cl = kk % g.CC, rs = kk / g.CC;
+    const int rs = kk / g.CC, cl = kk - rs * g.CC;
     const int r = rs / a.S, s = rs - r * a.S;
     koff[kk] = rs < RSf ? cl * g.PS + r * g.RS + s : 0;
-    const int wo = a.w_flip ? cl * a.Kout * RSf + (a.R - 1 - r) * a.S + (a.S - 1 - s) : cl * RSf + r * a.S + s;
-    wtab[kk] = make_int2(rs < RSf ? wo : -1, cl);
   }
-  // Only the first 2^jw_log columns of a filter slice can be non-zero (Kout is small); the others
-  // are cleared once here and never written again.
-  const int jw = 1 << g.jw_log;
-  if (jw < 16)
-    for (int e = tid; e < NT * g.KC * 16; e += kThreads) wl[e] = 0.0f;
+  if (tid < 16)
+    for (int nt = 0; nt < NT; ++nt)
+      for (int kk = RSf * g.CC; kk < g.KC; ++kk) wl[(nt * g.KC + kk) * 16 + tid] = 0.0f;
+  {
+    const bool border = oy0 < a.pad_h || ox0 < a.pad_w || oy0 - a.pad_h + g.rows > a.Hin || ox0 - a.pad_w + g.cols > a.Win;
+    if (border)
+      for (int e = tid; e < g.CC * g.PS; e += kThreads) xs[e] = 0.0f;
+  }
 
-  floatx4 acc[RP][4][NT];
+  floatx4 acc[RP][MT][NT];
 #pragma unroll
   for (int rp = 0; rp < RP; ++rp)
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) acc[rp][mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   // lane's pixel inside an M-tile: window gq, position (wa, wb)
   const int gq = i16 >> 2, wa = (i16 >> 1) & 1, wb = i16 & 1;
-  const int a_base = (wave * 2 * RP + wa) * g.RS + 8 * gq + wb;
+  const int a_base = (wave * 2 * RP + wa) * g.RS + 2 * MT * gq + wb;
 
-  for (int chunk = 0; chunk < g.nchunks; ++chunk) {
+  __syncthreads();   // the cleared planes
+  // A chunk's first values are asked for, the chunk before is multiplied, then they are stored and the rest follows.
+  for (int chunk = 0; chunk <= g.nchunks; ++chunk) {
     const int c0 = chunk * g.CC;
-    __syncthreads();  // previous chunk's readers are done
-    // Both staging loops work in batches of kStage elements per thread: all addresses first, then all
-    // loads, unconditionally and from clamped addresses (element 0 stands in for anything that is
-    // padding or out of range), then the selects and the LDS stores.  A load behind a per-lane
-    // branch would be waited for before the next one is issued.
-    constexpr int kStage = 4;
-    // ---- filter slice: wl[nt][kk][j] = wgt(ko0 + 16nt + j, c0 + cl, r, s) for the columns j < jw
-    const int f_total = NT * g.KC * jw;
-    const int w_base = a.w_flip ? c0 * a.Kout * RSf : c0 * RSf;   // + ko * RSf (flipped) or ko * Cin * RSf
-    const int w_ko = a.w_flip ? RSf : a.Cin * RSf;
-    for (int e0 = tid; e0 < f_total; e0 += kStage * kThreads) {
-      float v[kStage];
-      bool ok[kStage];
-      int dst[kStage];
-#pragma unroll
-      for (int u = 0; u < kStage; ++u) {
-        const int e = min(e0 + u * kThreads, f_total - 1);
-        const int j = e & (jw - 1);
-        int kk = e >> g.jw_log, nt = 0;
-        while (kk >= g.KC) { kk -= g.KC; ++nt; }   // at most NT - 1 rounds
-        const int2 t = wtab[kk];
-        const int ko = ko0 + nt * 16 + j;
-        ok[u] = t.x >= 0 && ko < a.Kout && c0 + t.y < a.Cin;
-        dst[u] = (nt * g.KC + kk) * 16 + j;
-        v[u] = a.w[ok[u] ? w_base + ko * w_ko + t.x : 0];
-      }
-#pragma unroll
-      for (int u = 0; u < kStage; ++u)
-        if (e0 + u * kThreads < f_total) wl[dst[u]] = ok[u] ? v[u] : 0.0f;
+    if (chunk < g.nchunks) {
+      row = row0; col = col0; cl = 0;
+      look();
+      load_halo(c0, 0);
+      load_taps(c0, 0);
     }
-    // ---- halo tile of the source, zero outside the image (padding) and past Cin
-    {
-      const int total = g.CC * g.rows * g.cols;
-      int col = tid % g.cols;
-      int q = tid / g.cols;
-      int row = q % g.rows, cl = q / g.rows;
-      const int dcol = kThreads % g.cols, dq = kThreads / g.cols;
-      const int Hp = a.Hin >> 1, Wp = a.Win >> 1;   // pooled dz sources only
-      const bool pooled = a.src_dz && a.src_pool == 2;
-      const bool need_y = a.src_dz && reads_output(a.src_act);
-      for (int e0 = tid; e0 < total; e0 += kStage * kThreads) {
-        float gv[kStage], yv[kStage];
-        unsigned char fv[kStage];
-        bool ok[kStage];
-        int dst[kStage], want[kStage];
-#pragma unroll
-        for (int u = 0; u < kStage; ++u) {
-          const int gi = oy0 - a.pad_h + row, gj = ox0 - a.pad_w + col, ci = c0 + cl;
-          ok[u] = e0 + u * kThreads < total && ci < a.Cin && gi >= 0 && gi < a.Hin && gj >= 0 && gj < a.Win;
-          dst[u] = cl * g.PS + row * g.RS + col;
-          want[u] = ((gi & 1) << 1) | (gj & 1);
-          int o = pooled ? ((n * a.Cin + ci) * Hp + (gi >> 1)) * Wp + (gj >> 1) : ((n * a.Cin + ci) * a.Hin + gi) * a.Win + gj;
-          o = ok[u] ? o : 0;
-          gv[u] = a.src[o];
-          yv[u] = need_y ? a.src_y[o] : 0.0f;
-          fv[u] = pooled ? a.src_idx[o] : (unsigned char)0;
-          col += dcol;
-          row += dq;
-          if (col >= g.cols) { col -= g.cols; ++row; }
-          while (row >= g.rows) { row -= g.rows; ++cl; }
-        }
-#pragma unroll
-        for (int u = 0; u < kStage; ++u) {
-          if (e0 + u * kThreads >= total) continue;
-          float v = gv[u];
-          if (a.src_dz) {
-            // dz at a pre-pool position: dy routed to the recorded arg-max, times act'(y)
-            if (pooled && (fv[u] & kIdxPosMask) != (unsigned char)want[u]) v = 0.0f;
-            if (a.src_act == ACT_RELU_FLAGGED) v = (fv[u] & kIdxInactive) ? 0.0f : v;
-            else if (a.src_act == ACT_SIGMOID) v *= yv[u] * (1.0f - yv[u]);
-            else if (a.src_act == ACT_RELU) v = yv[u] > 0.0f ? v : 0.0f;
-          }
-          xs[dst[u]] = ok[u] ? v : 0.0f;
-        }
-      }
-    }
-    __syncthreads();
     // ---- MFMA over the chunk's taps, software-pipelined over two register sets: while step t is
     // multiplied, the operand fragments of step t+1 are on their way from LDS and the tap offset of
     // step t+2 is being read (offset -> fragment -> MFMA is a chain of two LDS latencies that a
     // plain loop would pay at every step).  Steps past the end re-read the last step and are not
     // multiplied.
-    {
-      float afA[RP * 4], bfA[NT], afB[RP * 4], bfB[NT];
-      auto load_step = [&](int t, int o, float (&af)[RP * 4], float (&bf)[NT]) __attribute__((always_inline)) {
+    if (chunk > 0) {
+      float afA[RP * MT], bfA[NT], afB[RP * MT], bfB[NT];
+      auto load_step = [&](int t, int o, float (&af)[RP * MT], float (&bf)[NT]) __attribute__((always_inline)) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) bf[nt] = wl[(nt * g.KC + 4 * t + kq) * 16 + i16];
 #pragma unroll
         for (int rp = 0; rp < RP; ++rp)
 #pragma unroll
-          for (int mt = 0; mt < 4; ++mt) af[rp * 4 + mt] = xs[a_base + rp * 2 * g.RS + o + 2 * mt];
+          for (int mt = 0; mt < MT; ++mt) af[rp * MT + mt] = xs[a_base + rp * 2 * g.RS + o + 2 * mt];
       };
-      auto mfma_step = [&](const float (&af)[RP * 4], const float (&bf)[NT]) __attribute__((always_inline)) {
+      auto mfma_step = [&](const float (&af)[RP * MT], const float (&bf)[NT]) __attribute__((always_inline)) {
 #pragma unroll
         for (int rp = 0; rp < RP; ++rp)
 #pragma unroll
-          for (int mt = 0; mt < 4; ++mt)
+          for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
-              acc[rp][mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[rp * 4 + mt], bf[nt], acc[rp][mt][nt], 0, 0, 0);
+              acc[rp][mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[rp * MT + mt], bf[nt], acc[rp][mt][nt], 0, 0, 0);
       };
       const int last = g.KS - 1;
       int o1 = koff[4 * min(1, last) + kq];
@@ -407,10 +474,25 @@ __global__ __launch_bounds__(kThreads) void conv_engine_kernel(const EngineParam
         o1 = o3;
       }
     }
+    if (chunk == g.nchunks) break;
+    if (chunk > 0) __syncthreads();   // the chunk before has been read
+    for (int q0 = 0;;) {
+      store_halo(q0);
+      q0 += kBatch;
+      if (q0 >= pairs) break;
+      load_halo(c0, q0);
+    }
+    for (int r0 = 0;;) {
+      store_taps(r0);
+      r0 += kTaps * tstep;
+      if (r0 >= RSf) break;
+      load_taps(c0, r0);
+    }
+    __syncthreads();
   }
   float bias_v[NT];
   lane_bias<NT>(a, ko0, i16, bias_v);
-  engine_epilogue<NT, RP>(a, acc, bias_v, n, ko0, oy0, ox0, wave, i16, kq);
+  engine_epilogue<NT, RP, MT, true>(a, acc, bias_v, n, ko0, oy0, ox0, wave, i16, kq);
 }
 
 inline int round_up_mod(int v, int m, int r) {  // smallest value >= v congruent to r mod m
@@ -419,43 +501,56 @@ inline int round_up_mod(int v, int m, int r) {  // smallest value >= v congruent
   return x;
 }
 
-bool plan_engine(const ConvEngineArgs &a, int NT, int RP, EngineGeom *g, size_t *lds_bytes) {
-  const int TH = 8 * RP;
+bool plan_engine(const ConvEngineArgs &a, int NT, int RP, int MT, EngineGeom *g, size_t *lds_bytes) {
+  const int TH = 8 * RP, TW = 8 * MT;
   g->rows = TH + a.R - 1;
-  g->cols = kTileW + a.S - 1;
+  g->cols = TW + a.S - 1;
   g->RS = round_up_mod(g->cols, 8, 2);
   g->PS = round_up_mod(g->RS * g->rows, 8, 4);
   int CC = a.Cin < 16 ? a.Cin : 16;
-  for (;;) {
-    g->CC = CC;
-    g->KC = (CC * a.R * a.S + 3) / 4 * 4;
+  auto set = [&](int cc) {
+    g->CC = cc;
+    g->KC = (cc * a.R * a.S + 3) / 4 * 4;
     g->KS = g->KC / 4;
-    *lds_bytes = sizeof(float) * ((size_t)CC * g->PS + (size_t)NT * g->KC * 16 + 3 * (size_t)g->KC);
-    if (*lds_bytes <= 64 * 1024 || CC == 1) break;
-    CC = (CC + 1) / 2;
-  }
+    *lds_bytes = sizeof(float) * ((size_t)cc * g->PS + (size_t)NT * g->KC * 16 + (size_t)g->KC);
+  };
+  for (set(CC); *lds_bytes > 64 * 1024 && CC > 1; set(CC)) CC = (CC + 1) / 2;
   if (*lds_bytes > 64 * 1024) return false;
+  const int chunks = (a.Cin + CC - 1) / CC;
+  set((a.Cin + chunks - 1) / chunks);   // as many channels in every chunk: 40 are 14 + 14 + 12, not 16 + 16 + 8 and eight of zeros
   g->nchunks = (a.Cin + g->CC - 1) / g->CC;
-  g->tiles_x = (a.Wout + kTileW - 1) / kTileW;
+  g->tiles_x = (a.Wout + TW - 1) / TW;
   g->tiles_y = (a.Hout + TH - 1) / TH;
   g->kgroups = (a.Kout + NT * 16 - 1) / (NT * 16);
-  g->jw_log = 4;
-  if (NT == 1 && a.Kout < 16)
-    while (g->jw_log > 0 && (1 << (g->jw_log - 1)) >= a.Kout) --g->jw_log;
+  g->cw_log = 0;
+  while ((1 << g->cw_log) < g->CC) ++g->cw_log;
   return true;
 }
 
-template <int NT, int RP>
+template <int NT, int RP, int MT, bool WIDE = false>
 hipError_t launch_t(const ConvEngineArgs &a, hipStream_t stream) {
   EngineParams p;
   p.a = a;
   size_t lds = 0;
-  if (!plan_engine(a, NT, RP, &p.g, &lds)) return hipErrorInvalidValue;
+  if (!plan_engine(a, NT, RP, MT, &p.g, &lds)) return hipErrorInvalidValue;
   const long blocks = (long)a.N * p.g.tiles_x * p.g.tiles_y;
   if (blocks <= 0 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks, (unsigned)p.g.kgroups, 1);
-  hipLaunchKernelGGL((conv_engine_kernel<NT, RP>), grid, dim3(kThreads), lds, stream, p);
+  const bool shallow = (p.g.rows * p.g.cols + kThreads - 1) / kThreads * p.g.CC <= 8;
+  if (a.src_dz) hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, true, 12, WIDE>), grid, dim3(kThreads), lds, stream, p);
+  else if (shallow) hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, false, 8, WIDE>), grid, dim3(kThreads), lds, stream, p);
+  else hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, false, 16, WIDE>), grid, dim3(kThreads), lds, stream, p);
   return hipGetLastError();
+}
+
+// Tiles of 16 rows where they give every compute unit two workgroups, else of 8; maps of at most 8 or 16
+// columns take tiles that narrow.
+template <int NT>
+hipError_t launch_generic(const ConvEngineArgs &a, bool small, hipStream_t stream) {
+  if (a.Wout <= 8) return launch_t<NT, 1, 1>(a, stream);
+  if (a.Wout <= 16) return launch_t<NT, 1, 2>(a, stream);
+  if (small) return launch_t<NT, 1, 4>(a, stream);
+  return launch_t<NT, 2, 4>(a, stream);
 }
 
 
@@ -1008,7 +1103,12 @@ hipError_t launch_3x3(const ConvEngineArgs &a, hipStream_t stream) {
 hipError_t launch_conv_engine(const ConvEngineArgs &a, hipStream_t stream) {
   // 16 output channels per N-tile.  The generic kernel uses the 8-row tile for shallow maps
   // (<= 8 pre-pool rows) and whenever 16-row tiles would leave CUs without a workgroup.
-  const int nt = a.Kout <= 16 ? 1 : (a.Kout <= 32 ? 2 : 3);
+  // A launch that leaves compute units without a workgroup splits the output channels instead (four images of 40
+  // channels, 61 x 61, 33 filters 5x5: the layer's passes 228 -> 134 us; but splitting 396 tiles to give every
+  // unit two, 33 x 40 x 45 x 51: 61 -> 131).
+  const long tiles8 = (long)a.N * ((a.Wout + kTileW - 1) / kTileW) * ((a.Hout + 7) / 8);
+  int nt = a.Kout <= 16 ? 1 : (a.Kout <= 32 ? 2 : 3);
+  while (nt > 1 && tiles8 * ((a.Kout + nt * 16 - 1) / (nt * 16)) < chip().cus) --nt;
   const long tiles16 = (long)a.N * ((a.Wout + kTileW - 1) / kTileW) * ((a.Hout + 15) / 16) * ((a.Kout + nt * 16 - 1) / (nt * 16));
   const bool small = a.Hout <= 8 || tiles16 < 512;
   // very few output channels: the banded-filter kernel takes Kout * ceil((16 + S - 1) / 4) MFMA steps per
@@ -1022,21 +1122,24 @@ hipError_t launch_conv_engine(const ConvEngineArgs &a, hipStream_t stream) {
   if (conv_fwd_fewch_applies(a)) return launch_conv_fwd_fewch(a, stream);
   if (conv_wino_stream_applies(a) || conv_wino_stream_bwd_applies(a)) return launch_conv_wino_stream(a, stream);
   if (conv_wino_applies(a)) return launch_conv_wino(a, stream);
-  if (a.Hout > 8) {
+  // The 3x3 instance's tiles are 32 x 16: a map of at most 16 columns fills half of one, and few of them leave most of the
+  // chip idle.  There the generic instance's 16- and 8-wide tiles are the better ones: 100 x 12 x 16 x 16, 24
+  // filters 15.4 against 9.6 us, 8 x 64 x 16 x 16, 64 filters 49 against 27, 128 x 32 x 16 x 16, 32 filters 27 against 22; at 512
+  // images 48 against 53.
+  const bool narrow = a.Wout <= 16 && 4L * a.N * ((a.Hout + 15) / 16) <= 3L * chip().cus;
+  if (a.Hout > 8 && !narrow) {
     const Conv3x3Pick pick = conv3x3c16_pick(a);
     if (pick.NT == 1 && pick.CC == 8) return launch_3x3<1, 4, 8>(a, stream);
     if (pick.NT == 1 && pick.CC == 4) return launch_3x3<1, 4, 4>(a, stream);
     if (pick.NT == 2 && pick.CC == 4) return launch_3x3<2, 4, 4>(a, stream);
     if (pick.NT == 2 && pick.CC == 16) return launch_3x3<2, 8, 16>(a, stream);
   }
-  if (small) {
-    if (nt == 1) return launch_t<1, 1>(a, stream);
-    if (nt == 2) return launch_t<2, 1>(a, stream);
-    return launch_t<3, 1>(a, stream);
-  }
-  if (nt == 1) return launch_t<1, 2>(a, stream);
-  if (nt == 2) return launch_t<2, 2>(a, stream);
-  return launch_t<3, 2>(a, stream);
+  // the halo tile's rows of a plane and a workgroup's filters within 32-bit byte offsets
+  const long tile_rows = (long)(16 + a.R - 1) * a.Win, filters = 48L * (a.Cin > a.Kout ? a.Cin : a.Kout) * a.R * a.S;
+  if (tile_rows >= (1L << 29) || filters >= (1L << 29)) return launch_t<1, 1, 1, true>(a, stream);
+  if (nt == 1) return launch_generic<1>(a, small, stream);
+  if (nt == 2) return launch_generic<2>(a, small, stream);
+  return launch_generic<3>(a, small, stream);
 }
 
 }  // namespace dllk
