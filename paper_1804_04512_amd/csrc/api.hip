@@ -428,16 +428,20 @@ dll_status dll_crbm_cd1_step_units(const dll_conv_desc *din, int visible, int hi
   // statistics: filter gradients with dz := hidden probabilities
   dll_conv_desc di = d;
   di.act = DLL_ACT_IDENTITY;
-  if ((st = dev(launch_wgrad(wgrad_args(&di, v0, h0p, nullptr, nullptr, part_pos), plan, s))) != DLL_OK) return st;
-  if ((st = dev(launch_wgrad(wgrad_args(&di, v1p, h1p, nullptr, nullptr, part_neg), plan, s))) != DLL_OK) return st;
+  const WgradArgs pos = wgrad_args(&di, v0, h0p, nullptr, nullptr, part_pos), neg = wgrad_args(&di, v1p, h1p, nullptr, nullptr, part_neg);
+  if ((st = dev(launch_wgrad_two(pos, neg, plan, s))) != DLL_OK) return st;
   const float invB = 1.0f / (float)d.N;
   WgradReduceArgs r;
   r.pos = part_pos; r.neg = part_neg; r.scale = invB; r.dw = dW; r.db = db;
   r.C = d.C; r.K = d.K; r.R = d.R; r.S = d.S;
   if (lr != 0.0f) { r.w_update = W; r.b_update = b_hid; r.step = lr; }
-  if ((st = dev(launch_wgrad_reduce(r, plan, s))) != DLL_OK) return st;
-  return dev(launch_visible_stats(v0, v1p, d.N, d.C, d.H * d.W, invB, dc, recon_mse, lr != 0.0f ? c_vis : nullptr, lr,
-                                  stats, s));
+  StepTail t;   // the reduction and the visible sums side by side
+  t.reduce[0].a = r;
+  t.reduce[0].plan = plan;
+  t.n_reduce = 1;
+  t.vis.v0 = v0; t.vis.v1 = v1p; t.vis.N = d.N; t.vis.C = d.C; t.vis.HW = d.H * d.W; t.vis.scratch = stats;
+  if ((st = dev(launch_step_tail(t, s))) != DLL_OK) return st;
+  return dev(launch_visible_final(d.N, d.C, d.H * d.W, invB, dc, recon_mse, lr != 0.0f ? c_vis : nullptr, lr, stats, s));
 }
 
 dll_status dll_crbm_cd1_step(const dll_conv_desc *d, const float *v0, float *W, float *b_hid, float *c_vis,
@@ -935,6 +939,8 @@ dll_status dll_cnn_forward(const dll_net_desc *net, const float *const *params, 
     flip ^= 1;
   }
   float *lg = logits ? logits : own_logits;
+  int logits_split = 1;
+  bool softmax_fused = false;
   for (int q = 0; q < D; ++q) {
     const dll_dense_desc *dd = &net->dense[q];
     float *out = (q == D - 1) ? lg : buf[flip];
@@ -947,12 +953,19 @@ dll_status dll_cnn_forward(const dll_net_desc *net, const float *const *params, 
     g.Cout = out; g.c_m = dd->out; g.c_n = 1;
     g.split_k = gemm_pick_split_k(g.M, g.N, g.Kdim);
     g.partial = partial;
+    if (q == D - 1 && prob) {
+      // the softmax rides in the epilogue of a small product of few classes, or adds the split-K partials itself
+      // (one image through the MNIST network and 128 through the large-image one: a launch less each, 4 us)
+      if (gemm_fuses_softmax(g.M, g.N, g.Kdim)) { g.sm_prob = prob; softmax_fused = true; }
+      else if (g.split_k > 1) { g.defer_reduce = true; logits_split = g.split_k; }
+    }
     if ((st = dev(launch_gemm(g, s))) != DLL_OK) return st;
     cur = out;
     flip ^= 1;
   }
-  if (prob && (st = dev(launch_softmax_prob(lg, B, net->classes, prob, s))) != DLL_OK) return st;
-  return DLL_OK;
+  if (!prob || softmax_fused) return DLL_OK;
+  return dev(launch_softmax_prob(lg, B, net->classes, prob, logits_split > 1 ? partial : nullptr, logits_split,
+                                 params[2 * (L + D - 1) + 1], s));
 }
 
 }  // extern "C"

@@ -53,6 +53,9 @@ struct WgradParams {
   long db_offset;
   long group_stride;       // floats between filter groups in the dw partial area
   int nxi, nxh;            // fast path: staging rounds the tile really needs (<= NXI, NXH)
+  // a second filter gradient of the same shape in the same launch (blockIdx.z == 1): the CRBM's negative phase
+  const float *x2, *dy2;
+  float *partial2;
   unsigned x_bytes, dy_bytes;   // fast path: tensor sizes (below 2 GiB) for the range-checked loads
 };
 
@@ -105,7 +108,8 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const WgradParams p) {
   constexpr bool ONE_ROUND = FAST == 2 || FAST == 4, RAGGED = FAST >= 3;
   constexpr int XI = ONE_ROUND ? 1 : NXI, XH = ONE_ROUND ? 1 : NXH;
   extern __shared__ float lds[];
-  const WgradArgs &a = p.a;
+  WgradArgs a = p.a;
+  if (blockIdx.z != 0) { a.x = p.x2; a.dy = p.dy2; a.partial = p.partial2; }
   float *xs = lds;                 // [CC][PS]
   float *dzs = xs + p.CC * p.PS;   // [filters of the group][PSZ]
 
@@ -635,7 +639,7 @@ inline int reduce_blocks(const WgradReduceArgs &a, const WgradPlan &plan) {
 }
 
 // The step's closing kernel: workgroup ranges [start[j], start[j+1]) belong to job j; jobs are the small
-// weight-gradient products, the filter-gradient reductions, the column sums, then the mean loss.  The
+// weight-gradient products, the filter-gradient reductions, the column sums, the mean loss, then the visible sums.  The
 // reductions alone (PRODUCTS = false) are bound by memory latency and live from their occupancy, which the
 // products' registers and LDS would halve.  As launches of their own the products of a small network took
 // 4 to 10 us each, most of it latency; here they run beside each other and the reductions.
@@ -645,7 +649,8 @@ struct StepTailParams {
   StepTail::Colsum colsum[StepTail::kMaxColsum];
   small_gemm::SmallParams gemm[StepTail::kMaxGemm];
   const float *rowloss; int rows; float *loss; double count;
-  int start[StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 2];
+  StepTail::Visible vis;
+  int start[StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 3];
   long group_stride[StepTail::kMaxReduce];
   int kgroups[StepTail::kMaxReduce];
 };
@@ -673,8 +678,10 @@ __global__ __launch_bounds__(kThreads) void step_tail_kernel(const StepTailParam
   } else if (j < p.n_reduce + p.n_colsum) {
     const StepTail::Colsum &c = p.colsum[j - p.n_reduce];
     colsum_block(c.A, c.M, c.N, c.out, c.update, c.step, c.vel, c.mu, blk, c.A2, c.scale);
-  } else {
+  } else if (p.loss && j == p.n_reduce + p.n_colsum) {
     mean_block(p.rowloss, p.rows, p.loss, p.count);
+  } else {
+    visible_block(p.vis.v0, p.vis.v1, p.vis.N, p.vis.C, p.vis.HW, p.vis.scratch, blk);
   }
 }
 
@@ -793,7 +800,7 @@ enum class Staging { kElements, kVectors, kRagged };
 
 template <int MTF, int NTT>
 hipError_t launch_wgrad_t(const WgradParams &p, const WgradPlan &plan, Staging how, hipStream_t stream) {
-  dim3 grid((unsigned)(plan.G * plan.nchunks), (unsigned)p.kgroups, 1);
+  dim3 grid((unsigned)(plan.G * plan.nchunks), (unsigned)p.kgroups, p.partial2 ? 2 : 1);
   auto launch = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, dim3(kThreads), plan.lds_bytes, stream, p);
     return hipGetLastError();
@@ -824,11 +831,12 @@ inline bool aligned16(const void *q) { return (reinterpret_cast<uintptr_t>(q) & 
 
 }  // namespace
 
-hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &plan, hipStream_t stream) {
-  if (wgrad_wino_applies(a, plan)) return launch_wgrad_wino(a, plan, stream);
-  if (wgrad_fewch_applies(a, plan)) return launch_wgrad_fewch(a, plan, stream);
+namespace {
+// b: a second filter gradient of the same shape and activation (NULL: none)
+hipError_t launch_direct(const WgradArgs &a, const WgradArgs *b, const WgradPlan &plan, hipStream_t stream) {
   WgradParams p;
   p.a = a;
+  p.x2 = b ? b->x : nullptr; p.dy2 = b ? b->dy : nullptr; p.partial2 = b ? b->partial : nullptr;
   p.Ho = a.H + 2 * a.pad - a.R + 1;
   p.Wo = a.W + 2 * a.pad - a.S + 1;
   p.CC = plan.CC;
@@ -850,7 +858,7 @@ hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &plan, hipStream_t s
   const int lines = plan.CC * g.rows;
   const long x_bytes = 4L * a.N * a.C * a.H * a.W, dy_bytes = 4L * a.N * a.K * (p.Ho / a.pool) * (p.Wo / a.pool);
   const long limit = (1L << 31) - (1L << 24);
-  const bool vectors = aligned16(a.x) && aligned16(a.dy) && (!reads_output(a.act) || aligned16(a.y)) &&
+  const bool vectors = aligned16(a.x) && aligned16(a.dy) && aligned16(p.x2) && aligned16(p.dy2) && (!reads_output(a.act) || aligned16(a.y)) &&
                        lines * 8 <= NXI * kThreads && lines * (a.S - 1) <= NXH * kThreads && x_bytes < limit && dy_bytes < limit;
   const bool whole = a.W % 4 == 0 && (a.pool == 2 ? p.Wo % 8 == 0 && (reinterpret_cast<uintptr_t>(a.idx) & 3u) == 0 : p.Wo % 4 == 0);
   const Staging how = !vectors ? Staging::kElements : (whole ? Staging::kVectors : Staging::kRagged);
@@ -864,6 +872,19 @@ hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &plan, hipStream_t s
   case 3: return launch_wgrad_m<3>(p, plan, how, stream);
   default: return hipErrorInvalidValue;
   }
+}
+}  // namespace
+
+hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &plan, hipStream_t stream) {
+  if (wgrad_wino_applies(a, plan)) return launch_wgrad_wino(a, plan, stream);
+  if (wgrad_fewch_applies(a, plan)) return launch_wgrad_fewch(a, plan, stream);
+  return launch_direct(a, nullptr, plan, stream);
+}
+
+hipError_t launch_wgrad_two(const WgradArgs &a, const WgradArgs &b, const WgradPlan &plan, hipStream_t stream) {
+  const bool alike = a.act == ACT_IDENTITY && b.act == ACT_IDENTITY && a.pool == 1 && b.pool == 1 && a.N == b.N && a.C == b.C && a.H == b.H &&
+                     a.W == b.W && a.K == b.K && a.R == b.R && a.S == b.S && a.pad == b.pad && a.partial && b.partial;
+  return alike ? launch_direct(a, &b, plan, stream) : hipErrorInvalidValue;
 }
 
 hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, const WgradPlan &plan, hipStream_t stream) {
@@ -911,8 +932,13 @@ hipError_t launch_step_tail(const StepTail &t, hipStream_t stream) {
     p.start[jobs++] = blocks;
     blocks += 1;
   }
+  p.vis = t.vis;
+  if (t.vis.v0) {
+    p.start[jobs++] = blocks;
+    blocks += kStatBlocks * t.vis.C;
+  }
   if (blocks == 0) return hipSuccess;
-  for (int j = jobs; j < StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 2; ++j) p.start[j] = blocks;
+  for (int j = jobs; j < StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 3; ++j) p.start[j] = blocks;
   if (t.n_gemm == 0) hipLaunchKernelGGL(step_tail_kernel<false>, dim3(blocks), dim3(kThreads), 0, stream, p);
   else hipLaunchKernelGGL(step_tail_kernel<true>, dim3(blocks), dim3(kThreads), 0, stream, p);
   return hipGetLastError();

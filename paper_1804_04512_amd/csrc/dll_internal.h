@@ -157,6 +157,8 @@ bool wgrad_fewch_shape(int C, int H, int W, int K, int R, int S, int pad, int po
 bool wgrad_fewch_applies(const WgradArgs &a, const WgradPlan &plan);
 hipError_t launch_wgrad_fewch(const WgradArgs &a, const WgradPlan &plan, hipStream_t stream);
 hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &plan, hipStream_t stream);
+// Two unpooled identity layers' filter gradients of one shape in one launch (the CRBM's two phases).
+hipError_t launch_wgrad_two(const WgradArgs &a, const WgradArgs &b, const WgradPlan &plan, hipStream_t stream);
 
 // dw = scale * (sum(pos partials) - sum(neg partials)); optional in-place theta += step * dw.
 struct WgradReduceArgs {
@@ -202,6 +204,7 @@ struct GemmArgs {
   // (softmax - onehot(label)) * sm_scale, sm_rowloss[m] = -ln softmax[label].
   const int *sm_labels = nullptr;
   float *sm_dz = nullptr, *sm_rowloss = nullptr;
+  float *sm_prob = nullptr;   // or, without labels: the softmax itself (an inference pass)
   float sm_scale = 1.0f;
   // The RBM's epilogues, in the small-product kernel only (strides of Cout): sample = 1[uniform < C];
   // sq_partial receives the sums of (sq_ref - C)^2 over gemm_small_tiles(M, N) parts of the result.
@@ -239,14 +242,16 @@ hipError_t launch_softmax_ce(float *logits, const int *labels, int B, int classe
                              float *dlogits, float *rowloss, const float *partial, int split_k, const float *bias,
                              hipStream_t stream);
 
-// prob[n][j] = softmax(logits[n][:])[j] with the row maximum subtracted (inference output).
-hipError_t launch_softmax_prob(const float *logits, int B, int classes, float *prob, hipStream_t stream);
+// prob[n][j] = softmax(logits[n][:])[j] with the row maximum subtracted (inference output).  With partial !=
+// NULL the logits are formed first, as by launch_softmax_ce.
+hipError_t launch_softmax_prob(float *logits, int B, int classes, float *prob, const float *partial, int split_k, const float *bias,
+                               hipStream_t stream);
 
-// CRBM visible statistics: dc[ch] = scale * sum(v0 - v1), mse = mean((v0-v1)^2); scratch: 2 * nblocks floats.
+// CRBM visible statistics from the sums a closing launch left in scratch (visible_stats_scratch_floats floats):
+// dc[ch] = scale * sum(v0 - v1), mse = mean((v0-v1)^2).
 size_t visible_stats_scratch_floats(int N, int C, int HW);
-hipError_t launch_visible_stats(const float *v0, const float *v1, int N, int C, int HW, float scale,
-                                float *dc, float *mse, float *c_update, float step, float *scratch,
-                                hipStream_t stream);
+hipError_t launch_visible_final(int N, int C, int HW, float scale, float *dc, float *mse, float *c_update, float step,
+                                const float *scratch, hipStream_t stream);
 
 hipError_t launch_copy(const float *src, float *dst, size_t count, hipStream_t stream);
 
@@ -273,6 +278,8 @@ struct StepTail {
   GemmArgs gemm[kMaxGemm];   // small products of the weight-gradient form (A contiguous along m, B along n)
   // optional: *loss = sum(rowloss[0 .. rows)) / count (count 0: the number of rows)
   const float *rowloss = nullptr; int rows = 0; float *loss = nullptr; double count = 0.0;
+  // optional: the CRBM's visible sums per channel and slice (launch_visible_final adds them up)
+  struct Visible { const float *v0 = nullptr, *v1 = nullptr; int N = 0, C = 0, HW = 0; float *scratch = nullptr; } vis;
 };
 // Whether a product can be a job of the closing launch.
 bool step_tail_takes(const GemmArgs &g);

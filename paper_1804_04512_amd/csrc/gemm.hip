@@ -743,7 +743,8 @@ __global__ __launch_bounds__(kThreads) void colsum_kernel(const float *A, int M,
 
 // One workgroup per sample: p = softmax(logits) with the row maximum subtracted,
 // rowloss = -ln p[label], dlogits = (p - onehot) / B.  Rows of up to kRowCache classes are kept
-// in LDS between the passes; longer rows are read back from `logits`.
+// in LDS between the passes; longer rows are read back from `logits`.  Without labels (an inference pass) dlogits
+// receives p itself.
 constexpr int kRowCache = 4096;
 __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(float *logits, const int *labels, int B, int classes,
                                                              float *dlogits, float *rowloss, const float *partial,
@@ -807,8 +808,12 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(float *logits, con
   float s = 0.0f;
   for (int j = tid; j < classes; j += kThreads) s += expf(r[j] - m);
   s = block_reduce(s, sh, false);
-  const int label = labels[n];
   const float inv = 1.0f / s, invB = 1.0f / (float)B;
+  if (!labels) {
+    for (int j = tid; j < classes; j += kThreads) dlogits[(long)n * classes + j] = expf(r[j] - m) * inv;
+    return;
+  }
+  const int label = labels[n];
   for (int j = tid; j < classes; j += kThreads) {
     const float pj = expf(r[j] - m) * inv;
     dlogits[(long)n * classes + j] = (pj - (j == label ? 1.0f : 0.0f)) * invB;
@@ -816,62 +821,26 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(float *logits, con
   if (tid == 0) rowloss[n] = -(r[label] - m - logf(s));
 }
 
-// One workgroup per sample: prob = softmax(logits) with the row maximum subtracted.
-__global__ __launch_bounds__(kThreads) void softmax_prob_kernel(const float *logits, int classes, float *prob) {
-  __shared__ float sh[kThreads];
-  const int n = blockIdx.x, tid = threadIdx.x;
-  const float *row = logits + (long)n * classes;
-  float m = -INFINITY;
-  for (int j = tid; j < classes; j += kThreads) m = fmaxf(m, row[j]);
-  m = block_reduce(m, sh, true);
-  float s = 0.0f;
-  for (int j = tid; j < classes; j += kThreads) s += expf(row[j] - m);
-  s = block_reduce(s, sh, false);
-  const float inv = 1.0f / s;
-  for (int j = tid; j < classes; j += kThreads) prob[(long)n * classes + j] = expf(row[j] - m) * inv;
-}
-
 __global__ __launch_bounds__(kThreads) void mean_kernel(const float *v, int count, float *out) { mean_block(v, count, out, (double)count); }
 
-constexpr int kStatBlocks = 32;
-
-// scratch[ch][b] = sum over the block's slice of (v0 - v1); scratch[C*32 + ch*32 + b] = sum of squares
-__global__ __launch_bounds__(kThreads) void visible_stats_kernel(const float *v0, const float *v1, int N, int C, int HW,
-                                                                float *scratch) {
-  __shared__ float sh[kThreads];
-  const int ch = blockIdx.y, b = blockIdx.x;
-  const long per = (long)N * HW;
-  float s = 0.0f, q = 0.0f;
-  for (long e = (long)b * kThreads + threadIdx.x; e < per; e += (long)kStatBlocks * kThreads) {
-    const long nn = e / HW, r = e - nn * HW;
-    const long o = (nn * C + ch) * HW + r;
-    const float d = v0[o] - v1[o];
-    s += d;
-    q += d * d;
-  }
-  s = block_reduce(s, sh, false);
-  q = block_reduce(q, sh, false);
-  if (threadIdx.x == 0) {
-    scratch[ch * kStatBlocks + b] = s;
-    scratch[(C + ch) * kStatBlocks + b] = q;
-  }
-}
-
+// One wavefront: a lane per slice (32 sums, 32 sums of squares), added by lane exchanges in double.
 __global__ void visible_stats_final_kernel(const float *scratch, int N, int C, int HW, float scale, float *dc, float *mse,
                                            float *c_update, float step) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  const int lane = threadIdx.x, b = lane & (kStatBlocks - 1);
+  static_assert(kStatBlocks == 32, "half a wavefront per kind of sum");
   double sq = 0.0;
   for (int ch = 0; ch < C; ++ch) {
-    double s = 0.0;
-    for (int b = 0; b < kStatBlocks; ++b) {
-      s += (double)scratch[ch * kStatBlocks + b];
-      sq += (double)scratch[(C + ch) * kStatBlocks + b];
+    double s = (double)scratch[((lane < 32 ? 0 : C) + ch) * kStatBlocks + b];
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0) {
+      const float g = (float)(s * (double)scale);
+      if (dc) dc[ch] = g;
+      if (c_update) c_update[ch] += step * g;
     }
-    const float g = (float)(s * (double)scale);
-    if (dc) dc[ch] = g;
-    if (c_update) c_update[ch] += step * g;
+    sq += s;   // lanes 32 ..: the channel's squares
   }
-  if (mse) *mse = (float)(sq / ((double)N * C * HW));
+  if (mse && lane == 32) *mse = (float)(sq / ((double)N * C * HW));
 }
 
 __global__ __launch_bounds__(kThreads) void copy_kernel(const float *src, float *dst, size_t count) {
@@ -1009,18 +978,17 @@ hipError_t launch_softmax_ce(float *logits, const int *labels, int B, int classe
   return hipGetLastError();
 }
 
-hipError_t launch_softmax_prob(const float *logits, int B, int classes, float *prob, hipStream_t stream) {
-  hipLaunchKernelGGL(softmax_prob_kernel, dim3(B), dim3(kThreads), 0, stream, logits, classes, prob);
+hipError_t launch_softmax_prob(float *logits, int B, int classes, float *prob, const float *partial, int split_k, const float *bias,
+                               hipStream_t stream) {
+  hipLaunchKernelGGL(softmax_ce_kernel, dim3(B), dim3(kThreads), 0, stream, logits, nullptr, B, classes, prob, nullptr, partial,
+                     split_k, bias);
   return hipGetLastError();
 }
 
 size_t visible_stats_scratch_floats(int, int C, int) { return (size_t)2 * C * kStatBlocks; }
 
-hipError_t launch_visible_stats(const float *v0, const float *v1, int N, int C, int HW, float scale, float *dc, float *mse,
-                                float *c_update, float step, float *scratch, hipStream_t stream) {
-  hipLaunchKernelGGL(visible_stats_kernel, dim3(kStatBlocks, C), dim3(kThreads), 0, stream, v0, v1, N, C, HW, scratch);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+hipError_t launch_visible_final(int N, int C, int HW, float scale, float *dc, float *mse, float *c_update, float step,
+                                const float *scratch, hipStream_t stream) {
   hipLaunchKernelGGL(visible_stats_final_kernel, dim3(1), dim3(64), 0, stream, scratch, N, C, HW, scale, dc, mse, c_update,
                      step);
   return hipGetLastError();

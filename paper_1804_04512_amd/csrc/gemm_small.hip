@@ -60,6 +60,7 @@ bool gemm_prefers_small(const GemmArgs &a) {
 bool gemm_fuses_softmax(int M, int N, int Kdim) { return gemm_is_small(M, N, Kdim) && N <= 16 && (M + 31) / 32 <= 512; }
 
 hipError_t launch_gemm_small(const GemmArgs &a, hipStream_t stream) {
+  if (a.sm_prob && (a.sm_labels || !gemm_fuses_softmax(a.M, a.N, a.Kdim) || a.act != ACT_IDENTITY || a.update || a.C_ref)) return hipErrorInvalidValue;
   if (a.sm_labels && (!gemm_fuses_softmax(a.M, a.N, a.Kdim) || !a.sm_dz || !a.sm_rowloss || a.act != ACT_IDENTITY || a.update ||
                       a.C_ref))
     return hipErrorInvalidValue;
@@ -78,7 +79,7 @@ hipError_t launch_gemm_small(const GemmArgs &a, hipStream_t stream) {
 #define DLL_SMALL(BK_, WH, EX) (fine ? launch(gemm_small_kernel<BK_, WH, 4, 1, EX>) : launch(gemm_small_kernel<BK_, WH, 4, 2, EX>))
 #define DLL_SMALL_B(WH, EX) (b_kc ? DLL_SMALL(true, WH, EX) : DLL_SMALL(false, WH, EX))
   if (a.uniform || a.sq_ref) {
-    if (a.sm_labels || (a.uniform && !a.sample) || (a.sq_ref && !a.sq_partial)) return hipErrorInvalidValue;
+    if (a.sm_labels || a.sm_prob || (a.uniform && !a.sample) || (a.sq_ref && !a.sq_partial)) return hipErrorInvalidValue;
     return p.whole ? DLL_SMALL_B(true, true) : DLL_SMALL_B(false, true);
   }
   return p.whole ? DLL_SMALL_B(true, false) : DLL_SMALL_B(false, false);

@@ -187,11 +187,11 @@ __device__ __forceinline__ void tile_product(const SmallParams &p, int mt, int n
       sq[v] = a.sq_ref ? a.sq_ref[o[v]] : 0.0f;
     }
   }
-  if (Q == 1 && a.sm_labels) {
-    // Softmax + cross-entropy on the finished logits: a row's 16 columns sit in the four lanes
-    // i16, i16 + 16, i16 + 32, i16 + 48 (four columns each), so two exchanges complete a row.
+  if (Q == 1 && (a.sm_labels || a.sm_prob)) {
+    // Softmax (+ cross-entropy where there are labels) on the finished logits: a row's 16 columns sit in the four
+    // lanes i16, i16 + 16, i16 + 32, i16 + 48 (four columns each), so two exchanges complete a row.
     // Columns past N count as -inf / 0; rows past M compute on clamped data and store nothing.
-    const int label = a.sm_labels[min(m, a.M - 1)];
+    const int label = a.sm_labels ? a.sm_labels[min(m, a.M - 1)] : -1;
     float z[4], mx = -INFINITY;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -213,6 +213,7 @@ __device__ __forceinline__ void tile_product(const SmallParams &p, int mt, int n
     for (int v = 0; v < 4; ++v) {
       if (!ok[v]) continue;
       if (a.Cout) a.Cout[o[v]] = z[v];
+      if (a.sm_prob) { a.sm_prob[o[v]] = e[v] * inv; continue; }
       a.sm_dz[o[v]] = (e[v] * inv - (n + v == label ? 1.0f : 0.0f)) * a.sm_scale;
       if (n + v == label) a.sm_rowloss[m] = -(z[v] - mx - logf(sum));
     }
