@@ -83,12 +83,12 @@ __device__ __forceinline__ float dz_value(const WgradArgs &a, int Ho, int Wo, in
 __host__ __device__ __forceinline__ bool reads_output(int act) { return act == ACT_SIGMOID || act == ACT_RELU; }
 
 // Registers that carry one tile from global memory to LDS (fast path).
-template <int MTF, int POOL, int XI, int XH>
+template <int MTF, int POOL, int XI, int XH, bool Y>
 struct TileRegs {
   static constexpr int DZR = POOL == 2 ? MTF : 4 * MTF;   // staging rounds over the filter planes
   float4 xi[XI];
   float xh[XH];
-  float4 dyv[DZR], yv[DZR];
+  float4 dyv[DZR], yv[Y ? DZR : 1];
   uchar4 iv[DZR];
   int xlim, dlim;   // ragged rows: elements of the thread's 16-byte groups that lie inside their row (4 or more: all)
 };
@@ -103,8 +103,11 @@ struct TileRegs {
 // on the way to LDS.  Bound by the matrix pipe like the aligned form; the element-wise staging (0)
 // that such layers took before waits for each load behind its branch.  Filter gradient of
 // 33 x 24 x 45 x 51 images, 40 filters 3x3 (this kernel): 122 -> 43 us.
-template <int MTF, int NTT, int POOL, int FAST>
-__global__ __launch_bounds__(kThreads) void wgrad_kernel(const WgradParams p) {
+// Y: the layer output is read (sigmoid, ReLU without flags).  Unpooled layers whose derivative is 1 (the
+// CRBM's statistics among them) have an instance without those registers, four per 16 filters and row pair: two
+// workgroups per CU where there was one (64 x 28 x 28, 40 filters 9x9, both phases: 32 -> 22 us).
+template <int MTF, int NTT, int POOL, int FAST, bool Y>
+__global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_kernel(const WgradParams p) {
   constexpr bool ONE_ROUND = FAST == 2 || FAST == 4, RAGGED = FAST >= 3;
   constexpr int XI = ONE_ROUND ? 1 : NXI, XH = ONE_ROUND ? 1 : NXH;
   extern __shared__ float lds[];
@@ -122,7 +125,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const WgradParams p) {
   const int RSf = a.R * a.S;
   const int lines = p.CC * p.rows;
   constexpr int RW = TH / 4;                    // rows per wave
-  constexpr int DZR = TileRegs<MTF, POOL, XI, XH>::DZR;
+  constexpr int DZR = TileRegs<MTF, POOL, XI, XH, Y>::DZR;
 
   floatx4 acc[MTF][NTT];
 #pragma unroll
@@ -147,7 +150,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const WgradParams p) {
 #pragma unroll
   for (int mf = 0; mf < MTF; ++mf) fplane[mf] = min(mf * 16 + i16, kcount - 1) * PSZ;
 
-  TileRegs<MTF, POOL, XI, XH> tr;
+  TileRegs<MTF, POOL, XI, XH, Y> tr;
 
   // ---- fast path: everything about a thread's staging slots that does not depend on the
   // tile (which element of the tile it moves, where it lands in LDS) is worked out once here;
@@ -273,7 +276,8 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const WgradParams p) {
     for (int rd = 0; rd < DZR; ++rd) {
       const int eo = in ? dzo[rd] : (int)(kOob >> 2);
       tr.dyv[rd] = ldx4(rs_dy, 4 * eo, 4u * dbase);
-      if (reads_output(a.act)) tr.yv[rd] = ldx4(rs_y, 4 * eo, 4u * dbase);
+      if constexpr (Y)
+        if (reads_output(a.act)) tr.yv[rd] = ldx4(rs_y, 4 * eo, 4u * dbase);
       if constexpr (POOL == 2 && RAGGED) {   // bytes: a group of four need not start at a whole dword
         tr.iv[rd].x = __builtin_amdgcn_raw_buffer_load_b8(rs_idx, eo, (int)dbase, 0);
         tr.iv[rd].y = __builtin_amdgcn_raw_buffer_load_b8(rs_idx, eo + 1, (int)dbase, 0);
@@ -310,11 +314,12 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const WgradParams p) {
     for (int rd = 0; rd < DZR; ++rd) {
       if (!dzk[rd]) continue;
       const float gv[4] = {tr.dyv[rd].x, tr.dyv[rd].y, tr.dyv[rd].z, tr.dyv[rd].w};
-      const float ov[4] = {tr.yv[rd].x, tr.yv[rd].y, tr.yv[rd].z, tr.yv[rd].w};
+      const float4 yq = tr.yv[Y ? rd : 0];
+      const float ov[4] = {yq.x, yq.y, yq.z, yq.w};
       float g[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        g[e] = reads_output(ACT) ? gv[e] * act_deriv(ACT, ov[e]) : gv[e];
+        g[e] = Y && reads_output(ACT) ? gv[e] * act_deriv(ACT, ov[e]) : gv[e];
         if (RAGGED && e > 0 && e >= tr.dlim) g[e] = 0.0f;
       }
       float *d = dzs + dzl[rd];
@@ -344,9 +349,9 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const WgradParams p) {
     }
   };
   auto store_tile = [&]() {
-    if (a.act == ACT_SIGMOID) store_tile_as(std::integral_constant<int, ACT_SIGMOID>{});
-    else if (a.act == ACT_RELU) store_tile_as(std::integral_constant<int, ACT_RELU>{});
-    else if (a.act == ACT_RELU_FLAGGED) store_tile_as(std::integral_constant<int, ACT_RELU_FLAGGED>{});
+    if (Y && a.act == ACT_SIGMOID) store_tile_as(std::integral_constant<int, Y ? ACT_SIGMOID : ACT_IDENTITY>{});
+    else if (Y && a.act == ACT_RELU) store_tile_as(std::integral_constant<int, Y ? ACT_RELU : ACT_IDENTITY>{});
+    else if (POOL == 2 && a.act == ACT_RELU_FLAGGED) store_tile_as(std::integral_constant<int, POOL == 2 ? ACT_RELU_FLAGGED : ACT_IDENTITY>{});
     else store_tile_as(std::integral_constant<int, ACT_IDENTITY>{});
   };
 
@@ -805,16 +810,19 @@ hipError_t launch_wgrad_t(const WgradParams &p, const WgradPlan &plan, Staging h
     hipLaunchKernelGGL(kern, grid, dim3(kThreads), plan.lds_bytes, stream, p);
     return hipGetLastError();
   };
-  const bool pooled = p.a.pool == 2;
-  if (how == Staging::kElements) return launch(wgrad_kernel<MTF, NTT, 1, 0>);
+  const bool pooled = p.a.pool == 2, y = reads_output(p.a.act);
+  if (how == Staging::kElements) return launch(wgrad_kernel<MTF, NTT, 1, 0, true>);
+  auto form = [&](auto fastc) {
+    constexpr int FAST = decltype(fastc)::value;
+    if (pooled) return launch(wgrad_kernel<MTF, NTT, 2, FAST, true>);
+    return y ? launch(wgrad_kernel<MTF, NTT, 1, FAST, true>) : launch(wgrad_kernel<MTF, NTT, 1, FAST, false>);
+  };
   if constexpr (NTT == 2) {
     if (p.nxi <= 1 && p.nxh <= 1) {   // one staging round: the instances with the small loader
-      if (how == Staging::kRagged) return pooled ? launch(wgrad_kernel<MTF, NTT, 2, 4>) : launch(wgrad_kernel<MTF, NTT, 1, 4>);
-      return pooled ? launch(wgrad_kernel<MTF, NTT, 2, 2>) : launch(wgrad_kernel<MTF, NTT, 1, 2>);
+      return how == Staging::kRagged ? form(std::integral_constant<int, 4>{}) : form(std::integral_constant<int, 2>{});
     }
   }
-  if (how == Staging::kRagged) return pooled ? launch(wgrad_kernel<MTF, NTT, 2, 3>) : launch(wgrad_kernel<MTF, NTT, 1, 3>);
-  return pooled ? launch(wgrad_kernel<MTF, NTT, 2, 1>) : launch(wgrad_kernel<MTF, NTT, 1, 1>);
+  return how == Staging::kRagged ? form(std::integral_constant<int, 3>{}) : form(std::integral_constant<int, 1>{});
 }
 template <int MTF>
 hipError_t launch_wgrad_m(const WgradParams &p, const WgradPlan &plan, Staging how, hipStream_t stream) {
