@@ -269,10 +269,12 @@ __device__ __forceinline__ void engine_epilogue(const ConvEngineArgs &a, floatx4
 // element had an address of its own, walked with divergent carries, four at a time:
 // 33 x 40 x 45 x 51 gradients, 24 channels 3x3: 74 -> 67 us; 100 x 8 x 12 x 12, 8 filters 5x5: 14.9 -> 9.5.
 // Bound by the latency of that chain for a few channels, by the matrix pipe for many.
-// kBatch: values of the halo tile in flight per thread: 8 where that is all of them (one to three channels), which
-// leaves registers for twice the wavefronts, else 16, or 12 with everything dz needs.  WIDE: 64-bit offsets, for planes or filter rows of 4 GiB.
+// kBatch: values of the halo tile in flight per thread: 8 where that is all of them (one to three channels) and
+// where dz needs three loads for each, else 12.  Three workgroups per CU up to 32 output channels: layers with
+// large filters live from their number (64 x 32 x 43 x 43 behind 32 maps, 12x12: 759 us with two, 629 before).
+// WIDE: 64-bit offsets, for planes or filter rows of 4 GiB.
 template <int NT, int RP, int MT, bool DZ, int kBatch, bool WIDE = false>
-__global__ __launch_bounds__(kThreads, 2) void conv_engine_kernel(const EngineParams p) {
+__global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 && !WIDE ? 3 : 2) void conv_engine_kernel(const EngineParams p) {
   extern __shared__ float lds[];
   const ConvEngineArgs &a = p.a;
   const EngineGeom &g = p.g;
@@ -363,7 +365,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_engine_kernel(const EnginePa
 
   // ---- filter slice wl[nt][kk][j] = wgt(ko0 + 16nt + j, c0 + cl, r, s), kk = (r*S + s)*CC + cl: sixteen threads take the
   // 16 columns j of a (channel, tap); a thread keeps its channel and steps through the taps, `tstep` at a time
-  constexpr int kTaps = NT == 1 ? 9 : (NT == 2 ? 6 : 4);
+  constexpr int kTaps = NT == 1 ? 9 : (NT == 2 && !DZ ? 6 : 4);
   const int fj = tid & 15, fs = tid >> 4;
   const int fcl = fs & ((1 << g.cw_log) - 1), frs = fs >> g.cw_log, tstep = 16 >> g.cw_log;
   float tv[NT][kTaps];
@@ -537,9 +539,9 @@ hipError_t launch_t(const ConvEngineArgs &a, hipStream_t stream) {
   if (blocks <= 0 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks, (unsigned)p.g.kgroups, 1);
   const bool shallow = (p.g.rows * p.g.cols + kThreads - 1) / kThreads * p.g.CC <= 8;
-  if (a.src_dz) hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, true, 12, WIDE>), grid, dim3(kThreads), lds, stream, p);
+  if (a.src_dz) hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, true, 8, WIDE>), grid, dim3(kThreads), lds, stream, p);
   else if (shallow) hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, false, 8, WIDE>), grid, dim3(kThreads), lds, stream, p);
-  else hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, false, 16, WIDE>), grid, dim3(kThreads), lds, stream, p);
+  else hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, false, 12, WIDE>), grid, dim3(kThreads), lds, stream, p);
   return hipGetLastError();
 }
 
