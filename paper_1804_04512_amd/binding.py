@@ -101,12 +101,11 @@ def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()   # argtypes turn the number into a pointer
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    return (stream if stream is not None else torch.cuda.current_stream()).cuda_stream
 
 
 def _ok(status: int, where: str):

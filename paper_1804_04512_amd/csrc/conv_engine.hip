@@ -271,7 +271,7 @@ __device__ __forceinline__ void engine_epilogue(const ConvEngineArgs &a, floatx4
 // Bound by the latency of that chain for a few channels, by the matrix pipe for many.
 // kBatch: values of the halo tile in flight per thread: 8 where that is all of them (one to three channels) and
 // where dz needs three loads for each, else 12.  Three workgroups per CU up to 32 output channels: layers with
-// large filters live from their number (64 x 32 x 43 x 43 behind 32 maps, 12x12: 759 us with two, 629 before).
+// large filters live from their number (64 x 32 x 43 x 43 behind 32 maps, 12x12: 759 us with two, 604 with three).
 // WIDE: 64-bit offsets, for planes or filter rows of 4 GiB.
 template <int NT, int RP, int MT, bool DZ, int kBatch, bool WIDE = false>
 __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 && !WIDE ? 3 : 2) void conv_engine_kernel(const EngineParams p) {
