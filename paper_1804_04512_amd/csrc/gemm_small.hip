@@ -16,8 +16,8 @@
 //     on timing), and one wavefront per 16 x 16 quarter of the tile finishes it: bias, activation,
 //     act' of a reference tensor, store and/or fused parameter update.  No split-K partials in
 //     global memory, no reduction launch.
-// Every global load is issued unconditionally from a clamped address; nothing is masked before
-// the multiplication needs it.
+// Every global load is a range-checked buffer load: what lies past an operand's end reads as zero, so nothing
+// is masked but the rows that are no whole 16-byte groups, and that at the multiplication.
 #include "dll_internal.h"
 #include "gemm_small_body.h"
 
