@@ -357,10 +357,10 @@ dll_status dll_conv_valid_wgrad_noalloc(const dll_conv_desc *d, const float *x, 
 
 size_t dll_crbm_workspace_bytes(const dll_conv_desc *d) {
   if (check_desc(d, false) != DLL_OK) return 0;
-  WgradPlan plan;
-  if (!plan_for(d, &plan)) return 0;
   dll_conv_desc t = *d;
-  t.pool = 1;
+  t.pool = 1;   // the descriptor's own is ignored by the step, so by its plan too
+  WgradPlan plan;
+  if (!plan_for(&t, &plan)) return 0;
   Carver c(nullptr, 0);
   c.floats(y_count(&t)); c.floats(y_count(&t)); c.floats(y_count(&t));  // h0p, h0s, h1p
   c.floats(x_count(&t));                                                // v1
