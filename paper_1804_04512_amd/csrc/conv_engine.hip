@@ -37,6 +37,8 @@ struct EngineGeom {
   int tiles_x, tiles_y;
   int kgroups;       // groups of NT*16 output channels (gridDim.y)
   int cw_log;        // generic kernel: log2 of the next power of two of CC
+  int jw_log;        // lean kernel: log2 of the filter columns staged per N-tile (16, or fewer when Kout is small)
+  int split_log;     // generic kernel, dz source: log2 of the thread groups that stage channels side by side
   unsigned src_bytes; // 3x3 instance: bytes of the source tensor (below 2 GiB)
   int pack3;          // 3x3 instance, three input channels: the 27 taps run as 7 MFMA steps, not 9
 };
@@ -90,8 +92,10 @@ __device__ __forceinline__ void lane_bias(const ConvEngineArgs &a, int ko0, int 
 
 // Epilogue shared by the engine kernels.  Lane owns output channel ko0+16nt+i16, window column
 // MT*kq+mt of the tile, window row wave*RP+rp; acc[..][v] is window position v = 2a+b.
-// AHEAD: the sampling epilogue asks for its uniform numbers before their first use (registers the 3x3 instances lack).
-template <int NT, int RP, int ACT, int POOL, int MT = 4, bool AHEAD = false>
+// SAMPLING: states are drawn where a.sample asks for them, from uniform numbers loaded beside their use or (kAhead) before
+// the first one, in registers the 3x3 instances lack; kNever: the launch has none.
+enum Sampling { kNever, kBeside, kAhead };
+template <int NT, int RP, int ACT, int POOL, int MT = 4, Sampling SAMPLING = kBeside>
 __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floatx4 (&acc)[RP][MT][NT], const float (&bias)[NT],
                                                 int n, int ko0, int oy0, int ox0, int wave, int i16, int kq) {
 #pragma unroll
@@ -140,7 +144,7 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
         // the uniform numbers of the lane's windows, all of them ahead of the first use and from clamped addresses
         // (a load beside its use would be waited for on its own, one row of one channel group after the other)
         float uh[2][2 * MT];
-        if (AHEAD && a.sample && ACT != ACT_PMP) {
+        if (SAMPLING == kAhead && a.sample && ACT != ACT_PMP) {
           const int plane_o = (n * a.Kout + ko) * a.Hout * a.Wout;
 #pragma unroll
           for (int wa2 = 0; wa2 < 2; ++wa2)
@@ -165,7 +169,7 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
           const int Hp = a.Hout >> 1, Wp = a.Wout >> 1;
           const int ob = ((n * a.Kout + ko) * Hp + py) * Wp + px0;
           float ub[MT];   // the blocks' uniform numbers, loaded together from clamped addresses
-          if (a.sample) {
+          if (SAMPLING != kNever && a.sample) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) ub[mt] = a.uniform[ob - px0 + min(px0 + mt, Wp - 1)];   // stays inside the row
           }
@@ -173,7 +177,7 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
           for (int mt = 0; mt < MT; ++mt) {
             if (px0 + mt >= Wp) continue;
             if (a.out_pool) a.out_pool[ob + mt] = (pr[mt][0] + pr[mt][1]) + (pr[mt][2] + pr[mt][3]);
-            if (a.sample) {
+            if (SAMPLING != kNever && a.sample) {
               const float u = ub[mt];
               float lo = 0.0f;
               bool taken = false;
@@ -207,8 +211,8 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
             if constexpr (MT == 4) {
             *reinterpret_cast<float4 *>(a.out + o) = make_float4(yv[0], yv[1], yv[2], yv[3]);
             *reinterpret_cast<float4 *>(a.out + o + 4) = make_float4(yv[4], yv[5], yv[6], yv[7]);
-            if (a.sample) {
-              if (!AHEAD && ACT != ACT_PMP) {
+            if (SAMPLING != kNever && a.sample) {
+              if (SAMPLING == kBeside && ACT != ACT_PMP) {
                 const float4 u0 = *reinterpret_cast<const float4 *>(a.uniform + o);
                 const float4 u1 = *reinterpret_cast<const float4 *>(a.uniform + o + 4);
                 uh[wa2][0] = u0.x; uh[wa2][1] = u0.y; uh[wa2][2] = u0.z; uh[wa2][3] = u0.w;
@@ -223,7 +227,7 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
             }
             }
           } else {
-            if (!AHEAD && a.sample && ACT != ACT_PMP) {   // from clamped addresses: they stay inside the row
+            if (SAMPLING == kBeside && a.sample && ACT != ACT_PMP) {   // from clamped addresses: they stay inside the row
 #pragma unroll
               for (int e = 0; e < 2 * MT; ++e) uh[wa2][e] = a.uniform[o - ox + min(ox + e, a.Wout - 1)];
             }
@@ -231,7 +235,7 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
             for (int e = 0; e < 2 * MT; ++e)
               if (ox + e < a.Wout) {
                 a.out[o + e] = yv[e];
-                if (a.sample) a.sample[o + e] = ACT == ACT_PMP ? sv[e] : (uh[wa2][e] < yv[e] ? 1.f : 0.f);
+                if (SAMPLING != kNever && a.sample) a.sample[o + e] = ACT == ACT_PMP ? sv[e] : (uh[wa2][e] < yv[e] ? 1.f : 0.f);
               }
           }
         }
@@ -242,10 +246,10 @@ __device__ __forceinline__ void engine_epilogue_as(const ConvEngineArgs &a, floa
 
 // The activation and the pooling mode are fixed for a launch: dispatch once, so that the
 // per-element code carries no branches on them.
-template <int NT, int RP, int MT = 4, bool AHEAD = false>
+template <int NT, int RP, int MT = 4, Sampling SAMPLING = kBeside>
 __device__ __forceinline__ void engine_epilogue(const ConvEngineArgs &a, floatx4 (&acc)[RP][MT][NT], const float (&bias)[NT],
                                                 int n, int ko0, int oy0, int ox0, int wave, int i16, int kq) {
-#define DLL_EPI(ACT_, POOL_) engine_epilogue_as<NT, RP, ACT_, POOL_, MT, AHEAD>(a, acc, bias, n, ko0, oy0, ox0, wave, i16, kq)
+#define DLL_EPI(ACT_, POOL_) engine_epilogue_as<NT, RP, ACT_, POOL_, MT, SAMPLING>(a, acc, bias, n, ko0, oy0, ox0, wave, i16, kq)
   if (a.pool == 2) {
     if (a.act == ACT_RELU) DLL_EPI(ACT_RELU, 2);
     else if (a.act == ACT_SIGMOID) DLL_EPI(ACT_SIGMOID, 2);
@@ -257,6 +261,50 @@ __device__ __forceinline__ void engine_epilogue(const ConvEngineArgs &a, floatx4
     else DLL_EPI(ACT_IDENTITY, 1);
   }
 #undef DLL_EPI
+}
+
+// The MFMAs over a staged chunk's taps, software-pipelined over two register sets: while step t is
+// multiplied, the operand fragments of step t+1 are on their way from LDS and the tap offset of
+// step t+2 is being read (offset -> fragment -> MFMA is a chain of two LDS latencies that a
+// plain loop would pay at every step).  Steps past the end re-read the last step and are not
+// multiplied.
+template <int NT, int RP, int MT>
+__device__ __forceinline__ void multiply_chunk(const EngineGeom &g, const float *xs, const float *wl, const int *koff, int a_base, int i16,
+                                               int kq, floatx4 (&acc)[RP][MT][NT]) {
+  float afA[RP * MT], bfA[NT], afB[RP * MT], bfB[NT];
+  auto load_step = [&](int t, int o, float (&af)[RP * MT], float (&bf)[NT]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) bf[nt] = wl[(nt * g.KC + 4 * t + kq) * 16 + i16];
+#pragma unroll
+    for (int rp = 0; rp < RP; ++rp)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) af[rp * MT + mt] = xs[a_base + rp * 2 * g.RS + o + 2 * mt];
+  };
+  auto mfma_step = [&](const float (&af)[RP * MT], const float (&bf)[NT]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int rp = 0; rp < RP; ++rp)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          acc[rp][mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[rp * MT + mt], bf[nt], acc[rp][mt][nt], 0, 0, 0);
+  };
+  const int last = g.KS - 1;
+  int o1 = koff[4 * min(1, last) + kq];
+  load_step(0, koff[kq], afA, bfA);
+  for (int t = 0; t < g.KS; t += 2) {
+    const int o2 = koff[4 * min(t + 2, last) + kq];
+    load_step(min(t + 1, last), o1, afB, bfB);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_step(afA, bfA);
+    __builtin_amdgcn_sched_barrier(0);
+    const int o3 = koff[4 * min(t + 3, last) + kq];
+    load_step(min(t + 2, last), o2, afA, bfA);
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 1 < g.KS) mfma_step(afB, bfB);
+    __builtin_amdgcn_sched_barrier(0);
+    o1 = o3;
+  }
 }
 
 // The generic instance: any filter, any channel count.  MT: pooling windows per lane and row pair, i.e. the tile is
@@ -272,9 +320,8 @@ __device__ __forceinline__ void engine_epilogue(const ConvEngineArgs &a, floatx4
 // kBatch: values of the halo tile in flight per thread: 8 where that is all of them (one to three channels) and
 // where dz needs three loads for each, else 12.  Three workgroups per CU up to 32 output channels: layers with
 // large filters live from their number (64 x 32 x 43 x 43 behind 32 maps, 12x12: 759 us with two, 604 with three).
-// WIDE: 64-bit offsets, for planes or filter rows of 4 GiB.
-template <int NT, int RP, int MT, bool DZ, int kBatch, bool WIDE = false>
-__global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 && !WIDE ? 3 : 2) void conv_engine_kernel(const EngineParams p) {
+template <int NT, int RP, int MT, bool DZ, int kBatch>
+__global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 ? 3 : 2) void conv_engine_kernel(const EngineParams p) {
   extern __shared__ float lds[];
   const ConvEngineArgs &a = p.a;
   const EngineGeom &g = p.g;
@@ -300,31 +347,33 @@ __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 && !WIDE ? 3 : 2) void 
   const bool need_y = DZ && reads_output(a.src_act);
   const int sh = pooled ? 1 : 0, Ws = a.Win >> sh, plane = (a.Hin >> sh) * Ws;   // a plane as it is stored
   // one uniform base plus a 32-bit byte offset per lane: the form that costs no address arithmetic per load
-  auto fetch = [](const auto *base, auto offset) __attribute__((always_inline)) {
+  auto fetch = [](const auto *base, int offset) __attribute__((always_inline)) {
     using T = std::remove_cv_t<std::remove_reference_t<decltype(*base)>>;
-    if constexpr (WIDE) return base[offset];
-    else return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + (unsigned)offset * (unsigned)sizeof(T));
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + (unsigned)offset * (unsigned)sizeof(T));
   };
   // offsets are taken from the tile's first row and column inside the image
   const int gi0 = max(oy0 - a.pad_h, 0) >> sh, gj0 = max(ox0 - a.pad_w, 0) >> sh;
-  const int drow = kThreads / g.cols, dcol = kThreads - drow * g.cols;
-  const int row0 = tid / g.cols, col0 = tid - row0 * g.cols;
-  int row = row0, col = col0, cl = 0;   // the next pair
+  // dz: the threads work in groups of one, two or four wavefronts, a group on every first, second or fourth channel
+  const int groups = DZ ? 1 << g.split_log : 1, span_log = DZ ? 8 - g.split_log : 8, span = 1 << span_log;
+  const int cl0 = DZ ? __builtin_amdgcn_readfirstlane(tid >> span_log) : 0, st = tid & (span - 1);
+  const int drow = span / g.cols, dcol = span - drow * g.cols;
+  const int row0 = st / g.cols, col0 = st - row0 * g.cols;
+  constexpr int kZero = 1 << 30, kPlace = 1 << 20;   // (LDS offsets are below 2^14)
+  int row = row0, col = col0, cl = cl0;   // the next pair
   int o = 0, at = 0;                    // its position's offset in a plane and in LDS
   bool in = false;
-  unsigned char place = 0;              // its position's place in the pooling window
+  int place = 0;                        // its position's place in the pooling window, as a field of dst
   auto look = [&]() __attribute__((always_inline)) {
     const int gi = oy0 - a.pad_h + row, gj = ox0 - a.pad_w + col;
     in = row < g.rows && gi >= 0 && gi < a.Hin && gj >= 0 && gj < a.Win;
     o = in ? ((gi >> sh) - gi0) * Ws + (gj >> sh) - gj0 : 0;
     at = row * g.RS + col;
-    place = (unsigned char)(((gi & 1) << 1) | (gj & 1));
+    place = (((gi & 1) << 1) | (gj & 1)) * kPlace;
   };
-  const int pairs = (positions + kThreads - 1) / kThreads * g.CC;
+  const int pairs = ((positions + span - 1) >> span_log) * (DZ ? (g.CC - cl0 + groups - 1) >> g.split_log : g.CC);
   float gv[kBatch], yv[DZ ? kBatch : 1];
-  unsigned char fv[DZ ? kBatch : 1], want[DZ ? kBatch : 1];
-  int dst[kBatch];                      // LDS offset; negative: nothing to store; with kZero: a channel past the last
-  constexpr int kZero = 1 << 30;
+  unsigned char fv[DZ ? kBatch : 1];
+  int dst[kBatch];                      // LDS offset, place; negative: nothing to store; with kZero: a channel past the last
   auto load_halo = [&](int c0, int q0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
@@ -332,14 +381,13 @@ __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 && !WIDE ? 3 : 2) void 
       // a position outside the image and a channel past the last read an element that exists
       const long base = (long)(n * a.Cin + min(c0 + cl, a.Cin - 1)) * plane + (long)gi0 * Ws + gj0;
       gv[u] = fetch(a.src + base, o);
-      dst[u] = in ? (cl * g.PS + at) | (c0 + cl < a.Cin ? 0 : kZero) : -1;
+      dst[u] = in ? (cl * g.PS + at) | (c0 + cl < a.Cin ? 0 : kZero) | (DZ ? place : 0) : -1;
       if constexpr (DZ) {
         if (need_y) yv[u] = fetch(a.src_y + base, o);
         if (pooled) fv[u] = fetch(a.src_idx + base, o);
-        want[u] = place;
       }
-      if (++cl == g.CC) {
-        cl = 0;
+      if ((cl += groups) >= g.CC) {
+        cl = cl0;
         row += drow;
         col += dcol;
         if (col >= g.cols) { col -= g.cols; ++row; }
@@ -354,12 +402,12 @@ __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 && !WIDE ? 3 : 2) void 
       float v = gv[u];
       if constexpr (DZ) {
         // dz at a pre-pool position: dy routed to the recorded arg-max, times act'(y)
-        if (pooled && (fv[u] & kIdxPosMask) != want[u]) v = 0.0f;
+        if (pooled && (fv[u] & kIdxPosMask) * kPlace != (dst[u] & (kIdxPosMask * kPlace))) v = 0.0f;
         if (a.src_act == ACT_RELU_FLAGGED) v = (fv[u] & kIdxInactive) ? 0.0f : v;
         else if (a.src_act == ACT_SIGMOID) v *= yv[u] * (1.0f - yv[u]);
         else if (a.src_act == ACT_RELU) v = yv[u] > 0.0f ? v : 0.0f;
       }
-      if (dst[u] >= 0) xs[dst[u] & (kZero - 1)] = (dst[u] & kZero) ? 0.0f : v;
+      if (dst[u] >= 0) xs[dst[u] & (kPlace - 1)] = (dst[u] & kZero) ? 0.0f : v;
     }
   };
 
@@ -381,7 +429,7 @@ __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 && !WIDE ? 3 : 2) void 
       for (int u = 0; u < kTaps; ++u) {
         if (r0 + u * tstep >= RSf) break;
         const int rs = min(r0 + u * tstep + frs, RSf - 1), at = a.w_flip ? RSf - 1 - rs : rs;
-        const float v = WIDE ? fetch(base, lane_o + at) : fetch(base, (int)lane_o + at);
+        const float v = fetch(base, (int)lane_o + at);
         tv[nt][u] = ok ? v : 0.0f;
       }
     }
@@ -430,52 +478,12 @@ __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 && !WIDE ? 3 : 2) void 
   for (int chunk = 0; chunk <= g.nchunks; ++chunk) {
     const int c0 = chunk * g.CC;
     if (chunk < g.nchunks) {
-      row = row0; col = col0; cl = 0;
+      row = row0; col = col0; cl = cl0;
       look();
       load_halo(c0, 0);
       load_taps(c0, 0);
     }
-    // ---- MFMA over the chunk's taps, software-pipelined over two register sets: while step t is
-    // multiplied, the operand fragments of step t+1 are on their way from LDS and the tap offset of
-    // step t+2 is being read (offset -> fragment -> MFMA is a chain of two LDS latencies that a
-    // plain loop would pay at every step).  Steps past the end re-read the last step and are not
-    // multiplied.
-    if (chunk > 0) {
-      float afA[RP * MT], bfA[NT], afB[RP * MT], bfB[NT];
-      auto load_step = [&](int t, int o, float (&af)[RP * MT], float (&bf)[NT]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) bf[nt] = wl[(nt * g.KC + 4 * t + kq) * 16 + i16];
-#pragma unroll
-        for (int rp = 0; rp < RP; ++rp)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) af[rp * MT + mt] = xs[a_base + rp * 2 * g.RS + o + 2 * mt];
-      };
-      auto mfma_step = [&](const float (&af)[RP * MT], const float (&bf)[NT]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int rp = 0; rp < RP; ++rp)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-              acc[rp][mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[rp * MT + mt], bf[nt], acc[rp][mt][nt], 0, 0, 0);
-      };
-      const int last = g.KS - 1;
-      int o1 = koff[4 * min(1, last) + kq];
-      load_step(0, koff[kq], afA, bfA);
-      for (int t = 0; t < g.KS; t += 2) {
-        const int o2 = koff[4 * min(t + 2, last) + kq];
-        load_step(min(t + 1, last), o1, afB, bfB);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_step(afA, bfA);
-        __builtin_amdgcn_sched_barrier(0);
-        const int o3 = koff[4 * min(t + 3, last) + kq];
-        load_step(min(t + 2, last), o2, afA, bfA);
-        __builtin_amdgcn_sched_barrier(0);
-        if (t + 1 < g.KS) mfma_step(afB, bfB);
-        __builtin_amdgcn_sched_barrier(0);
-        o1 = o3;
-      }
-    }
+    if (chunk > 0) multiply_chunk<NT, RP, MT>(g, xs, wl, koff, a_base, i16, kq, acc);
     if (chunk == g.nchunks) break;
     if (chunk > 0) __syncthreads();   // the chunk before has been read
     for (int q0 = 0;;) {
@@ -494,7 +502,147 @@ __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 && !WIDE ? 3 : 2) void 
   }
   float bias_v[NT];
   lane_bias<NT>(a, ko0, i16, bias_v);
-  engine_epilogue<NT, RP, MT, true>(a, acc, bias_v, n, ko0, oy0, ox0, wave, i16, kq);
+  engine_epilogue<NT, RP, MT, DZ ? kNever : kAhead>(a, acc, bias_v, n, ko0, oy0, ox0, wave, i16, kq);
+}
+
+// The same for layers that bring workgroups enough: four elements in flight per thread and five (NT = RP = 1) or four
+// workgroups per CU instead of the three and two that the longer batches above leave, addresses of 64 bits, an
+// element's place worked out from the one before.  Where a launch fills the chip, or has a single chunk and so
+// nothing to fetch behind its products, the number of wavefronts hides the latency better than the number of loads.
+// (the bound also keeps the accumulators in vector registers: left to itself the compiler carried them through
+// accumulation registers and back at every step, 180 -> 222 us on 236 x 32 x 26 x 26, 8 filters 9x9)
+template <int NT, int RP>
+__global__ __launch_bounds__(kThreads, NT + RP == 2 ? 5 : (NT == 3 ? 3 : 4)) void conv_engine_lean_kernel(const EngineParams p) {
+  extern __shared__ float lds[];
+  const ConvEngineArgs &a = p.a;
+  const EngineGeom &g = p.g;
+  float *xs = lds;                                  // [CC][PS]
+  float *wl = xs + g.CC * g.PS;                     // [NT][KC][16]
+  int *koff = reinterpret_cast<int *>(wl + NT * g.KC * 16);  // [KC]
+  int2 *wtab = reinterpret_cast<int2 *>(koff + g.KC);        // [KC]: offset of tap kk inside a filter slice (-1: padding), channel
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i16 = lane & 15, kq = lane >> 4;
+  const int bid = blockIdx.x;
+  const int tx = bid % g.tiles_x;
+  const int ty = (bid / g.tiles_x) % g.tiles_y;
+  const int n = bid / (g.tiles_x * g.tiles_y);
+  const int ko0 = blockIdx.y * (NT * 16);
+  constexpr int TH = 8 * RP;
+  const int oy0 = ty * TH, ox0 = tx * kTileW;       // pre-pool output origin of the tile
+  const int RSf = a.R * a.S;
+
+  // tap offsets inside the halo tile: kk = (r*S + s)*CC + cl  ->  cl*PS + r*RS + s, and inside the
+  // filter tensor relative to the chunk's first channel (rotated and transposed filters: w_flip)
+  for (int kk = tid; kk < g.KC; kk += kThreads) {
+    const int cl = kk % g.CC, rs = kk / g.CC;
+    const int r = rs / a.S, s = rs - r * a.S;
+    koff[kk] = rs < RSf ? cl * g.PS + r * g.RS + s : 0;
+    const int wo = a.w_flip ? cl * a.Kout * RSf + (a.R - 1 - r) * a.S + (a.S - 1 - s) : cl * RSf + r * a.S + s;
+    wtab[kk] = make_int2(rs < RSf ? wo : -1, cl);
+  }
+  // Only the first 2^jw_log columns of a filter slice can be non-zero (Kout is small); the others
+  // are cleared once here and never written again.
+  const int jw = 1 << g.jw_log;
+  if (jw < 16)
+    for (int e = tid; e < NT * g.KC * 16; e += kThreads) wl[e] = 0.0f;
+
+  floatx4 acc[RP][4][NT];
+#pragma unroll
+  for (int rp = 0; rp < RP; ++rp)
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[rp][mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  // lane's pixel inside an M-tile: window gq, position (wa, wb)
+  const int gq = i16 >> 2, wa = (i16 >> 1) & 1, wb = i16 & 1;
+  const int a_base = (wave * 2 * RP + wa) * g.RS + 8 * gq + wb;
+
+  for (int chunk = 0; chunk < g.nchunks; ++chunk) {
+    const int c0 = chunk * g.CC;
+    __syncthreads();  // previous chunk's readers are done
+    // Both staging loops work in batches of kStage elements per thread: all addresses first, then all
+    // loads, unconditionally and from clamped addresses (element 0 stands in for anything that is
+    // padding or out of range), then the selects and the LDS stores.  A load behind a per-lane
+    // branch would be waited for before the next one is issued.
+    constexpr int kStage = 4;
+    // ---- filter slice: wl[nt][kk][j] = wgt(ko0 + 16nt + j, c0 + cl, r, s) for the columns j < jw
+    const int f_total = NT * g.KC * jw;
+    const int w_base = a.w_flip ? c0 * a.Kout * RSf : c0 * RSf;   // + ko * RSf (flipped) or ko * Cin * RSf
+    const int w_ko = a.w_flip ? RSf : a.Cin * RSf;
+    for (int e0 = tid; e0 < f_total; e0 += kStage * kThreads) {
+      float v[kStage];
+      bool ok[kStage];
+      int dst[kStage];
+#pragma unroll
+      for (int u = 0; u < kStage; ++u) {
+        const int e = min(e0 + u * kThreads, f_total - 1);
+        const int j = e & (jw - 1);
+        int kk = e >> g.jw_log, nt = 0;
+        while (kk >= g.KC) { kk -= g.KC; ++nt; }   // at most NT - 1 rounds
+        const int2 t = wtab[kk];
+        const int ko = ko0 + nt * 16 + j;
+        ok[u] = t.x >= 0 && ko < a.Kout && c0 + t.y < a.Cin;
+        dst[u] = (nt * g.KC + kk) * 16 + j;
+        v[u] = a.w[ok[u] ? w_base + ko * w_ko + t.x : 0];
+      }
+#pragma unroll
+      for (int u = 0; u < kStage; ++u)
+        if (e0 + u * kThreads < f_total) wl[dst[u]] = ok[u] ? v[u] : 0.0f;
+    }
+    // ---- halo tile of the source, zero outside the image (padding) and past Cin
+    {
+      const int total = g.CC * g.rows * g.cols;
+      int col = tid % g.cols;
+      int q = tid / g.cols;
+      int row = q % g.rows, cl = q / g.rows;
+      const int dcol = kThreads % g.cols, dq = kThreads / g.cols;
+      const int Hp = a.Hin >> 1, Wp = a.Win >> 1;   // pooled dz sources only
+      const bool pooled = a.src_dz && a.src_pool == 2;
+      const bool need_y = a.src_dz && reads_output(a.src_act);
+      for (int e0 = tid; e0 < total; e0 += kStage * kThreads) {
+        float gv[kStage], yv[kStage];
+        unsigned char fv[kStage];
+        bool ok[kStage];
+        int dst[kStage], want[kStage];
+#pragma unroll
+        for (int u = 0; u < kStage; ++u) {
+          const int gi = oy0 - a.pad_h + row, gj = ox0 - a.pad_w + col, ci = c0 + cl;
+          ok[u] = e0 + u * kThreads < total && ci < a.Cin && gi >= 0 && gi < a.Hin && gj >= 0 && gj < a.Win;
+          dst[u] = cl * g.PS + row * g.RS + col;
+          want[u] = ((gi & 1) << 1) | (gj & 1);
+          int o = pooled ? ((n * a.Cin + ci) * Hp + (gi >> 1)) * Wp + (gj >> 1) : ((n * a.Cin + ci) * a.Hin + gi) * a.Win + gj;
+          o = ok[u] ? o : 0;
+          gv[u] = a.src[o];
+          yv[u] = need_y ? a.src_y[o] : 0.0f;
+          fv[u] = pooled ? a.src_idx[o] : (unsigned char)0;
+          col += dcol;
+          row += dq;
+          if (col >= g.cols) { col -= g.cols; ++row; }
+          while (row >= g.rows) { row -= g.rows; ++cl; }
+        }
+#pragma unroll
+        for (int u = 0; u < kStage; ++u) {
+          if (e0 + u * kThreads >= total) continue;
+          float v = gv[u];
+          if (a.src_dz) {
+            // dz at a pre-pool position: dy routed to the recorded arg-max, times act'(y)
+            if (pooled && (fv[u] & kIdxPosMask) != (unsigned char)want[u]) v = 0.0f;
+            if (a.src_act == ACT_RELU_FLAGGED) v = (fv[u] & kIdxInactive) ? 0.0f : v;
+            else if (a.src_act == ACT_SIGMOID) v *= yv[u] * (1.0f - yv[u]);
+            else if (a.src_act == ACT_RELU) v = yv[u] > 0.0f ? v : 0.0f;
+          }
+          xs[dst[u]] = ok[u] ? v : 0.0f;
+        }
+      }
+    }
+    __syncthreads();
+    multiply_chunk<NT, RP, 4>(g, xs, wl, koff, a_base, i16, kq, acc);
+  }
+  float bias_v[NT];
+  lane_bias<NT>(a, ko0, i16, bias_v);
+  engine_epilogue<NT, RP>(a, acc, bias_v, n, ko0, oy0, ox0, wave, i16, kq);
 }
 
 inline int round_up_mod(int v, int m, int r) {  // smallest value >= v congruent to r mod m
@@ -503,7 +651,14 @@ inline int round_up_mod(int v, int m, int r) {  // smallest value >= v congruent
   return x;
 }
 
-bool plan_engine(const ConvEngineArgs &a, int NT, int RP, int MT, EngineGeom *g, size_t *lds_bytes) {
+// Pairs of a position of the halo tile and a channel that a thread stages at most, in 1 << split_log groups of threads.
+inline int staging_rounds(const EngineGeom &g, int split_log) {
+  const int span = kThreads >> split_log, groups = 1 << split_log;
+  return (g.rows * g.cols + span - 1) / span * ((g.CC + groups - 1) / groups);
+}
+
+// `tables`: ints of LDS per padded tap (the lean kernel keeps three).
+bool plan_engine(const ConvEngineArgs &a, int NT, int RP, int MT, int tables, EngineGeom *g, size_t *lds_bytes) {
   const int TH = 8 * RP, TW = 8 * MT;
   g->rows = TH + a.R - 1;
   g->cols = TW + a.S - 1;
@@ -514,7 +669,7 @@ bool plan_engine(const ConvEngineArgs &a, int NT, int RP, int MT, EngineGeom *g,
     g->CC = cc;
     g->KC = (cc * a.R * a.S + 3) / 4 * 4;
     g->KS = g->KC / 4;
-    *lds_bytes = sizeof(float) * ((size_t)cc * g->PS + (size_t)NT * g->KC * 16 + (size_t)g->KC);
+    *lds_bytes = sizeof(float) * ((size_t)cc * g->PS + (size_t)NT * g->KC * 16 + tables * (size_t)g->KC);
   };
   for (set(CC); *lds_bytes > 64 * 1024 && CC > 1; set(CC)) CC = (CC + 1) / 2;
   if (*lds_bytes > 64 * 1024) return false;
@@ -526,33 +681,71 @@ bool plan_engine(const ConvEngineArgs &a, int NT, int RP, int MT, EngineGeom *g,
   g->kgroups = (a.Kout + NT * 16 - 1) / (NT * 16);
   g->cw_log = 0;
   while ((1 << g->cw_log) < g->CC) ++g->cw_log;
+  g->jw_log = 4;
+  if (NT == 1 && a.Kout < 16)
+    while (g->jw_log > 0 && (1 << (g->jw_log - 1)) >= a.Kout) --g->jw_log;
+  // 3x3 filters: the 340 positions of a tile are 1.3 rounds of 256 threads but 5.3 of 64
+  g->split_log = 0;
+  for (int l = 1; l <= 2; ++l)
+    if (staging_rounds(*g, l) < staging_rounds(*g, g->split_log)) g->split_log = l;
   return true;
 }
 
-template <int NT, int RP, int MT, bool WIDE = false>
+constexpr long kMaxGrid = (1L << 24) - 1;   // workgroups of 256 threads that a launch can have along x
+
+template <int NT, int RP, int MT>
 hipError_t launch_t(const ConvEngineArgs &a, hipStream_t stream) {
   EngineParams p;
   p.a = a;
   size_t lds = 0;
-  if (!plan_engine(a, NT, RP, MT, &p.g, &lds)) return hipErrorInvalidValue;
+  if (!plan_engine(a, NT, RP, MT, 1, &p.g, &lds)) return hipErrorInvalidValue;
   const long blocks = (long)a.N * p.g.tiles_x * p.g.tiles_y;
-  if (blocks <= 0 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  if (blocks <= 0 || blocks > kMaxGrid) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks, (unsigned)p.g.kgroups, 1);
-  const bool shallow = (p.g.rows * p.g.cols + kThreads - 1) / kThreads * p.g.CC <= 8;
-  if (a.src_dz) hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, true, 8, WIDE>), grid, dim3(kThreads), lds, stream, p);
-  else if (shallow) hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, false, 8, WIDE>), grid, dim3(kThreads), lds, stream, p);
-  else hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, false, 12, WIDE>), grid, dim3(kThreads), lds, stream, p);
+  const bool shallow = staging_rounds(p.g, 0) <= 8;
+  if (a.src_dz) hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, true, 8>), grid, dim3(kThreads), lds, stream, p);
+  else if (shallow) hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, false, 8>), grid, dim3(kThreads), lds, stream, p);
+  else hipLaunchKernelGGL((conv_engine_kernel<NT, RP, MT, false, 12>), grid, dim3(kThreads), lds, stream, p);
   return hipGetLastError();
 }
 
-// Tiles of 16 rows where they give every compute unit two workgroups, else of 8; maps of at most 8 or 16
-// columns take tiles that narrow.
+template <int NT, int RP>
+hipError_t launch_lean(const ConvEngineArgs &a, hipStream_t stream) {
+  EngineParams p;
+  p.a = a;
+  size_t lds = 0;
+  if (!plan_engine(a, NT, RP, 4, 3, &p.g, &lds)) return hipErrorInvalidValue;
+  const long blocks = (long)a.N * p.g.tiles_x * p.g.tiles_y;
+  if (blocks <= 0 || blocks > kMaxGrid) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((conv_engine_lean_kernel<NT, RP>), dim3((unsigned)blocks, (unsigned)p.g.kgroups, 1), dim3(kThreads), lds, stream, p);
+  return hipGetLastError();
+}
+
+// Which kernel and tile takes a layer.  Tiles of 16 rows where they give every compute unit two workgroups (`small`: not),
+// else of 8; maps of at most 8 or 16 columns take tiles that narrow.  The pipelined kernel hides the latency of a
+// launch that does not fill the chip, and keeps 32-bit byte offsets inside a tile's rows of a plane and a workgroup's
+// filters.  The lean one takes what lies beyond those, launches of two workgroups per compute unit or more, and
+// gradients with nothing to pipeline: one chunk into more than 16 channels, or of at most four channels.  Over 4000
+// random layers the pipelined kernel alone was more than 5 % slower than the lean one on 247 forward and 473
+// backward-data passes (at worst 1.7 times: 233 x 3 x 25 x 112, 2 filters 1x1, backward-data 26 against 15.5 us); the choice
+// made here is on 48 and 63, and the sum of all times went from 127.7 + 157.9 to 126.6 + 152.4 ms.
 template <int NT>
 hipError_t launch_generic(const ConvEngineArgs &a, bool small, hipStream_t stream) {
-  if (a.Wout <= 8) return launch_t<NT, 1, 1>(a, stream);
-  if (a.Wout <= 16) return launch_t<NT, 1, 2>(a, stream);
-  if (small) return launch_t<NT, 1, 4>(a, stream);
-  return launch_t<NT, 2, 4>(a, stream);
+  const long tile_rows = (long)(16 + a.R - 1) * a.Win, filters = 48L * (a.Cin > a.Kout ? a.Cin : a.Kout) * a.R * a.S;
+  const bool far = tile_rows >= (1L << 29) || filters >= (1L << 29);
+  const long rows8 = (long)a.N * ((a.Hout + 7) / 8);
+  EngineGeom g;
+  size_t lds;
+  const bool short_dz = a.src_dz && plan_engine(a, NT, 1, 4, 1, &g, &lds) && g.nchunks == 1;
+  if (NT > 1 && short_dz && a.Cin <= 4) return launch_lean<NT, 1>(a, stream);
+  if (a.Wout <= 16 && !far && rows8 <= kMaxGrid) return a.Wout <= 8 ? launch_t<NT, 1, 1>(a, stream) : launch_t<NT, 1, 2>(a, stream);
+  if (!small) {
+    if constexpr (NT == 1) return launch_lean<1, 2>(a, stream);
+    else return far ? launch_lean<NT, 1>(a, stream) : launch_t<NT, 2, 4>(a, stream);
+  }
+  const long units = rows8 * ((a.Wout + kTileW - 1) / kTileW) * ((a.Kout + NT * 16 - 1) / (NT * 16));
+  if (far || units >= 2L * chip().cus || (short_dz && (NT > 1 || a.Cin <= 4))) return launch_lean<NT, 1>(a, stream);
+  return launch_t<NT, 1, 4>(a, stream);
 }
 
 
@@ -1000,7 +1193,7 @@ __global__ __launch_bounds__(WAVES * 64, conv3x3_occupancy(NT, WAVES, CC)) void 
       const int ty = (tile / g.tiles_x) % g.tiles_y;
       const int n = tile / (g.tiles_x * g.tiles_y);
       if constexpr (EPI == 1) engine_epilogue_as<NT, RP, ACT_RELU, 2>(a, acc, bias_v, n, ko0, ty * TH, tx * kTileW, wave, i16, kq);
-      else if constexpr (EPI == 2) engine_epilogue_as<NT, RP, ACT_IDENTITY, 1>(a, acc, bias_v, n, ko0, ty * TH, tx * kTileW, wave, i16, kq);
+      else if constexpr (EPI == 2) engine_epilogue_as<NT, RP, ACT_IDENTITY, 1, 4, kNever>(a, acc, bias_v, n, ko0, ty * TH, tx * kTileW, wave, i16, kq);
       else engine_epilogue<NT, RP>(a, acc, bias_v, n, ko0, ty * TH, tx * kTileW, wave, i16, kq);
     }
     q = qn;
@@ -1033,7 +1226,7 @@ Conv3x3Pick conv3x3c16_pick(const ConvEngineArgs &a) {
   if ((long)a.N * a.Cin * a.Hin * a.Win * 4 >= (1L << 31)) return none;
   if (a.src_dz) {
     // the dz instances store plainly: anything else on top of a backward-form pass takes the generic kernel
-    if (a.act != ACT_IDENTITY || a.pool != 1) return none;
+    if (a.act != ACT_IDENTITY || a.pool != 1 || a.sample) return none;
     if (reads_output(a.src_act) && !aligned16(a.src_y)) return none;
     if (a.src_pool == 2) {
       if (a.Win % 8 != 0 || (reinterpret_cast<uintptr_t>(a.src_idx) & 3u) != 0) return none;
@@ -1103,6 +1296,7 @@ hipError_t launch_3x3(const ConvEngineArgs &a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_conv_engine(const ConvEngineArgs &a, hipStream_t stream) {
+  if (a.src_dz && a.sample) return hipErrorInvalidValue;   // states are drawn by forward passes only
   // 16 output channels per N-tile.  The generic kernel uses the 8-row tile for shallow maps
   // (<= 8 pre-pool rows) and whenever 16-row tiles would leave CUs without a workgroup.
   // A launch that leaves compute units without a workgroup splits the output channels instead (four images of 40
@@ -1116,10 +1310,11 @@ hipError_t launch_conv_engine(const ConvEngineArgs &a, hipStream_t stream) {
   // very few output channels: the banded-filter kernel takes Kout * ceil((16 + S - 1) / 4) MFMA steps per
   // channel and filter row for 256 pixels where the channel columns of the engine take 4 * S (one to three
   // of whose 16 columns are real): 16 x 2 x 45 x 45 behind 20 maps, 3x3: both backward passes 38 -> 20 us; but three channels, 3x3,
-  // 64 x 64 maps: 32 -> 43.  Two or three channels of a layer the 3x3 instance takes stay with it until the filter
+  // 64 x 64 maps: 32 -> 43.  With fewer source channels than outputs most of its wavefronts idle (3 x 20 x 56 x 23 behind
+  // one map, 11x11: 12.8 us against 9.0).  Two or three channels of a layer the 3x3 instance takes stay with it until the filter
   // rows are long.
   const int few_steps = a.Kout * ((16 + a.S - 1 + 3) / 4);
-  if (a.Kout <= 3 && few_steps < 4 * a.S && conv_fewout_applies(a) && (few_steps * 3 < 8 * a.S || conv3x3c16_pick(a).NT == 0))
+  if (a.Kout <= 3 && a.Cin >= a.Kout && few_steps < 4 * a.S && conv_fewout_applies(a) && (few_steps * 3 < 8 * a.S || conv3x3c16_pick(a).NT == 0))
     return launch_conv_fewout(a, stream);
   if (conv_fwd_fewch_applies(a)) return launch_conv_fwd_fewch(a, stream);
   if (conv_wino_stream_applies(a) || conv_wino_stream_bwd_applies(a)) return launch_conv_wino_stream(a, stream);
@@ -1136,9 +1331,6 @@ hipError_t launch_conv_engine(const ConvEngineArgs &a, hipStream_t stream) {
     if (pick.NT == 2 && pick.CC == 4) return launch_3x3<2, 4, 4>(a, stream);
     if (pick.NT == 2 && pick.CC == 16) return launch_3x3<2, 8, 16>(a, stream);
   }
-  // the halo tile's rows of a plane and a workgroup's filters within 32-bit byte offsets
-  const long tile_rows = (long)(16 + a.R - 1) * a.Win, filters = 48L * (a.Cin > a.Kout ? a.Cin : a.Kout) * a.R * a.S;
-  if (tile_rows >= (1L << 29) || filters >= (1L << 29)) return launch_t<1, 1, 1, true>(a, stream);
   if (nt == 1) return launch_generic<1>(a, small, stream);
   if (nt == 2) return launch_generic<2>(a, small, stream);
   return launch_generic<3>(a, small, stream);

@@ -1,8 +1,11 @@
-"""What the library settles on the host before it launches anything: workspace sizes (no GPU needed)."""
+"""What the library settles on the host before it launches anything: workspace sizes, and which kernel takes a call
+(launches are noted instead of run: no GPU needed)."""
 import pytest
 
 from paper_1804_04512_amd import binding as B
 from paper_1804_04512_amd.workloads import ConvSpec
+
+from launch_record import record
 
 
 @pytest.mark.parametrize("shape", [(256, 1, 64, 64, 8, 3, 3, 1), (64, 1, 28, 28, 40, 9, 9, 0), (16, 3, 32, 32, 16, 5, 5, 2),
@@ -12,3 +15,28 @@ def test_crbm_workspace_ignores_pooling_and_activation(shape):
     are (a size taken from the pooled layer's plan was up to 1 MB short of what the step writes)."""
     sizes = {B.dll_crbm_workspace_bytes(ConvSpec(*shape, act, pool)) for act in ("identity", "relu") for pool in (1, 2)}
     assert len(sizes) == 1 and sizes.pop() > 0
+
+
+# pass, layer, the lean kernel's instance <16-filter groups, row pairs>
+LEAN = [
+    ("fwd", (130, 3, 40, 40, 8, 3, 3, 0, "relu", 2), (1, 2)), ("bwd", (130, 9, 33, 47, 18, 2, 3, 1, "sigmoid", 1), (1, 2)),
+    ("fwd", (260, 2, 8, 40, 5, 3, 3, 1, "sigmoid", 1), (1, 1)), ("fwd", (171, 20, 10, 69, 7, 5, 4, 0, "identity", 1), (1, 1)),
+    ("fwd", (260, 17, 8, 34, 18, 3, 2, 0, "relu", 1), (2, 1)), ("bwd", (260, 18, 7, 40, 17, 3, 3, 0, "relu", 1), (2, 1)),
+    ("fwd", (258, 3, 8, 40, 33, 3, 3, 1, "relu", 2), (3, 1)), ("bwd", (130, 40, 14, 20, 3, 3, 3, 1, "relu", 2), (3, 1)),
+    ("bwd", (3, 5, 20, 36, 4, 5, 5, 2, "sigmoid", 2), (1, 1)),
+]
+
+
+def test_lean_layers_reach_the_lean_kernel(tmp_path):
+    got = record([[what, *c] for what, c, _ in LEAN], tmp_path)
+    for (what, c, (nt, rp)), (status, launches) in zip(LEAN, got):
+        assert status == 0 and f"conv_engine_lean_kernelILi{nt}ELi{rp}E" in launches[0][0], (what, c, launches)
+
+
+def test_layers_past_the_pipelined_kernel(tmp_path):
+    """Rows of a tile or filters of a workgroup 2 GiB apart, and maps of few columns whose narrow tiles would be more
+    than a launch can have: neither is refused."""
+    calls = [["fwd", 1, 1, 3, 30_000_000, 4, 3, 3, 0, "identity", 1], ["fwd", 1, 3_000_000, 4, 20, 5, 2, 2, 0, "identity", 1],
+             ["fwd", 9_000_000, 1, 12, 8, 1, 1, 1, 0, "identity", 1], ["bwd", 9_000_000, 1, 10, 9, 1, 1, 1, 0, "relu", 1]]
+    for call, (status, launches) in zip(calls, record(calls, tmp_path)):
+        assert status == 0 and "conv_engine_lean_kernel" in launches[0][0], (call, launches)
