@@ -281,7 +281,7 @@ struct StepTail {
   // optional: the CRBM's visible sums per channel and slice (launch_visible_final adds them up)
   struct Visible { const float *v0 = nullptr, *v1 = nullptr; int N = 0, C = 0, HW = 0; float *scratch = nullptr; } vis;
 };
-// Whether a product can be a job of the closing launch.
+// Whether a product can be a job of the closing launch (operands below 2 GiB, as gemm_is_small asks).
 bool step_tail_takes(const GemmArgs &g);
 hipError_t launch_step_tail(const StepTail &t, hipStream_t stream);
 

@@ -43,8 +43,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_small_kernel(const SmallParam
 // 128 x 2048 x 2000 products of a large-image step 370 against 379 in all).  Up to 2^30 where an extent is no
 // multiple of four, which the persistent kernel's 16-byte loads need (500 x 1600 x 1001 RBM step 267
 // against 192).
+// And only while every operand and result lies below 2 GiB, where the kernel's buffers end (one row through a
+// weight matrix of 2^29 floats is not many multiply-adds); 32 elements less, so that its tiles are fewer than 2^24.
 bool gemm_is_small(int M, int N, int Kdim) {
-  const long macs = (long)M * N * Kdim;
+  const long macs = (long)M * N * Kdim, limit = (1L << 29) - 32;
+  if ((long)M * N > limit || (long)M * Kdim > limit || (long)N * Kdim > limit) return false;
   const int least = M < N ? (M < Kdim ? M : Kdim) : (N < Kdim ? N : Kdim);
   if (((M | N | Kdim) & 3) != 0) return macs <= (1L << 30);
   if (least >= 256) return macs <= (1L << 29);
@@ -65,7 +68,7 @@ hipError_t launch_gemm_small(const GemmArgs &a, hipStream_t stream) {
                       a.C_ref))
     return hipErrorInvalidValue;
   SmallParams p;
-  // A across k: the weight-gradient form, a job of the closing launch; operands of 2 GiB never are small products
+  // A across k: the weight-gradient form, a job of the closing launch
   if (a.a_k != 1 || a.A2 || a.B2 || !small_gemm::make_params(a, &p)) return hipErrorInvalidValue;
   const bool b_kc = a.b_k == 1;
   const bool fine = small_gemm::tile_quarters(a.M, a.N) == 1;

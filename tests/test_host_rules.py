@@ -40,3 +40,16 @@ def test_layers_past_the_pipelined_kernel(tmp_path):
              ["fwd", 9_000_000, 1, 12, 8, 1, 1, 1, 0, "identity", 1], ["bwd", 9_000_000, 1, 10, 9, 1, 1, 1, 0, "relu", 1]]
     for call, (status, launches) in zip(calls, record(calls, tmp_path)):
         assert status == 0 and "conv_engine_lean_kernel" in launches[0][0], (call, launches)
+
+
+def test_products_with_an_operand_of_2_gib(tmp_path):
+    """The header allows tensors of fewer than 2^31 elements; the small-product kernel's buffers end at 2 GiB.  Products
+    beyond are the persistent kernel's, however few multiply-adds they have (they were refused)."""
+    calls = [["infer", [], [[20000, 32768], [32768, 10]], 10, 1], ["train", [], [[20000, 32768], [32768, 10]], 10, 1],
+             ["rbm", 1, 32768, 20000], ["rbm", 1, 20000, 32768], ["infer", [], [[2000, 1]], 1, 300000],
+             ["train", [], [[2001, 1]], 1, 300000], ["rbm", 2, 16384, 32768], ["train", [], [[3, 5], [5, 40000000], [40000000, 3]], 3, 5],
+             ["infer", [], [[16384, 32768], [32768, 3]], 3, 1], ["infer", [], [[16384, 32752], [32752, 3]], 3, 1]]
+    got = record(calls, tmp_path)
+    for call, (status, launches) in zip(calls, got):
+        assert status == 0 and launches, call
+    assert "gemm_small" not in got[-2][1][0][0] and "gemm_small" in got[-1][1][0][0]   # either side of the line
