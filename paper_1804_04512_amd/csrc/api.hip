@@ -455,7 +455,7 @@ dll_status dll_crbm_cd1_step(const dll_conv_desc *d, const float *v0, float *W, 
 namespace {
 // split-K partial area the three batch-by-units products of the RBM step need at most
 size_t rbm_partial_floats(int B, int nv, int nh) {
-  const size_t a = (size_t)gemm_pick_split_k(B, nh, nv) * B * nh, b = (size_t)gemm_pick_split_k(B, nv, nh) * B * nv;
+  const size_t a = (size_t)gemm_pick_split_k(GemmForm::kForward, B, nh, nv) * B * nh, b = (size_t)gemm_pick_split_k(GemmForm::kDataGrad, B, nv, nh) * B * nv;
   return a > b ? a : b;
 }
 bool rbm_sizes_ok(int B, int nv, int nh) {
@@ -506,7 +506,8 @@ dll_status dll_rbm_cd1_step(int batch, int n_vis, int n_hid, int visible, const 
   // the epilogue that forms their probabilities, and the statistics - dW as the difference of two
   // products, both column sums, the reconstruction error from the squares summed by the reconstruction's
   // epilogue - are jobs of one closing launch.  100 x 784 x 500: ten launches and 44.7 us before, 29.0 now.
-  const bool small = gemm_is_small(B, nh, nv);
+  // (The hidden products follow the other two: see small_form.)
+  const bool small = gemm_is_small(GemmForm::kDataGrad, B, nv, nh) && gemm_is_small(GemmForm::kWeightGrad, nh, nv, B);
   float *v1p = small && v1 ? v1 : vstack + nV;   // else the reconstruction is the lower half of the stack
   float *sq_partial = vstack;                    // small: gemm_small_tiles(B, nv) <= B * nv floats
 
@@ -518,7 +519,8 @@ dll_status dll_rbm_cd1_step(int batch, int n_vis, int n_hid, int visible, const 
     g.B = W; g.b_k = 1; g.b_n = nv;
     g.bias = b_hid; g.act = ACT_SIGMOID;
     g.Cout = out; g.c_m = nh; g.c_n = 1;
-    g.split_k = gemm_pick_split_k(g.M, g.N, g.Kdim);
+    g.split_k = small ? 1 : gemm_pick_split_k(GemmForm::kForward, g.M, g.N, g.Kdim);
+    g.small_form = small;
     g.partial = partial;
     if (states) { g.uniform = uniform; g.sample = h0s; }
     return dev(launch_gemm(g, s));
@@ -540,7 +542,7 @@ dll_status dll_rbm_cd1_step(int batch, int n_vis, int n_hid, int visible, const 
     g.B = W; g.b_k = nv; g.b_n = 1;
     g.bias = c_vis; g.act = visible == DLL_VISIBLE_BINARY ? ACT_SIGMOID : ACT_IDENTITY;
     g.Cout = v1p; g.c_m = nv; g.c_n = 1;
-    g.split_k = gemm_pick_split_k(g.M, g.N, g.Kdim);
+    g.split_k = gemm_pick_split_k(GemmForm::kDataGrad, g.M, g.N, g.Kdim);
     g.partial = partial;
     if (small && recon_mse) { g.sq_ref = v0; g.sq_partial = sq_partial; }
     if ((st = dev(launch_gemm(g, s))) != DLL_OK) return st;
@@ -627,9 +629,9 @@ dll_status check_net(const dll_net_desc *net, NetLayout *lay) {
     if (gi > gmax) gmax = gi;
     if (go > gmax) gmax = go;
     size_t p;
-    p = (size_t)gemm_pick_split_k(B, dd->out, dd->in) * B * dd->out;      // forward
+    p = (size_t)gemm_pick_split_k(GemmForm::kForward, B, dd->out, dd->in) * B * dd->out;      // forward
     if (p > partial) partial = p;
-    p = (size_t)gemm_pick_split_k(B, dd->in, dd->out) * B * dd->in;       // backward data
+    p = (size_t)gemm_pick_split_k(GemmForm::kDataGrad, B, dd->in, dd->out) * B * dd->in;       // backward data
     if (p > partial) partial = p;
     feat = dd->out;
   }
@@ -739,7 +741,7 @@ dll_status run_cnn_step(const dll_net_desc *net, float *const *params, float *co
     g.bias = params[2 * (L + q) + 1];
     g.act = (q == D - 1) ? ACT_IDENTITY : dd->act;
     g.Cout = nb.act[L + q + 1]; g.c_m = dd->out; g.c_n = 1;
-    g.split_k = gemm_pick_split_k(g.M, g.N, g.Kdim);
+    g.split_k = gemm_pick_split_k(GemmForm::kForward, g.M, g.N, g.Kdim);
     g.partial = nb.partial;
     // the logits' split-K partials are added by the loss kernel, which reads them anyway
     if (q == D - 1 && g.split_k > 1) { g.defer_reduce = true; logits_split = g.split_k; }
@@ -781,7 +783,7 @@ dll_status run_cnn_step(const dll_net_desc *net, float *const *params, float *co
     g.B = Wq; g.b_k = dd->in; g.b_n = 1;
     g.Cout = gnext; g.c_m = dd->in; g.c_n = 1;
     if (q > 0 && net->dense[q - 1].act != DLL_ACT_IDENTITY) { g.C_ref = nb.act[L + q]; g.c_ref_act = net->dense[q - 1].act; }
-    g.split_k = gemm_pick_split_k(g.M, g.N, g.Kdim);
+    g.split_k = gemm_pick_split_k(GemmForm::kDataGrad, g.M, g.N, g.Kdim);
     g.partial = nb.partial;
     if (g.split_k > 1 && gemm_prefers_small(g)) { g.split_k = 1; g.small_form = true; }
     // the gradient with respect to the network input has no consumer
@@ -951,7 +953,7 @@ dll_status dll_cnn_forward(const dll_net_desc *net, const float *const *params, 
     g.bias = params[2 * (L + q) + 1];
     g.act = (q == D - 1) ? ACT_IDENTITY : dd->act;
     g.Cout = out; g.c_m = dd->out; g.c_n = 1;
-    g.split_k = gemm_pick_split_k(g.M, g.N, g.Kdim);
+    g.split_k = gemm_pick_split_k(GemmForm::kForward, g.M, g.N, g.Kdim);
     g.partial = partial;
     if (q == D - 1 && prob) {
       // the softmax rides in the epilogue of a small product of few classes, or adds the split-K partials itself

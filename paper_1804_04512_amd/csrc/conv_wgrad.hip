@@ -903,7 +903,7 @@ hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, const WgradPlan &plan, 
 }
 
 bool step_tail_takes(const GemmArgs &g) {
-  return g.split_k <= 1 && gemm_is_small(g.M, g.N, g.Kdim) && g.a_m == 1 && g.b_n == 1 && g.c_n == 1 && !g.bias && !g.C_ref &&
+  return g.split_k <= 1 && gemm_is_small(GemmForm::kWeightGrad, g.M, g.N, g.Kdim) && g.a_m == 1 && g.b_n == 1 && g.c_n == 1 && !g.bias && !g.C_ref &&
          g.act == ACT_IDENTITY && !g.sm_labels && !g.uniform && !g.sq_ref && (g.A2 == nullptr) == (g.B2 == nullptr);
 }
 

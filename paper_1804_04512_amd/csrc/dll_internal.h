@@ -197,7 +197,7 @@ struct GemmArgs {
   // then the bias) itself.  Only for an identity epilogue without update.
   bool defer_reduce = false;
   // split_k <= 1 only: take the small-product kernel although the product is larger than
-  // gemm_is_small() allows (see gemm_prefers_small)
+  // gemm_is_small() allows (see gemm_prefers_small; the RBM's hidden products where the others are small)
   bool small_form = false;
   // Softmax + cross-entropy in the epilogue (only where gemm_fuses_softmax() says so: every row of
   // logits lies inside one 16-column tile): Cout receives the logits, sm_dz (strides of Cout)
@@ -214,14 +214,20 @@ struct GemmArgs {
   const float *A2 = nullptr, *B2 = nullptr;
   float alpha = 1.0f;
 };
-int gemm_pick_split_k(int M, int N, int Kdim);
+// The three forms of a dense product, by the axis along which its operands' rows are contiguous.
+enum class GemmForm {
+  kForward,      // A along k, B along k: activations and weights
+  kDataGrad,     // A along k, B along n: gradients and weights
+  kWeightGrad,   // A along m, B along n: gradients and activations
+};
+int gemm_pick_split_k(GemmForm form, int M, int N, int Kdim);
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream);
 // Two products that do not depend on each other, in one launch where their forms allow it.
 hipError_t launch_gemm_pair(const GemmArgs &a, const GemmArgs &b, hipStream_t stream);
 // Small products (the dense layers of the MNIST/CIFAR-sized networks) take a kernel built for a
 // short latency chain instead: 32 x 32 tiles, the k range split between the wavefronts of a
 // workgroup, no split-K partials (gemm_pick_split_k returns 1 for them).  launch_gemm routes there.
-bool gemm_is_small(int M, int N, int Kdim);
+bool gemm_is_small(GemmForm form, int M, int N, int Kdim);
 // Data-gradient products (A contiguous along k, B along n) of up to 2^28 multiply-adds are still
 // faster there than as a split-K product with its reduction launch behind it (measured on the
 // 128 x 2048 x 1000 product of the 1000-class layer: 15.4 against 21 us); the forward and

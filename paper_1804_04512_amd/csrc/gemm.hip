@@ -849,8 +849,8 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(const float *src, float 
 
 }  // namespace
 
-int gemm_pick_split_k(int M, int N, int Kdim) {
-  if (gemm_is_small(M, N, Kdim)) return 1;   // the small-product kernel splits k inside the workgroup
+int gemm_pick_split_k(GemmForm form, int M, int N, int Kdim) {
+  if (gemm_is_small(form, M, N, Kdim)) return 1;   // the small-product kernel splits k inside the workgroup
   const long tiles = (long)((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   const int ksteps = (Kdim + BK - 1) / BK;
   int split = 1;
@@ -899,7 +899,7 @@ GemmPlan plan_gemm(const GemmArgs &a) {
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream) {
-  if (a.split_k <= 1 && a.a_k == 1 && (gemm_is_small(a.M, a.N, a.Kdim) || a.small_form)) return launch_gemm_small(a, stream);
+  if (a.split_k <= 1 && a.a_k == 1 && (a.small_form || gemm_is_small(a.b_k == 1 ? GemmForm::kForward : GemmForm::kDataGrad, a.M, a.N, a.Kdim))) return launch_gemm_small(a, stream);
   if (a.sm_labels) return hipErrorInvalidValue;   // the fused loss exists in the small-product kernel only
   const GemmPlan g = plan_gemm(a);
   const GemmParams &p = g.p;
@@ -942,7 +942,7 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream) {
 // persistent kernel's fused-update form with the same operand forms, the units of the second are
 // appended to the first's; else they are launched one after the other.
 hipError_t launch_gemm_pair(const GemmArgs &a, const GemmArgs &b, hipStream_t stream) {
-  const bool a_small = a.split_k <= 1 && gemm_is_small(a.M, a.N, a.Kdim), b_small = b.split_k <= 1 && gemm_is_small(b.M, b.N, b.Kdim);
+  const bool a_small = a.split_k <= 1 && gemm_is_small(GemmForm::kWeightGrad, a.M, a.N, a.Kdim), b_small = b.split_k <= 1 && gemm_is_small(GemmForm::kWeightGrad, b.M, b.N, b.Kdim);
   if (!a_small && !b_small && !a.sm_labels && !b.sm_labels && a.split_k <= 1 && b.split_k <= 1) {
     const GemmPlan ga = plan_gemm(a), gb = plan_gemm(b);
     if (ga.fast && gb.fast && ga.mode == 1 && gb.mode == 1 && ga.a_kc == gb.a_kc && ga.b_kc == gb.b_kc) {

@@ -40,27 +40,32 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_small_kernel(const SmallParam
 // them there, 27 here).  Up to 2^28 where the shortest extent leaves the persistent kernel's tiles half
 // empty (large-image step at batch 16: 274 against 259 us).  Up to 2^29 where all three are at least 256, i.e.
 // where several rows of its tiles re-read operands (512 x 1000 x 1000 RBM step 184 against 117; but with the
-// 128 x 2048 x 2000 products of a large-image step 370 against 379 in all).  Up to 2^30 where an extent is no
-// multiple of four, which the persistent kernel's 16-byte loads need (500 x 1600 x 1001 RBM step 267
-// against 192).
+// 128 x 2048 x 2000 products of a large-image step 370 against 379 in all).  Up to 2^30 where rows of the operands
+// or the result are no multiples of four, which the persistent kernel's 16-byte accesses need (500 x 1600 x 1001 RBM step 267
+// against 192).  Where only the batch is none and the product is a gradient, as far from 128 on (RBM steps of
+// 903 x 2148 x 136 242 against 102, 867 x 1036 x 680 265 against 132) and up to 2^29 below (127 x 3012 x 2392 184
+// against 240); a forward product does not mind its batch (255 x 1912 x 1696: 47 there against 64 here).
 // And only while every operand and result lies below 2 GiB, where the kernel's buffers end (one row through a
 // weight matrix of 2^29 floats is not many multiply-adds); 32 elements less, so that its tiles are fewer than 2^24.
-bool gemm_is_small(int M, int N, int Kdim) {
+bool gemm_is_small(GemmForm form, int M, int N, int Kdim) {
   const long macs = (long)M * N * Kdim, limit = (1L << 29) - 32;
   if ((long)M * N > limit || (long)M * Kdim > limit || (long)N * Kdim > limit) return false;
+  const int rows = (form == GemmForm::kWeightGrad ? M : Kdim) | N;
+  if ((rows & 3) != 0) return macs <= (1L << 30);
+  const int batch = form == GemmForm::kDataGrad ? M : (form == GemmForm::kWeightGrad ? Kdim : 0);
   const int least = M < N ? (M < Kdim ? M : Kdim) : (N < Kdim ? N : Kdim);
-  if (((M | N | Kdim) & 3) != 0) return macs <= (1L << 30);
+  if ((batch & 3) != 0) return macs <= (least >= 128 ? 1L << 30 : 1L << 29);
   if (least >= 256) return macs <= (1L << 29);
   return macs <= (least <= 64 ? 1L << 28 : 3L << 26);
 }
 
 bool gemm_prefers_small(const GemmArgs &a) {
-  if (gemm_is_small(a.M, a.N, a.Kdim)) return true;
+  if (gemm_is_small(a.b_k == 1 ? GemmForm::kForward : GemmForm::kDataGrad, a.M, a.N, a.Kdim)) return true;
   return a.a_k == 1 && a.b_n == 1 && !a.update && !a.sm_labels && (long)a.M * a.N * a.Kdim <= (1L << 28);
 }
 
 // Tiles of 16 x 16 (the launcher's choice below for this size) hold whole rows of up to 16 logits.
-bool gemm_fuses_softmax(int M, int N, int Kdim) { return gemm_is_small(M, N, Kdim) && N <= 16 && (M + 31) / 32 <= 512; }
+bool gemm_fuses_softmax(int M, int N, int Kdim) { return gemm_is_small(GemmForm::kForward, M, N, Kdim) && N <= 16 && (M + 31) / 32 <= 512; }
 
 hipError_t launch_gemm_small(const GemmArgs &a, hipStream_t stream) {
   if (a.sm_prob && (a.sm_labels || !gemm_fuses_softmax(a.M, a.N, a.Kdim) || a.act != ACT_IDENTITY || a.update || a.C_ref)) return hipErrorInvalidValue;

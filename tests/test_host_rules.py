@@ -48,8 +48,18 @@ def test_products_with_an_operand_of_2_gib(tmp_path):
     calls = [["infer", [], [[20000, 32768], [32768, 10]], 10, 1], ["train", [], [[20000, 32768], [32768, 10]], 10, 1],
              ["rbm", 1, 32768, 20000], ["rbm", 1, 20000, 32768], ["infer", [], [[2000, 1]], 1, 300000],
              ["train", [], [[2001, 1]], 1, 300000], ["rbm", 2, 16384, 32768], ["train", [], [[3, 5], [5, 40000000], [40000000, 3]], 3, 5],
-             ["infer", [], [[16384, 32768], [32768, 3]], 3, 1], ["infer", [], [[16384, 32752], [32752, 3]], 3, 1]]
+             ["infer", [], [[16384, 32769], [32769, 3]], 3, 1], ["infer", [], [[16384, 32751], [32751, 3]], 3, 1]]
     got = record(calls, tmp_path)
     for call, (status, launches) in zip(calls, got):
         assert status == 0 and launches, call
     assert "gemm_small" not in got[-2][1][0][0] and "gemm_small" in got[-1][1][0][0]   # either side of the line
+
+
+def test_forward_products_do_not_mind_an_odd_batch(tmp_path):
+    """What a forward product takes is settled by its rows' lengths: the batch is no row (odd batches of large layers ran
+    on the small-product kernel, up to a third slower).  Rows that are no multiples of four take it up to 2^30 multiply-adds."""
+    calls = [["infer", [], [[1696, 1912], [1912, 8]], 8, b] for b in (254, 255, 256)]
+    calls += [["infer", [], [[1696, 1911], [1911, 8]], 8, 256], ["rbm", 127, 3012, 2392], ["rbm", 903, 2148, 136], ["rbm", 500, 1600, 1001]]
+    first = [launches[0][0] for _, launches in record(calls, tmp_path)]
+    assert all("gemm_fast" in f for f in first[:3]) and "gemm_small" in first[3]
+    assert "gemm_fast" in first[4] and "gemm_small" in first[5] and "gemm_small" in first[6]
