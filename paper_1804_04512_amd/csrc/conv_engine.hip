@@ -1303,27 +1303,29 @@ hipError_t launch_conv_engine(const ConvEngineArgs &a, hipStream_t stream) {
   // channels, 61 x 61, 33 filters 5x5: the layer's passes 228 -> 134 us; but splitting 396 tiles to give every
   // unit two, 33 x 40 x 45 x 51: 61 -> 131).
   const long tiles8 = (long)a.N * ((a.Wout + kTileW - 1) / kTileW) * ((a.Hout + 7) / 8);
-  int nt = a.Kout <= 16 ? 1 : (a.Kout <= 32 ? 2 : 3);
+  // 49 to 64 filters are two groups of 32 rather than of 48 (88 x 64 x 10 x 16, 64 filters 3x3: 67 -> 53 us).
+  int nt = a.Kout <= 16 ? 1 : (a.Kout <= 32 || (a.Kout > 48 && a.Kout <= 64) ? 2 : 3);
   while (nt > 1 && tiles8 * ((a.Kout + nt * 16 - 1) / (nt * 16)) < chip().cus) --nt;
   const long tiles16 = (long)a.N * ((a.Wout + kTileW - 1) / kTileW) * ((a.Hout + 15) / 16) * ((a.Kout + nt * 16 - 1) / (nt * 16));
   const bool small = a.Hout <= 8 || tiles16 < 512;
+  // The 3x3 instance's tiles are 32 x 16: a map of at most 16 columns fills half of one, and few of them leave most of the
+  // chip idle.  There the generic instance's 16- and 8-wide tiles are the better ones: 100 x 12 x 16 x 16, 24
+  // filters 15.4 against 9.6 us, 8 x 64 x 16 x 16, 64 filters 49 against 27, 128 x 32 x 16 x 16, 32 filters 27 against 22; at 512
+  // images 48 against 53.  Gradients of few channels into few, where little is left of a tile, cross at two thirds of
+  // that number (187 x 4 x 10 x 16 behind pooling, 16 channels: 7.2 against 9.1).
+  const bool narrow = a.Wout <= 16 && 4L * a.N * ((a.Hout + 15) / 16) <= (a.src_dz && a.Cin <= 16 && a.Kout <= 16 ? 2L : 3L) * chip().cus;
   // very few output channels: the banded-filter kernel takes Kout * ceil((16 + S - 1) / 4) MFMA steps per
   // channel and filter row for 256 pixels where the channel columns of the engine take 4 * S (one to three
   // of whose 16 columns are real): 16 x 2 x 45 x 45 behind 20 maps, 3x3: both backward passes 38 -> 20 us; but three channels, 3x3,
   // 64 x 64 maps: 32 -> 43.  With fewer source channels than outputs most of its wavefronts idle (3 x 20 x 56 x 23 behind
-  // one map, 11x11: 12.8 us against 9.0).  Two or three channels of a layer the 3x3 instance takes stay with it until the filter
-  // rows are long.
+  // one map, 11x11: 12.8 us against 9.0).  Two channels of a layer that the 3x3 instance takes stay with it, except on narrow maps
+  // (112 x 16 x 16 x 16 into two channels: 13.6 us in the 3x3 instance, 11.9 in the generic one, 9.6 here).
   const int few_steps = a.Kout * ((16 + a.S - 1 + 3) / 4);
-  if (a.Kout <= 3 && a.Cin >= a.Kout && few_steps < 4 * a.S && conv_fewout_applies(a) && (few_steps * 3 < 8 * a.S || conv3x3c16_pick(a).NT == 0))
+  if (a.Kout <= 3 && a.Cin >= a.Kout && few_steps < 4 * a.S && conv_fewout_applies(a) && (few_steps * 3 < 8 * a.S || narrow || conv3x3c16_pick(a).NT == 0))
     return launch_conv_fewout(a, stream);
   if (conv_fwd_fewch_applies(a)) return launch_conv_fwd_fewch(a, stream);
   if (conv_wino_stream_applies(a) || conv_wino_stream_bwd_applies(a)) return launch_conv_wino_stream(a, stream);
   if (conv_wino_applies(a)) return launch_conv_wino(a, stream);
-  // The 3x3 instance's tiles are 32 x 16: a map of at most 16 columns fills half of one, and few of them leave most of the
-  // chip idle.  There the generic instance's 16- and 8-wide tiles are the better ones: 100 x 12 x 16 x 16, 24
-  // filters 15.4 against 9.6 us, 8 x 64 x 16 x 16, 64 filters 49 against 27, 128 x 32 x 16 x 16, 32 filters 27 against 22; at 512
-  // images 48 against 53.
-  const bool narrow = a.Wout <= 16 && 4L * a.N * ((a.Hout + 15) / 16) <= 3L * chip().cus;
   if (a.Hout > 8 && !narrow) {
     const Conv3x3Pick pick = conv3x3c16_pick(a);
     if (pick.NT == 1 && pick.CC == 8) return launch_3x3<1, 4, 8>(a, stream);

@@ -63,3 +63,15 @@ def test_forward_products_do_not_mind_an_odd_batch(tmp_path):
     first = [launches[0][0] for _, launches in record(calls, tmp_path)]
     assert all("gemm_fast" in f for f in first[:3]) and "gemm_small" in first[3]
     assert "gemm_fast" in first[4] and "gemm_small" in first[5] and "gemm_small" in first[6]
+
+
+def test_narrow_3x3_layers(tmp_path):
+    """Maps of at most 16 columns that leave the chip half empty: two channels are the few-output kernel's, as on any
+    layer that the 3x3 instance does not take (they had come to the generic one, two of whose 16 columns they fill);
+    gradients of few channels stay with the 3x3 instance from two thirds of the other layers' number of tiles on."""
+    calls = [["bwd", 100, 2, 16, 16, 16, 3, 3, 1, "relu", 2], ["fwd", 100, 20, 16, 16, 2, 3, 3, 1, "relu", 1],
+             ["bwd", 128, 16, 16, 16, 8, 3, 3, 1, "relu", 1], ["bwd", 129, 16, 16, 16, 8, 3, 3, 1, "relu", 1],
+             ["bwd", 192, 32, 16, 16, 8, 3, 3, 1, "relu", 1], ["bwd", 193, 32, 16, 16, 8, 3, 3, 1, "relu", 1]]
+    names = [launches[0][0] for _, launches in record(calls, tmp_path)]
+    want = ["conv_fewout_kernel", "conv_fewout_kernel", "conv_engine_kernel", "conv3x3c16_kernel", "conv_engine_kernel", "conv3x3c16_kernel"]
+    assert all(w in n for w, n in zip(want, names)), names
