@@ -48,6 +48,44 @@ __device__ __forceinline__ float act_apply(int act, float z) {
   return z;
 }
 
+// The same sums tap by tap, straight from memory: the zeros beside the band carry an infinity or NaN of the source into
+// all 16 columns, so a wavefront whose sums are not all finite takes its channels again here, and it reaches the
+// outputs whose windows hold it and no others.  It reads the kernel's arguments again: kept in scalar registers for it,
+// they cost the loop above 2 to 8 %.
+template <int KO, int WAVES, bool POOL>
+__device__ __forceinline__ void tap_by_tap(floatx4 (&acc)[KO]) {
+  unsigned long args = (unsigned long)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
+  const auto &p = *(const __attribute__((address_space(4))) FewoutParams *)args;
+  const auto &a = p.a;
+  const int bid = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = bid / (p.tiles_x * p.tiles_y), ty = (bid / p.tiles_x) % p.tiles_y;
+  const int i = ty * 16 + 4 * (lane >> 4), j = bid % p.tiles_x * 16 + (lane & 15);
+  const int RSf = a.R * a.S, Ws = POOL ? a.Win >> 1 : a.Win, Hs = POOL ? a.Hin >> 1 : a.Hin;
+#pragma unroll
+  for (int c = 0; c < KO; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int ci = wave; ci < a.Cin; ci += WAVES)
+    for (int rs = 0; rs < RSf; ++rs) {
+      const int gj = j - a.pad_w + rs % a.S;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int gi = i + v - a.pad_h + rs / a.S;
+        if (gi < 0 || gi >= a.Hin || gj < 0 || gj >= a.Win) continue;
+        const long o = ((long)(n * a.Cin + ci) * Hs + (POOL ? gi >> 1 : gi)) * Ws + (POOL ? gj >> 1 : gj);
+        float x = a.src[o];
+        if (a.src_dz && a.src_act == ACT_SIGMOID) x *= a.src_y[o] * (1.0f - a.src_y[o]);
+        if (a.src_dz && a.src_act == ACT_RELU) x = a.src_y[o] > 0.0f ? x : 0.0f;
+        if constexpr (POOL) {
+          const unsigned char f = a.src_idx[o];
+          if ((f & kIdxPosMask) != (((gi & 1) << 1) | (gj & 1)) || (a.src_act == ACT_RELU_FLAGGED && (f & kIdxInactive))) x = 0.0f;
+        }
+#pragma unroll
+        for (int c = 0; c < KO; ++c)
+          acc[c][v] = fmaf(x, a.w[a.w_flip ? (long)(ci * KO + c) * RSf + (RSf - 1 - rs) : (long)(c * a.Cin + ci) * RSf + rs], acc[c][v]);
+      }
+    }
+}
+
 // NS: window values per lane and channel; POOL: the source is dz behind 2x2 pooling
 template <int KO, int NS, int WAVES, bool POOL>
 __global__ __launch_bounds__(WAVES * 64) void conv_fewout_kernel(const FewoutParams p) {
@@ -187,6 +225,13 @@ __global__ __launch_bounds__(WAVES * 64) void conv_fewout_kernel(const FewoutPar
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
+
+  bool finite = true;
+#pragma unroll
+  for (int c = 0; c < KO; ++c)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) finite = finite && __builtin_isfinite(acc[c][v]);
+  if (!__all(finite)) tap_by_tap<KO, WAVES, POOL>(acc);
 
   // ---- the wavefronts' partial tiles, added in wavefront order, then bias, activation, store.
   // Lane holds D[row 4*kq + v][column i16].
