@@ -691,8 +691,6 @@ bool plan_engine(const ConvEngineArgs &a, int NT, int RP, int MT, int tables, En
   return true;
 }
 
-constexpr long kMaxGrid = (1L << 24) - 1;   // workgroups of 256 threads that a launch can have along x
-
 template <int NT, int RP, int MT>
 hipError_t launch_t(const ConvEngineArgs &a, hipStream_t stream) {
   EngineParams p;

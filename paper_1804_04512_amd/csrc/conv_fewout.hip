@@ -299,6 +299,7 @@ bool conv_fewout_applies(const ConvEngineArgs &a) {
   if (a.act != ACT_IDENTITY && a.act != ACT_SIGMOID && a.act != ACT_RELU) return false;
   if (a.src_dz && a.src_pool != 2 && a.src_act != ACT_IDENTITY && a.src_act != ACT_SIGMOID && a.src_act != ACT_RELU) return false;
   if (16 + a.S - 1 > 4 * kSteps || (16 + a.R - 1) * fewout_winp(a) > 64 * kPlaneSlots || a.Kout * a.R * a.S > 64 * kTapSlots) return false;
+  if ((long)a.N * ((a.Hout + 15) / 16) * ((a.Wout + 15) / 16) > kMaxGrid) return false;   // the engine's tiles are wider
   // 32-bit byte offsets inside a plane and a channel's filters
   if (4L * a.Hin * a.Win >= (long)kOob || 4L * a.Kout * a.Cin * a.R * a.S >= (long)kOob) return false;
   return fewout_lds_bytes(a, 4) <= 64 * 1024;
@@ -314,7 +315,7 @@ hipError_t launch_conv_fewout(const ConvEngineArgs &a, hipStream_t stream) {
   p.wsteps = p.winp / 4;
   p.inv_winp = (65536 + p.winp - 1) / p.winp;
   const long blocks = (long)a.N * p.tiles_x * p.tiles_y;
-  if (blocks <= 0 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  if (blocks <= 0 || blocks > kMaxGrid) return hipErrorInvalidValue;
   // eight wavefronts a tile halve the chain of channels each walks, as long as the tiles alone leave SIMDs idle
   const bool huge = a.src_dz && a.src_pool == 2 && p.rows * p.winp > 64 * 12;
   const int waves = !huge && a.Cin > 4 && blocks < 4L * chip().cus && fewout_lds_bytes(a, 8) <= 64 * 1024 ? 8 : 4;

@@ -446,12 +446,18 @@ hipError_t launch_conv_full_fft(const ConvFftArgs &g, hipStream_t stream) {
   f.count = g.K * g.C; f.H = g.R; f.W = g.S; f.lph = lph; f.lpw = lpw;
   f.pair_stride = 0; f.planes = 1;
   f.out = g.wf;
-  hipLaunchKernelGGL(fft2_forward_kernel, dim3(pairs * g.K + f.count), dim3(kFftThreads), lds, stream, x, f, pairs * g.K);
+  const long nx = (long)pairs * g.K, nw = f.count;
+  if (nx + nw <= kMaxGrid) {
+    hipLaunchKernelGGL(fft2_forward_kernel, dim3((unsigned)(nx + nw)), dim3(kFftThreads), lds, stream, x, f, (int)nx);
+  } else {   // more transforms than a grid holds: one operand after the other
+    hipLaunchKernelGGL(fft2_forward_kernel, dim3((unsigned)nx), dim3(kFftThreads), lds, stream, x, f, (int)nx);
+    hipLaunchKernelGGL(fft2_forward_kernel, dim3((unsigned)nw), dim3(kFftThreads), lds, stream, x, f, 0);
+  }
   FftInvArgs v;
   v.xf = g.xf; v.wf = g.wf; v.N = g.N; v.K = g.K; v.C = g.C; v.lph = lph; v.lpw = lpw;
   v.H = g.H; v.W = g.W; v.off = g.pad; v.out = g.dx;
   v.yf = g.yf;
-  if (g.yf) {
+  if (g.yf && (long)pairs * g.C <= kMaxGrid) {
     // 4 x 8 tiles once they give every SIMD of the chip two wavefronts (one wavefront of 8 x 8 tiles moves
     // less but waits out every k's loads: 38 against 35 us at 32 x 32 x 32 maps), 4 x 4 ones below
     const int chunks = (F + 63) / 64, prows = (pairs + 3) / 4;

@@ -655,6 +655,7 @@ struct StepTailParams {
   small_gemm::SmallParams gemm[StepTail::kMaxGemm];
   const float *rowloss; int rows; float *loss; double count;
   StepTail::Visible vis;
+  int vis_channels;   // side by side
   int start[StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 3];
   long group_stride[StepTail::kMaxReduce];
   int kgroups[StepTail::kMaxReduce];
@@ -686,7 +687,7 @@ __global__ __launch_bounds__(kThreads) void step_tail_kernel(const StepTailParam
   } else if (p.loss && j == p.n_reduce + p.n_colsum) {
     mean_block(p.rowloss, p.rows, p.loss, p.count);
   } else {
-    visible_block(p.vis.v0, p.vis.v1, p.vis.N, p.vis.C, p.vis.HW, p.vis.scratch, blk);
+    visible_block(p.vis.v0, p.vis.v1, p.vis.N, p.vis.C, p.vis.HW, p.vis.scratch, blk, p.vis_channels);
   }
 }
 
@@ -941,9 +942,12 @@ hipError_t launch_step_tail(const StepTail &t, hipStream_t stream) {
     blocks += 1;
   }
   p.vis = t.vis;
-  if (t.vis.v0) {
+  p.vis_channels = 1;
+  if (t.vis.v0) {   // as many channels side by side as the grid has left
+    const long left = (kMaxGrid - blocks) / kStatBlocks;
+    if (left > 1) p.vis_channels = (int)(t.vis.C < left ? t.vis.C : left);
     p.start[jobs++] = blocks;
-    blocks += kStatBlocks * t.vis.C;
+    blocks += kStatBlocks * p.vis_channels;
   }
   if (blocks == 0) return hipSuccess;
   for (int j = jobs; j < StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 3; ++j) p.start[j] = blocks;

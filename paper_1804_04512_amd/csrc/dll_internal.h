@@ -24,6 +24,8 @@ constexpr unsigned char kIdxPosMask = 3, kIdxInactive = 4;
 // units and the LDS of one compute unit, asked of the runtime once per device.
 struct ChipInfo { int cus = 0; size_t lds_bytes = 0; };
 const ChipInfo &chip();
+// Workgroups of 256 threads that a launch can have along x: the runtime refuses 2^32 threads.
+constexpr long kMaxGrid = (1L << 24) - 1;
 // Kernels that use more than 64 KB of dynamic LDS need the limit raised once per kernel and device;
 // this remembers which it has done.  A no-op for smaller sizes.
 hipError_t allow_large_lds(const void *kernel, size_t lds_bytes);

@@ -46,10 +46,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_small_kernel(const SmallParam
 // 903 x 2148 x 136 242 against 102, 867 x 1036 x 680 265 against 132) and up to 2^29 below (127 x 3012 x 2392 184
 // against 240); a forward product does not mind its batch (255 x 1912 x 1696: 47 there against 64 here).
 // And only while every operand and result lies below 2 GiB, where the kernel's buffers end (one row through a
-// weight matrix of 2^29 floats is not many multiply-adds); 32 elements less, so that its tiles are fewer than 2^24.
+// weight matrix of 2^29 floats is not many multiply-adds), and no extent is past 2^26, so that the jobs of a closing
+// launch, column sums of 16 columns a workgroup among them, fit a grid.
 bool gemm_is_small(GemmForm form, int M, int N, int Kdim) {
-  const long macs = (long)M * N * Kdim, limit = (1L << 29) - 32;
-  if ((long)M * N > limit || (long)M * Kdim > limit || (long)N * Kdim > limit) return false;
+  const long macs = (long)M * N * Kdim, limit = 1L << 29;
+  if ((long)M * N >= limit || (long)M * Kdim >= limit || (long)N * Kdim >= limit) return false;
+  if (M > (1 << 26) || N > (1 << 26) || Kdim > (1 << 26)) return false;
   const int rows = (form == GemmForm::kWeightGrad ? M : Kdim) | N;
   if ((rows & 3) != 0) return macs <= (1L << 30);
   const int batch = form == GemmForm::kDataGrad ? M : (form == GemmForm::kWeightGrad ? Kdim : 0);

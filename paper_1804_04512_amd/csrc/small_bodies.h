@@ -76,26 +76,28 @@ __device__ __forceinline__ void mean_block(const float *v, int n, float *out, do
   if (threadIdx.x == 0) *out = (float)(((sh[0] + sh[1]) + (sh[2] + sh[3])) / count);
 }
 
-// The CRBM's visible sums, kStatBlocks workgroups per channel: scratch[ch][b] = sum over the block's slice of
-// (v0 - v1); scratch[C*32 + ch*32 + b] = sum of squares
+// The CRBM's visible sums, kStatBlocks workgroups per channel, `channels` of them side by side: scratch[ch][b] = sum over
+// the block's slice of (v0 - v1); scratch[C*32 + ch*32 + b] = sum of squares
 constexpr int kStatBlocks = 32;
-__device__ __forceinline__ void visible_block(const float *v0, const float *v1, int N, int C, int HW, float *scratch, int blk) {
+__device__ __forceinline__ void visible_block(const float *v0, const float *v1, int N, int C, int HW, float *scratch, int blk, int channels) {
   __shared__ float sh[kSmallThreads];
-  const int ch = blk / kStatBlocks, b = blk - ch * kStatBlocks;
+  const int b = blk % kStatBlocks;
   const long per = (long)N * HW;
-  float s = 0.0f, q = 0.0f;
-  for (long e = (long)b * kSmallThreads + threadIdx.x; e < per; e += (long)kStatBlocks * kSmallThreads) {
-    const long nn = e / HW, r = e - nn * HW;
-    const long o = (nn * C + ch) * HW + r;
-    const float d = v0[o] - v1[o];
-    s += d;
-    q += d * d;
-  }
-  s = block_reduce(s, sh, false);
-  q = block_reduce(q, sh, false);
-  if (threadIdx.x == 0) {
-    scratch[ch * kStatBlocks + b] = s;
-    scratch[(C + ch) * kStatBlocks + b] = q;
+  for (int ch = blk / kStatBlocks; ch < C; ch += channels) {
+    float s = 0.0f, q = 0.0f;
+    for (long e = (long)b * kSmallThreads + threadIdx.x; e < per; e += (long)kStatBlocks * kSmallThreads) {
+      const long nn = e / HW, r = e - nn * HW;
+      const long o = (nn * C + ch) * HW + r;
+      const float d = v0[o] - v1[o];
+      s += d;
+      q += d * d;
+    }
+    s = block_reduce(s, sh, false);
+    q = block_reduce(q, sh, false);
+    if (threadIdx.x == 0) {
+      scratch[ch * kStatBlocks + b] = s;
+      scratch[(C + ch) * kStatBlocks + b] = q;
+    }
   }
 }
 

@@ -75,3 +75,19 @@ def test_narrow_3x3_layers(tmp_path):
     names = [launches[0][0] for _, launches in record(calls, tmp_path)]
     want = ["conv_fewout_kernel", "conv_fewout_kernel", "conv_engine_kernel", "conv3x3c16_kernel", "conv_engine_kernel", "conv3x3c16_kernel"]
     assert all(w in n for w, n in zip(want, names)), names
+
+
+def test_grids_past_what_a_launch_can_have(tmp_path):
+    """A launch holds 2^24 - 1 workgroups of 256 threads along x.  Layers of more tiles, transforms or sums than that are
+    not refused where a kernel or a sequence of fewer exists."""
+    calls = [["bwd", 9_000_000, 1, 4, 20, 1, 3, 3, 1, "identity", 2],     # two 16 x 16 tiles an image, or one of 32 columns
+             ["fft", 16_000_000, 4, 2, 2, 2, 2, 2, 0, "identity", 1],     # 32 million inverse transforms, or 8 million of 2 x 2
+             ["fft", 2, 4096, 2, 2, 4095, 2, 2, 0, "identity", 1],        # as many transforms as fit
+             ["fft", 2, 4095, 2, 2, 4096, 2, 2, 0, "identity", 1],        # one operand after the other
+             ["crbm", 1, 600_000, 2, 2, 1, 1, 1, 0],                      # 19 million visible sums
+             ["rbm", 1, 400_000_000, 1]]                                  # 25 million column sums
+    got = record(calls, tmp_path)
+    for call, (status, launches) in zip(calls, got):
+        assert status == 0 and launches, call
+    forward = [[l for l in launches if "fft2_forward" in l[0]] for _, launches in got]
+    assert [len(f) for f in forward[1:4]] == [1, 1, 2] and forward[2][0][1] == (1 << 24) - 1
