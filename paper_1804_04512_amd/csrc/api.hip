@@ -508,7 +508,9 @@ dll_status dll_rbm_cd1_step(int batch, int n_vis, int n_hid, int visible, const 
   // epilogue - are jobs of one closing launch.  100 x 784 x 500: ten launches and 44.7 us before, 29.0 now.
   // (The hidden products follow the other two: see small_form.)
   const bool small = gemm_is_small(GemmForm::kDataGrad, B, nv, nh) && gemm_is_small(GemmForm::kWeightGrad, nh, nv, B);
-  float *v1p = small && v1 ? v1 : vstack + nV;   // else the reconstruction is the lower half of the stack
+  // The reconstruction goes straight to v1 unless its product still reads the states from there; else it is the
+  // lower half of the stack.
+  float *v1p = small && v1 && v1 != h0_sample_in ? v1 : vstack + nV;
   float *sq_partial = vstack;                    // small: gemm_small_tiles(B, nv) <= B * nv floats
 
   // hidden probabilities of a visible batch: sigmoid(b_hid + v W^T)
@@ -561,7 +563,8 @@ dll_status dll_rbm_cd1_step(int batch, int n_vis, int n_hid, int visible, const 
     t.colsum[t.n_colsum++] = StepTail::Colsum{h0p, B, nh, db, lr != 0.0f ? b_hid : nullptr, lr, nullptr, 0.0f, h1p, invB};
     t.colsum[t.n_colsum++] = StepTail::Colsum{v0, B, nv, dc, lr != 0.0f ? c_vis : nullptr, lr, nullptr, 0.0f, v1p, invB};
     if (recon_mse) { t.rowloss = sq_partial; t.rows = (int)gemm_small_tiles(B, nv); t.count = (double)B * nv; t.loss = recon_mse; }
-    return dev(launch_step_tail(t, s));
+    if ((st = dev(launch_step_tail(t, s))) != DLL_OK) return st;
+    return v1 && v1 != v1p ? dev(launch_copy(v1p, v1, nV, s)) : DLL_OK;
   }
   if (v1 && (st = dev(launch_copy(v1p, v1, nV, s))) != DLL_OK) return st;
   // statistics: with the phases stacked along the batch axis (signs and 1/B folded into the hidden
@@ -958,7 +961,8 @@ dll_status dll_cnn_forward(const dll_net_desc *net, const float *const *params, 
     if (q == D - 1 && prob) {
       // the softmax rides in the epilogue of a small product of few classes, or adds the split-K partials itself
       // (one image through the MNIST network and 128 through the large-image one: a launch less each, 4 us)
-      if (gemm_fuses_softmax(g.M, g.N, g.Kdim)) { g.sm_prob = prob; softmax_fused = true; }
+      // unless other tiles of that product still read its input where the probabilities go
+      if (gemm_fuses_softmax(g.M, g.N, g.Kdim) && prob != cur) { g.sm_prob = prob; softmax_fused = true; }
       else if (g.split_k > 1) { g.defer_reduce = true; logits_split = g.split_k; }
     }
     if ((st = dev(launch_gemm(g, s))) != DLL_OK) return st;

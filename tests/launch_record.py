@@ -33,7 +33,8 @@ class _Pointers:
 
 def _make(B, L, what, *args):
     """One call by name: 'fwd' / 'bwd' / 'wgrad' / 'fft' / 'crbm' (ConvSpec fields), 'rbm' (batch, n_vis, n_hid),
-    'infer' / 'train' (conv layers, dense layers, classes, batch)."""
+    'infer' / 'train' (conv layers, dense layers, classes, batch); 'rbm_in_place' writes v1 over h0_sample_in,
+    'infer_in_place' the probabilities over x."""
     from paper_1804_04512_amd.workloads import ConvSpec, DenseSpec
     p, ws = _Pointers(), C.c_void_p(1 << 20)
     if what in ("fwd", "bwd", "wgrad", "fft", "crbm"):
@@ -48,12 +49,18 @@ def _make(B, L, what, *args):
         if what == "fft":
             return L.dll_conv_full_bwd_fft(ref, p(), None if d.act == 0 else p(), idx, p(), p(), ws, WORKSPACE, None)
         return L.dll_crbm_cd1_step_units(ref, 0, 1, p(), p(), p(), p(), p(), None, 0.1, p(), p(), p(), *([None] * 6), ws, WORKSPACE, None)
+    if what == "rbm_in_place":
+        h = p()
+        return L.dll_rbm_cd1_step(*args, 0, p(), p(), p(), p(), None, h, 0.1, p(), p(), p(), None, None, h, None, p(), ws, WORKSPACE, None)
     if what == "rbm":
         return L.dll_rbm_cd1_step(*args, 0, p(), p(), p(), p(), p(), None, 0.1, p(), p(), p(), *([None] * 4), p(), ws, WORKSPACE, None)
     conv, dense, classes, batch = args
     net = B.net_desc([ConvSpec(*c) for c in conv], [DenseSpec(*q) for q in dense], classes, batch)
     params = (C.c_void_p * (2 * (len(conv) + len(dense))))(*[p() for _ in range(2 * (len(conv) + len(dense)))])
     ref = C.byref(net.desc)
+    if what == "infer_in_place":
+        x = p()
+        return L.dll_cnn_forward(ref, params, x, None, x, ws, WORKSPACE, None)
     if what == "infer":
         return L.dll_cnn_forward(ref, params, p(), None, p(), ws, WORKSPACE, None)
     return L.dll_cnn_train_step(ref, params, None, p(), p(), 0.1, p(), None, None, ws, WORKSPACE, None)

@@ -91,3 +91,12 @@ def test_grids_past_what_a_launch_can_have(tmp_path):
         assert status == 0 and launches, call
     forward = [[l for l in launches if "fft2_forward" in l[0]] for _, launches in got]
     assert [len(f) for f in forward[1:4]] == [1, 1, 2] and forward[2][0][1] == (1 << 24) - 1
+
+
+def test_outputs_over_inputs(tmp_path):
+    """A one-layer network's probabilities over its input and an RBM step's reconstruction over the states it starts from:
+    nothing writes there while a product still reads (both had come to be written by that product itself)."""
+    calls = [["infer_in_place", [], [[12, 10]], 10, 50], ["infer", [], [[12, 10]], 10, 50], ["rbm_in_place", 40, 48, 48], ["rbm", 40, 48, 48]]
+    names = [[l[0] for l in launches] for _, launches in record(calls, tmp_path)]
+    assert [len(n) for n in names] == [2, 1, 5, 4]
+    assert "softmax" in names[0][1] and "copy" in names[2][4]
