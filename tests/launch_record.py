@@ -32,12 +32,12 @@ class _Pointers:
 
 
 def _make(B, L, what, *args):
-    """One call by name: 'fwd' / 'bwd' / 'wgrad' / 'fft' / 'crbm' (ConvSpec fields), 'rbm' (batch, n_vis, n_hid),
+    """One call by name: 'fwd' / 'bwd' / 'wgrad' / 'fft' / 'fft_less' / 'crbm' (ConvSpec fields), 'rbm' (batch, n_vis, n_hid),
     'infer' / 'train' (conv layers, dense layers, classes, batch); 'rbm_in_place' writes v1 over h0_sample_in,
     'infer_in_place' the probabilities over x."""
     from paper_1804_04512_amd.workloads import ConvSpec, DenseSpec
     p, ws = _Pointers(), C.c_void_p(1 << 20)
-    if what in ("fwd", "bwd", "wgrad", "fft", "crbm"):
+    if what in ("fwd", "bwd", "wgrad", "fft", "fft_less", "crbm"):
         d = B.conv_desc(ConvSpec(*args))
         ref, idx = C.byref(d), p() if d.pool == 2 else None
         if what == "fwd":
@@ -46,8 +46,9 @@ def _make(B, L, what, *args):
             return L.dll_conv_full_bwd(ref, p(), None if d.act == 0 else p(), idx, p(), p(), None, 0, None)
         if what == "wgrad":
             return L.dll_conv_valid_wgrad(ref, p(), p(), None if d.act == 0 else p(), idx, p(), p(), ws, WORKSPACE, None)
-        if what == "fft":
-            return L.dll_conv_full_bwd_fft(ref, p(), None if d.act == 0 else p(), idx, p(), p(), ws, WORKSPACE, None)
+        if what in ("fft", "fft_less"):   # less: a workspace without the product spectra
+            room = WORKSPACE if what == "fft" else L.dll_conv_full_fft_workspace_bytes(ref) - 256
+            return L.dll_conv_full_bwd_fft(ref, p(), None if d.act == 0 else p(), idx, p(), p(), ws, room, None)
         return L.dll_crbm_cd1_step_units(ref, 0, 1, p(), p(), p(), p(), p(), None, 0.1, p(), p(), p(), *([None] * 6), ws, WORKSPACE, None)
     if what == "rbm_in_place":
         h = p()

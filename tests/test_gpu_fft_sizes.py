@@ -1,6 +1,7 @@
 """The Fourier route of the full convolution over its padded sides (every power of two from 2 to 64, equal and
-not), the edges of the product kernel's 4 x 8 and 4 x 4 tiles of image pairs and channels, odd batches, a
-single map, and a workspace that holds no product spectra (the route in two launches instead of three)."""
+not), the edges of the product kernel's 4 x 4 tiles of image pairs and channels and, where there is work for them, 4 x 8
+ones, odd batches, a single map, and a workspace that holds no product spectra (the route in two launches instead of
+three, in tiles of one or, where there is work for them, 2 x 2)."""
 import numpy as np
 import pytest
 
@@ -22,6 +23,8 @@ TOL = 4e-6
 SIDES = [ConvSpec(2, 2, h + r - 1, w + s - 1, 3, r, s, 0, "identity", 1)
          for h, r, w, s in [(1, 2, 1, 1), (2, 2, 3, 3), (5, 4, 4, 5), (8, 9, 20, 7), (18, 15, 1, 64), (64, 1, 2, 2), (50, 15, 25, 8), (33, 2, 9, 9)]]
 TILES = [ConvSpec(n, c, 20, 37, k, 6, 9, 3, "identity", 1) for n, c, k in [(1, 1, 1), (7, 5, 2), (16, 8, 3), (17, 9, 4), (33, 17, 5)]]
+# enough work for tiles of 4 x 8 (2048 wavefronts of them) and 2 x 2 (1024 image pairs x channels), short at both ends
+TILES += [ConvSpec(63, 33, 48, 48, 5, 15, 15, 0, "identity", 1), ConvSpec(61, 35, 50, 40, 3, 9, 6, 2, "identity", 1)]
 
 
 @pytest.mark.parametrize("cs", SIDES + TILES, ids=lambda c: f"N{c.N}C{c.C}K{c.K}_{c.Ho}x{c.Wo}_{c.R}x{c.S}p{c.pad}")

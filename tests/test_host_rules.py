@@ -100,3 +100,24 @@ def test_outputs_over_inputs(tmp_path):
     names = [[l[0] for l in launches] for _, launches in record(calls, tmp_path)]
     assert [len(n) for n in names] == [2, 1, 5, 4]
     assert "softmax" in names[0][1] and "copy" in names[2][4]
+
+
+def test_fourier_tile_sizes_have_a_test(tmp_path):
+    """test_gpu_fft_sizes.py reaches every instance of the product kernels."""
+    cases = [(n, c, h, w, k, r, s, p) for n, c, k, h, w, r, s, p in [(63, 33, 5, 48, 48, 15, 15, 0), (61, 35, 3, 50, 40, 9, 6, 2), (33, 17, 5, 20, 37, 6, 9, 3)]]
+    calls = [[what, *c, "identity", 1] for c in cases for what in ("fft", "fft_less")]
+    names = ["".join(l[0] for l in launches) for _, launches in record(calls, tmp_path)]
+    want = ["product_kernelILi4ELi8E", "product_inverse_kernelILi2ELi2E"] * 2 + ["product_kernelILi4ELi4E", "product_inverse_kernelILi1ELi1E"]
+    assert all(w in n for w, n in zip(want, names)), names
+
+
+# RBM steps (batch, visible, hidden units): the largest of their kind in the small-product kernels, and the next beyond
+LINES = [((64, 1024, 4096), (64, 1024, 4100)), ((128, 1024, 1536), (128, 1024, 1540)), ((512, 1024, 1024), (516, 1024, 1024)),
+         ((127, 1024, 4124), (127, 1024, 4132)), ((129, 2048, 4064), (129, 2048, 4068)), ((513, 1025, 2041), (513, 1025, 2045))]
+
+
+def test_rbm_steps_on_either_side_of_the_lines(tmp_path):
+    got = record([["rbm", *c] for pair in LINES for c in pair], tmp_path)
+    small = ["step_tail_kernelILb1E" in launches[-1][0] and len(launches) == 4 for _, launches in got]
+    assert small == [True, False] * len(LINES), small
+    assert any("11gemm_kernel" in l[0] for l in got[-1][1])   # the element-wise form
