@@ -767,7 +767,7 @@ dll_status run_cnn_step(const dll_net_desc *net, float *const *params, float *co
   };
   tail.rowloss = nb.rowloss; tail.rows = B; tail.loss = loss;
   if (!loss_fused) {
-    st = dev(launch_softmax_ce(nb.act[L + D], labels, B, net->classes, nullptr, nb.dz[D - 1], nb.rowloss,
+    st = dev(launch_softmax_ce(nb.act[L + D], labels, B, net->classes, nb.dz[D - 1], nb.rowloss,
                                logits_split > 1 ? nb.partial : nullptr, logits_split, params[2 * (L + D - 1) + 1], s));
     if (st != DLL_OK) return st;
   }

@@ -243,12 +243,11 @@ size_t gemm_small_tiles(int M, int N);
 hipError_t launch_colsum(const float *A, int M, int N, float *out,
                          float *update, float step, float *vel, float mu, hipStream_t stream);
 
-// Softmax cross-entropy over rows; loss = mean; dlogits = (p - onehot)/B.  rowloss: B floats scratch.
+// Softmax cross-entropy over rows: dlogits = (p - onehot)/B, rowloss[n] = the row's loss (the closing launch takes the mean).
 // With partial != NULL the logits are first formed from split_k partial products [z][B][classes]
 // plus bias (what the deferred split-K reduction would have written) and stored to `logits`.
-hipError_t launch_softmax_ce(float *logits, const int *labels, int B, int classes, float *loss,
-                             float *dlogits, float *rowloss, const float *partial, int split_k, const float *bias,
-                             hipStream_t stream);
+hipError_t launch_softmax_ce(float *logits, const int *labels, int B, int classes, float *dlogits, float *rowloss,
+                             const float *partial, int split_k, const float *bias, hipStream_t stream);
 
 // prob[n][j] = softmax(logits[n][:])[j] with the row maximum subtracted (inference output).  With partial !=
 // NULL the logits are formed first, as by launch_softmax_ce.

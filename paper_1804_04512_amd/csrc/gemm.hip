@@ -821,8 +821,6 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(float *logits, con
   if (tid == 0) rowloss[n] = -(r[label] - m - logf(s));
 }
 
-__global__ __launch_bounds__(kThreads) void mean_kernel(const float *v, int count, float *out) { mean_block(v, count, out, (double)count); }
-
 // One wavefront: a lane per slice (32 sums, 32 sums of squares), added by lane exchanges in double.
 __global__ void visible_stats_final_kernel(const float *scratch, int N, int C, int HW, float scale, float *dc, float *mse,
                                            float *c_update, float step) {
@@ -899,7 +897,7 @@ GemmPlan plan_gemm(const GemmArgs &a) {
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream) {
-  if (a.split_k <= 1 && a.a_k == 1 && (a.small_form || gemm_is_small(a.b_k == 1 ? GemmForm::kForward : GemmForm::kDataGrad, a.M, a.N, a.Kdim))) return launch_gemm_small(a, stream);
+  if (a.split_k <= 1 && a.a_k == 1 && !a.update && (a.small_form || gemm_is_small(a.b_k == 1 ? GemmForm::kForward : GemmForm::kDataGrad, a.M, a.N, a.Kdim))) return launch_gemm_small(a, stream);
   if (a.sm_labels) return hipErrorInvalidValue;   // the fused loss exists in the small-product kernel only
   const GemmPlan g = plan_gemm(a);
   const GemmParams &p = g.p;
@@ -942,8 +940,7 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream) {
 // persistent kernel's fused-update form with the same operand forms, the units of the second are
 // appended to the first's; else they are launched one after the other.
 hipError_t launch_gemm_pair(const GemmArgs &a, const GemmArgs &b, hipStream_t stream) {
-  const bool a_small = a.split_k <= 1 && gemm_is_small(GemmForm::kWeightGrad, a.M, a.N, a.Kdim), b_small = b.split_k <= 1 && gemm_is_small(GemmForm::kWeightGrad, b.M, b.N, b.Kdim);
-  if (!a_small && !b_small && !a.sm_labels && !b.sm_labels && a.split_k <= 1 && b.split_k <= 1) {
+  if (!a.sm_labels && !b.sm_labels && a.split_k <= 1 && b.split_k <= 1) {
     const GemmPlan ga = plan_gemm(a), gb = plan_gemm(b);
     if (ga.fast && gb.fast && ga.mode == 1 && gb.mode == 1 && ga.a_kc == gb.a_kc && ga.b_kc == gb.b_kc) {
       const long units = (long)ga.grid.x * ga.grid.y + (long)gb.grid.x * gb.grid.y;
@@ -967,14 +964,10 @@ hipError_t launch_colsum(const float *A, int M, int N, float *out, float *update
   return hipGetLastError();
 }
 
-hipError_t launch_softmax_ce(float *logits, const int *labels, int B, int classes, float *loss, float *dlogits,
-                             float *rowloss, const float *partial, int split_k, const float *bias, hipStream_t stream) {
+hipError_t launch_softmax_ce(float *logits, const int *labels, int B, int classes, float *dlogits, float *rowloss,
+                             const float *partial, int split_k, const float *bias, hipStream_t stream) {
   hipLaunchKernelGGL(softmax_ce_kernel, dim3(B), dim3(kThreads), 0, stream, logits, labels, B, classes, dlogits, rowloss,
                      partial, split_k, bias);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (!loss) return e;   // the caller takes the mean of rowloss later (step closing kernel)
-  hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kThreads), 0, stream, rowloss, B, loss);
   return hipGetLastError();
 }
 

@@ -14,8 +14,7 @@
 //     operands use the same one), which makes a k-contiguous operand two 16-byte loads per row;
 //   * the partial tiles meet in LDS once, are added in wavefront order (results do not depend
 //     on timing), and one wavefront per 16 x 16 quarter of the tile finishes it: bias, activation,
-//     act' of a reference tensor, store and/or fused parameter update.  No split-K partials in
-//     global memory, no reduction launch.
+//     act' of a reference tensor, store.  No split-K partials in global memory, no reduction launch.
 // Every global load is a range-checked buffer load: what lies past an operand's end reads as zero, so nothing
 // is masked but the rows that are no whole 16-byte groups, and that at the multiplication.
 #include "dll_internal.h"
@@ -70,13 +69,12 @@ bool gemm_prefers_small(const GemmArgs &a) {
 bool gemm_fuses_softmax(int M, int N, int Kdim) { return gemm_is_small(GemmForm::kForward, M, N, Kdim) && N <= 16 && (M + 31) / 32 <= 512; }
 
 hipError_t launch_gemm_small(const GemmArgs &a, hipStream_t stream) {
-  if (a.sm_prob && (a.sm_labels || !gemm_fuses_softmax(a.M, a.N, a.Kdim) || a.act != ACT_IDENTITY || a.update || a.C_ref)) return hipErrorInvalidValue;
-  if (a.sm_labels && (!gemm_fuses_softmax(a.M, a.N, a.Kdim) || !a.sm_dz || !a.sm_rowloss || a.act != ACT_IDENTITY || a.update ||
-                      a.C_ref))
+  if (a.sm_prob && (a.sm_labels || !gemm_fuses_softmax(a.M, a.N, a.Kdim) || a.act != ACT_IDENTITY || a.C_ref)) return hipErrorInvalidValue;
+  if (a.sm_labels && (!gemm_fuses_softmax(a.M, a.N, a.Kdim) || !a.sm_dz || !a.sm_rowloss || a.act != ACT_IDENTITY || a.C_ref))
     return hipErrorInvalidValue;
   SmallParams p;
-  // A across k: the weight-gradient form, a job of the closing launch
-  if (a.a_k != 1 || a.A2 || a.B2 || !small_gemm::make_params(a, &p)) return hipErrorInvalidValue;
+  // A across k, updates: the weight-gradient form, a job of the closing launch
+  if (a.a_k != 1 || a.update || a.A2 || a.B2 || !small_gemm::make_params(a, &p)) return hipErrorInvalidValue;
   const bool b_kc = a.b_k == 1;
   const bool fine = small_gemm::tile_quarters(a.M, a.N) == 1;
   const int TS = fine ? 16 : 32;

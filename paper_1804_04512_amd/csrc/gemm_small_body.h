@@ -169,15 +169,13 @@ __device__ __forceinline__ void tile_product(const SmallParams &p, int mt, int n
   const bool min_ = m < a.M;
   bool ok[4];
   long o[4];
-  float bv[4], rv[4], uv[4], vv[4];
+  float bv[4], rv[4];
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     ok[v] = min_ && n + v < a.N;
     o[v] = ok[v] ? (long)m * a.c_m + (long)(n + v) * a.c_n : 0;
     bv[v] = a.bias ? a.bias[n + v < a.N ? n + v : 0] : 0.0f;
     rv[v] = a.C_ref ? a.C_ref[o[v]] : 0.0f;
-    uv[v] = a.update ? a.update[o[v]] : 0.0f;
-    vv[v] = a.vel ? a.vel[o[v]] : 0.0f;
   }
   float un[4] = {0.0f, 0.0f, 0.0f, 0.0f}, sq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   if constexpr (EXTRAS) {
@@ -231,11 +229,6 @@ __device__ __forceinline__ void tile_product(const SmallParams &p, int mt, int n
     if (a.C_ref) c[v] *= act_deriv(a.c_ref_act, rv[v]);
     if (!ok[v]) continue;
     if (a.Cout) a.Cout[o[v]] = c[v];
-    if (a.update) {
-      update_param(&uv[v], a.vel ? &vv[v] : nullptr, c[v], a.step, a.mu, a.decay);
-      a.update[o[v]] = uv[v];
-      if (a.vel) a.vel[o[v]] = vv[v];
-    }
   }
   if constexpr (EXTRAS) {
     if (a.sq_ref) {   // one number per finished quarter, added up later in a fixed order
