@@ -354,26 +354,27 @@ __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 ? 3 : 2) void conv_engi
   // offsets are taken from the tile's first row and column inside the image
   const int gi0 = max(oy0 - a.pad_h, 0) >> sh, gj0 = max(ox0 - a.pad_w, 0) >> sh;
   // dz: the threads work in groups of one, two or four wavefronts, a group on every first, second or fourth channel
+  // (plain sources gain less than it costs to set up)
   const int groups = DZ ? 1 << g.split_log : 1, span_log = DZ ? 8 - g.split_log : 8, span = 1 << span_log;
   const int cl0 = DZ ? __builtin_amdgcn_readfirstlane(tid >> span_log) : 0, st = tid & (span - 1);
   const int drow = span / g.cols, dcol = span - drow * g.cols;
   const int row0 = st / g.cols, col0 = st - row0 * g.cols;
-  constexpr int kZero = 1 << 30, kPlace = 1 << 20;   // (LDS offsets are below 2^14)
+  constexpr int kZero = 1 << 30;
   int row = row0, col = col0, cl = cl0;   // the next pair
   int o = 0, at = 0;                    // its position's offset in a plane and in LDS
   bool in = false;
-  int place = 0;                        // its position's place in the pooling window, as a field of dst
+  unsigned char place = 0;              // its position's place in the pooling window
   auto look = [&]() __attribute__((always_inline)) {
     const int gi = oy0 - a.pad_h + row, gj = ox0 - a.pad_w + col;
     in = row < g.rows && gi >= 0 && gi < a.Hin && gj >= 0 && gj < a.Win;
     o = in ? ((gi >> sh) - gi0) * Ws + (gj >> sh) - gj0 : 0;
     at = row * g.RS + col;
-    place = (((gi & 1) << 1) | (gj & 1)) * kPlace;
+    place = (unsigned char)(((gi & 1) << 1) | (gj & 1));
   };
   const int pairs = ((positions + span - 1) >> span_log) * (DZ ? (g.CC - cl0 + groups - 1) >> g.split_log : g.CC);
   float gv[kBatch], yv[DZ ? kBatch : 1];
-  unsigned char fv[DZ ? kBatch : 1];
-  int dst[kBatch];                      // LDS offset, place; negative: nothing to store; with kZero: a channel past the last
+  unsigned char fv[DZ ? kBatch : 1], want[DZ ? kBatch : 1];
+  int dst[kBatch];                      // LDS offset; negative: nothing to store; with kZero: a channel past the last
   auto load_halo = [&](int c0, int q0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
@@ -381,7 +382,8 @@ __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 ? 3 : 2) void conv_engi
       // a position outside the image and a channel past the last read an element that exists
       const long base = (long)(n * a.Cin + min(c0 + cl, a.Cin - 1)) * plane + (long)gi0 * Ws + gj0;
       gv[u] = fetch(a.src + base, o);
-      dst[u] = in ? (cl * g.PS + at) | (c0 + cl < a.Cin ? 0 : kZero) | (DZ ? place : 0) : -1;
+      dst[u] = in ? (cl * g.PS + at) | (c0 + cl < a.Cin ? 0 : kZero) : -1;
+      if (DZ) want[u] = place;
       if constexpr (DZ) {
         if (need_y) yv[u] = fetch(a.src_y + base, o);
         if (pooled) fv[u] = fetch(a.src_idx + base, o);
@@ -402,12 +404,12 @@ __global__ __launch_bounds__(kThreads, NT < 3 && RP == 1 ? 3 : 2) void conv_engi
       float v = gv[u];
       if constexpr (DZ) {
         // dz at a pre-pool position: dy routed to the recorded arg-max, times act'(y)
-        if (pooled && (fv[u] & kIdxPosMask) * kPlace != (dst[u] & (kIdxPosMask * kPlace))) v = 0.0f;
+        if (pooled && (fv[u] & kIdxPosMask) != want[u]) v = 0.0f;
         if (a.src_act == ACT_RELU_FLAGGED) v = (fv[u] & kIdxInactive) ? 0.0f : v;
         else if (a.src_act == ACT_SIGMOID) v *= yv[u] * (1.0f - yv[u]);
         else if (a.src_act == ACT_RELU) v = yv[u] > 0.0f ? v : 0.0f;
       }
-      if (dst[u] >= 0) xs[dst[u] & (kPlace - 1)] = (dst[u] & kZero) ? 0.0f : v;
+      if (dst[u] >= 0) xs[dst[u] & (kZero - 1)] = (dst[u] & kZero) ? 0.0f : v;
     }
   };
 
@@ -722,11 +724,13 @@ hipError_t launch_lean(const ConvEngineArgs &a, hipStream_t stream) {
 // Which kernel and tile takes a layer.  Tiles of 16 rows where they give every compute unit two workgroups (`small`: not),
 // else of 8; maps of at most 8 or 16 columns take tiles that narrow.  The pipelined kernel hides the latency of a
 // launch that does not fill the chip, and keeps 32-bit byte offsets inside a tile's rows of a plane and a workgroup's
-// filters.  The lean one takes what lies beyond those, launches of two workgroups per compute unit or more, and
-// gradients with nothing to pipeline: one chunk into more than 16 channels, or of at most four channels.  Over 4000
-// random layers the pipelined kernel alone was more than 5 % slower than the lean one on 247 forward and 473
-// backward-data passes (at worst 1.7 times: 233 x 3 x 25 x 112, 2 filters 1x1, backward-data 26 against 15.5 us); the choice
-// made here is on 48 and 63, and the sum of all times went from 127.7 + 157.9 to 126.6 + 152.4 ms.
+// filters.  The lean one takes what lies beyond those, gradients with nothing to pipeline (one chunk into more than 16
+// channels, or of at most four channels), and launches of two workgroups per compute unit or more, unless LDS holds
+// no more of them than the pipelined kernel's registers (large filters), or a forward pass into 17 to 32 channels has
+// chunks to pipeline.  Over 4000 random layers the pipelined kernel alone was more than 5 % slower than the lean one on
+// 247 forward and 473 backward-data passes (at worst 1.7 times: 233 x 3 x 25 x 112, 2 filters 1x1, backward-data 26
+// against 15.5 us), over 1500 that fill the chip 270 and 489; there the lean one alone lost up to a quarter on large filters
+// (64 x 64 x 35 x 35, 32 channels 9x9, backward-data 888 against 680 us).
 template <int NT>
 hipError_t launch_generic(const ConvEngineArgs &a, bool small, hipStream_t stream) {
   const long tile_rows = (long)(16 + a.R - 1) * a.Win, filters = 48L * (a.Cin > a.Kout ? a.Cin : a.Kout) * a.R * a.S;
@@ -734,15 +738,18 @@ hipError_t launch_generic(const ConvEngineArgs &a, bool small, hipStream_t strea
   const long rows8 = (long)a.N * ((a.Hout + 7) / 8);
   EngineGeom g;
   size_t lds;
-  const bool short_dz = a.src_dz && plan_engine(a, NT, 1, 4, 1, &g, &lds) && g.nchunks == 1;
-  if (NT > 1 && short_dz && a.Cin <= 4) return launch_lean<NT, 1>(a, stream);
+  if (!plan_engine(a, NT, small ? 1 : 2, 4, 1, &g, &lds)) return hipErrorInvalidValue;
+  const bool lds_bound = (long)(chip().lds_bytes / lds) <= (NT < 3 && small ? 3 : 2);
+  const bool one_chunk = a.Cin <= 16 && plan_engine(a, NT, 1, 4, 1, &g, &lds) && g.nchunks == 1, short_dz = a.src_dz && one_chunk;
+  if (NT > 1 && short_dz && (a.Wout > 16 ? a.Cin <= 4 : a.Cin == 1 && a.Wout > 8)) return launch_lean<NT, 1>(a, stream);
   if (a.Wout <= 16 && !far && rows8 <= kMaxGrid) return a.Wout <= 8 ? launch_t<NT, 1, 1>(a, stream) : launch_t<NT, 1, 2>(a, stream);
   if (!small) {
-    if constexpr (NT == 1) return launch_lean<1, 2>(a, stream);
-    else return far ? launch_lean<NT, 1>(a, stream) : launch_t<NT, 2, 4>(a, stream);
+    if (!far && (NT > 1 || lds_bound)) return launch_t<NT, 2, 4>(a, stream);
+    return launch_lean<NT, NT == 1 ? 2 : 1>(a, stream);
   }
   const long units = rows8 * ((a.Wout + kTileW - 1) / kTileW) * ((a.Kout + NT * 16 - 1) / (NT * 16));
-  if (far || units >= 2L * chip().cus || (short_dz && (NT > 1 || a.Cin <= 4))) return launch_lean<NT, 1>(a, stream);
+  const bool pipelined = lds_bound || (NT == 2 && !a.src_dz && !one_chunk);
+  if (far || (units >= 2L * chip().cus && !pipelined) || (short_dz && (NT > 1 || a.Cin <= 4))) return launch_lean<NT, 1>(a, stream);
   return launch_t<NT, 1, 4>(a, stream);
 }
 
@@ -1316,10 +1323,11 @@ hipError_t launch_conv_engine(const ConvEngineArgs &a, hipStream_t stream) {
   // channel and filter row for 256 pixels where the channel columns of the engine take 4 * S (one to three
   // of whose 16 columns are real): 16 x 2 x 45 x 45 behind 20 maps, 3x3: both backward passes 38 -> 20 us; but three channels, 3x3,
   // 64 x 64 maps: 32 -> 43.  With fewer source channels than outputs most of its wavefronts idle (3 x 20 x 56 x 23 behind
-  // one map, 11x11: 12.8 us against 9.0).  Two channels of a layer that the 3x3 instance takes stay with it, except on narrow maps
+  // one map, 11x11: 12.8 us against 9.0; but two outputs of one unpooled channel, 59 x 100 x 100, 11x11: 39 against 52).  Two channels of a layer that the 3x3 instance takes stay with it, except on narrow maps
   // (112 x 16 x 16 x 16 into two channels: 13.6 us in the 3x3 instance, 11.9 in the generic one, 9.6 here).
   const int few_steps = a.Kout * ((16 + a.S - 1 + 3) / 4);
-  if (a.Kout <= 3 && a.Cin >= a.Kout && few_steps < 4 * a.S && conv_fewout_applies(a) && (few_steps * 3 < 8 * a.S || narrow || conv3x3c16_pick(a).NT == 0))
+  const bool enough = a.Cin >= a.Kout || (a.Kout == 2 && few_steps < 2 * a.S && !(a.src_dz && a.src_pool == 2));
+  if (a.Kout <= 3 && enough && few_steps < 4 * a.S && conv_fewout_applies(a) && (few_steps * 3 < 8 * a.S || narrow || conv3x3c16_pick(a).NT == 0))
     return launch_conv_fewout(a, stream);
   if (conv_fwd_fewch_applies(a)) return launch_conv_fwd_fewch(a, stream);
   if (conv_wino_stream_applies(a) || conv_wino_stream_bwd_applies(a)) return launch_conv_wino_stream(a, stream);

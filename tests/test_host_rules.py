@@ -21,7 +21,7 @@ def test_crbm_workspace_ignores_pooling_and_activation(shape):
 LEAN = [
     ("fwd", (130, 3, 40, 40, 8, 3, 3, 0, "relu", 2), (1, 2)), ("bwd", (130, 9, 33, 47, 18, 2, 3, 1, "sigmoid", 1), (1, 2)),
     ("fwd", (260, 2, 8, 40, 5, 3, 3, 1, "sigmoid", 1), (1, 1)), ("fwd", (171, 20, 10, 69, 7, 5, 4, 0, "identity", 1), (1, 1)),
-    ("fwd", (260, 17, 8, 34, 18, 3, 2, 0, "relu", 1), (2, 1)), ("bwd", (260, 18, 7, 40, 17, 3, 3, 0, "relu", 1), (2, 1)),
+    ("fwd", (260, 15, 8, 34, 18, 3, 2, 0, "relu", 1), (2, 1)), ("bwd", (260, 18, 7, 40, 17, 3, 3, 0, "relu", 1), (2, 1)),
     ("fwd", (258, 3, 8, 40, 33, 3, 3, 1, "relu", 2), (3, 1)), ("bwd", (130, 40, 14, 20, 3, 3, 3, 1, "relu", 2), (3, 1)),
     ("bwd", (3, 5, 20, 36, 4, 5, 5, 2, "sigmoid", 2), (1, 1)),
 ]
@@ -31,6 +31,15 @@ def test_lean_layers_reach_the_lean_kernel(tmp_path):
     got = record([[what, *c] for what, c, _ in LEAN], tmp_path)
     for (what, c, (nt, rp)), (status, launches) in zip(LEAN, got):
         assert status == 0 and f"conv_engine_lean_kernelILi{nt}ELi{rp}E" in launches[0][0], (what, c, launches)
+
+
+def test_full_launches_that_stay_pipelined(tmp_path):
+    """Large filters, of which LDS holds no more workgroups than the pipelined kernel's registers, and forward passes
+    into 17 to 32 channels with chunks to pipeline."""
+    calls = [["bwd", 64, 32, 43, 43, 64, 9, 9, 0, "sigmoid", 1], ["fwd", 260, 17, 8, 34, 18, 3, 2, 0, "relu", 1],
+             ["fwd", 60, 32, 56, 56, 8, 7, 7, 0, "relu", 2], ["bwd", 186, 8, 48, 48, 40, 7, 7, 3, "relu", 2]]
+    for call, (status, launches) in zip(calls, record(calls, tmp_path)):
+        assert status == 0 and "conv_engine_kernel" in launches[0][0], (call, launches)
 
 
 def test_layers_past_the_pipelined_kernel(tmp_path):
