@@ -49,8 +49,8 @@ __device__ __forceinline__ float act_apply(int act, float z) {
 }
 
 // The same sums tap by tap, straight from memory: the zeros beside the band carry an infinity or NaN of the source into
-// all 16 columns, so a wavefront whose sums are not all finite takes its channels again here, and it reaches the
-// outputs whose windows hold it and no others.  It reads the kernel's arguments again: kept in scalar registers for it,
+// all 16 columns, so a wavefront with finite sums and others takes its channels again here, and it reaches the
+// outputs whose windows hold it and no others (a filter of more than 16 rows can leave no sum of a tile finite).  It reads the kernel's arguments again: kept in scalar registers for it,
 // they cost the loop above 2 to 8 %.
 template <int KO, int WAVES, bool POOL>
 __device__ __forceinline__ void tap_by_tap(floatx4 (&acc)[KO]) {
@@ -226,12 +226,17 @@ __global__ __launch_bounds__(WAVES * 64) void conv_fewout_kernel(const FewoutPar
     __builtin_amdgcn_wave_barrier();
   }
 
-  bool finite = true;
+  // (a tile with no finite output, as all are once a training run has diverged, has nothing to set apart)
+  bool some = false, all = true;
 #pragma unroll
   for (int c = 0; c < KO; ++c)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) finite = finite && __builtin_isfinite(acc[c][v]);
-  if (!__all(finite)) tap_by_tap<KO, WAVES, POOL>(acc);
+    for (int v = 0; v < 4; ++v) {
+      const bool stored = i0 + 4 * kq + v < a.Hout && j0 + i16 < a.Wout, finite = __builtin_isfinite(acc[c][v]);
+      some = some || (stored && finite);
+      all = all && (!stored || finite);
+    }
+  if (!__all(all) && __any(some)) tap_by_tap<KO, WAVES, POOL>(acc);
 
   // ---- the wavefronts' partial tiles, added in wavefront order, then bias, activation, store.
   // Lane holds D[row 4*kq + v][column i16].
