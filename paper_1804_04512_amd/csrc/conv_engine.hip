@@ -315,7 +315,7 @@ __device__ __forceinline__ void multiply_chunk(const EngineGeom &g, const float 
 // element costs its load and its store.  Positions outside the image are cleared once and never written.
 // The first positions of a chunk are on their way during the products of the chunk before.  Before, each
 // element had an address of its own, walked with divergent carries, four at a time:
-// 33 x 40 x 45 x 51 gradients, 24 channels 3x3: 74 -> 67 us; 100 x 8 x 12 x 12, 8 filters 5x5: 14.9 -> 9.5.
+// 33 x 40 x 45 x 51 gradients, 24 channels 3x3: 74 -> 63 us; 100 x 8 x 12 x 12, 8 filters 5x5: 13.8 -> 8.7.
 // Bound by the latency of that chain for a few channels, by the matrix pipe for many.
 // kBatch: values of the halo tile in flight per thread: 8 where that is all of them (one to three channels) and
 // where dz needs three loads for each, else 12.  Three workgroups per CU up to 32 output channels: layers with

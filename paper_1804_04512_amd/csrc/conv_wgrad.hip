@@ -760,8 +760,10 @@ bool plan_wgrad(int N, int C, int H, int W, int K, int R, int S, int pad, int po
   // persistent workgroups: as many as stay resident (LDS and register budget), at least two
   // tiles each where the problem is large enough
   long resident = (long)(chip().lds_bytes / plan->lds_bytes);
-  // waves per SIMD that the kernel instance's registers (vector + accumulator, from the compiler's
-  // resource report) leave room for; a grid beyond it would queue workgroups behind resident ones
+  // waves per SIMD that the registers of the instances with layer output and whole rows (vector + accumulator, from
+  // the compiler's resource report) leave room for; a grid beyond it queues workgroups behind resident ones.  The
+  // instances without layer output fit one more at <3, 2>, <3, 5> and <3, 7> unpooled, some ragged ones one less: the
+  // grid, on which the partial sums' layout and order depend, is the same for all of a shape's instances.
   static const int kByRegs[2][3][4] = {
       // NTT =  2  5  7  9     (pooled staging)
       {{5, 4, 3, 3}, {4, 3, 2, 2}, {3, 2, 2, 2}},
