@@ -429,19 +429,19 @@ dll_status dll_crbm_cd1_step_units(const dll_conv_desc *din, int visible, int hi
   dll_conv_desc di = d;
   di.act = DLL_ACT_IDENTITY;
   const WgradArgs pos = wgrad_args(&di, v0, h0p, nullptr, nullptr, part_pos), neg = wgrad_args(&di, v1p, h1p, nullptr, nullptr, part_neg);
-  if ((st = dev(launch_wgrad_two(pos, neg, plan, s))) != DLL_OK) return st;
+  if ((st = dev(launch_wgrad_two(pos, neg, plan, stats, s))) != DLL_OK) return st;
   const float invB = 1.0f / (float)d.N;
   WgradReduceArgs r;
   r.pos = part_pos; r.neg = part_neg; r.scale = invB; r.dw = dW; r.db = db;
   r.C = d.C; r.K = d.K; r.R = d.R; r.S = d.S;
   if (lr != 0.0f) { r.w_update = W; r.b_update = b_hid; r.step = lr; }
-  StepTail t;   // the reduction and the visible sums side by side
+  StepTail t;   // the reduction and the visible statistics side by side
   t.reduce[0].a = r;
   t.reduce[0].plan = plan;
   t.n_reduce = 1;
-  t.vis.v0 = v0; t.vis.v1 = v1p; t.vis.N = d.N; t.vis.C = d.C; t.vis.HW = d.H * d.W; t.vis.scratch = stats;
-  if ((st = dev(launch_step_tail(t, s))) != DLL_OK) return st;
-  return dev(launch_visible_final(d.N, d.C, d.H * d.W, invB, dc, recon_mse, lr != 0.0f ? c_vis : nullptr, lr, stats, s));
+  t.vis.scratch = stats; t.vis.N = d.N; t.vis.C = d.C; t.vis.HW = d.H * d.W; t.vis.scale = invB; t.vis.dc = dc; t.vis.mse = recon_mse;
+  if (lr != 0.0f) { t.vis.c_update = c_vis; t.vis.step = lr; }
+  return dev(launch_step_tail(t, s));
 }
 
 dll_status dll_crbm_cd1_step(const dll_conv_desc *d, const float *v0, float *W, float *b_hid, float *c_vis,

@@ -56,6 +56,7 @@ struct WgradParams {
   // a second filter gradient of the same shape in the same launch (blockIdx.z == 1): the CRBM's negative phase
   const float *x2, *dy2;
   float *partial2;
+  float *visible;          // and the sums of x - x2 per channel and slice (blockIdx.z == 2): small workgroups beside the large ones
   unsigned x_bytes, dy_bytes;   // fast path: tensor sizes (below 2 GiB) for the range-checked loads
 };
 
@@ -112,6 +113,13 @@ __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_k
   constexpr int XI = ONE_ROUND ? 1 : NXI, XH = ONE_ROUND ? 1 : NXH;
   extern __shared__ float lds[];
   WgradArgs a = p.a;
+  if constexpr (POOL == 1) {
+    if (blockIdx.z == 2) {
+      for (int blk = blockIdx.y * gridDim.x + blockIdx.x; blk < kStatBlocks * a.C; blk += gridDim.x * gridDim.y)
+        visible_block(a.x, p.x2, a.N, a.C, a.H * a.W, p.visible, blk, lds);
+      return;
+    }
+  }
   if (blockIdx.z != 0) { a.x = p.x2; a.dy = p.dy2; a.partial = p.partial2; }
   float *xs = lds;                 // [CC][PS]
   float *dzs = xs + p.CC * p.PS;   // [filters of the group][PSZ]
@@ -658,7 +666,7 @@ inline int reduce_blocks(const WgradReduceArgs &a, const WgradPlan &plan) {
 }
 
 // The step's closing kernel: workgroup ranges [start[j], start[j+1]) belong to job j; jobs are the small
-// weight-gradient products, the filter-gradient reductions, the column sums, the mean loss, then the visible sums.  The
+// weight-gradient products, the filter-gradient reductions, the column sums, the mean loss, then the visible statistics.  The
 // reductions alone (PRODUCTS = false) are bound by memory latency and live from their occupancy, which the
 // products' registers and LDS would halve.  As launches of their own the products of a small network took
 // 4 to 10 us each, most of it latency; here they run beside each other and the reductions.
@@ -669,7 +677,6 @@ struct StepTailParams {
   small_gemm::SmallParams gemm[StepTail::kMaxGemm];
   const float *rowloss; int rows; float *loss; double count;
   StepTail::Visible vis;
-  int vis_channels;   // side by side
   int start[StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 3];
   long group_stride[StepTail::kMaxReduce];
   int kgroups[StepTail::kMaxReduce];
@@ -701,7 +708,7 @@ __global__ __launch_bounds__(kThreads) void step_tail_kernel(const StepTailParam
   } else if (p.loss && j == p.n_reduce + p.n_colsum) {
     mean_block(p.rowloss, p.rows, p.loss, p.count);
   } else {
-    visible_block(p.vis.v0, p.vis.v1, p.vis.N, p.vis.C, p.vis.HW, p.vis.scratch, blk, p.vis_channels);
+    if (threadIdx.x < 64) visible_final(p.vis.scratch, p.vis.N, p.vis.C, p.vis.HW, p.vis.scale, p.vis.dc, p.vis.mse, p.vis.c_update, p.vis.step);
   }
 }
 
@@ -822,7 +829,7 @@ enum class Staging { kElements, kVectors, kRagged };
 
 template <int MTF, int NTT>
 hipError_t launch_wgrad_t(const WgradParams &p, const WgradPlan &plan, Staging how, hipStream_t stream) {
-  dim3 grid((unsigned)(plan.G * plan.nchunks), (unsigned)p.kgroups, p.partial2 ? 2 : 1);
+  dim3 grid((unsigned)(plan.G * plan.nchunks), (unsigned)p.kgroups, p.visible ? 3 : (p.partial2 ? 2 : 1));
   auto launch = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, dim3(kThreads), plan.lds_bytes, stream, p);
     return hipGetLastError();
@@ -858,10 +865,11 @@ inline bool aligned16(const void *q) { return (reinterpret_cast<uintptr_t>(q) & 
 
 namespace {
 // b: a second filter gradient of the same shape and activation (NULL: none)
-hipError_t launch_direct(const WgradArgs &a, const WgradArgs *b, const WgradPlan &plan, hipStream_t stream) {
+hipError_t launch_direct(const WgradArgs &a, const WgradArgs *b, const WgradPlan &plan, float *visible_scratch, hipStream_t stream) {
   WgradParams p;
   p.a = a;
   p.x2 = b ? b->x : nullptr; p.dy2 = b ? b->dy : nullptr; p.partial2 = b ? b->partial : nullptr;
+  p.visible = b ? visible_scratch : nullptr;
   p.Ho = a.H + 2 * a.pad - a.R + 1;
   p.Wo = a.W + 2 * a.pad - a.S + 1;
   p.CC = plan.CC;
@@ -903,13 +911,13 @@ hipError_t launch_direct(const WgradArgs &a, const WgradArgs *b, const WgradPlan
 hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &plan, hipStream_t stream) {
   if (wgrad_wino_applies(a, plan)) return launch_wgrad_wino(a, plan, stream);
   if (wgrad_fewch_applies(a, plan)) return launch_wgrad_fewch(a, plan, stream);
-  return launch_direct(a, nullptr, plan, stream);
+  return launch_direct(a, nullptr, plan, nullptr, stream);
 }
 
-hipError_t launch_wgrad_two(const WgradArgs &a, const WgradArgs &b, const WgradPlan &plan, hipStream_t stream) {
+hipError_t launch_wgrad_two(const WgradArgs &a, const WgradArgs &b, const WgradPlan &plan, float *visible_scratch, hipStream_t stream) {
   const bool alike = a.act == ACT_IDENTITY && b.act == ACT_IDENTITY && a.pool == 1 && b.pool == 1 && a.N == b.N && a.C == b.C && a.H == b.H &&
                      a.W == b.W && a.K == b.K && a.R == b.R && a.S == b.S && a.pad == b.pad && a.partial && b.partial;
-  return alike ? launch_direct(a, &b, plan, stream) : hipErrorInvalidValue;
+  return alike ? launch_direct(a, &b, plan, visible_scratch, stream) : hipErrorInvalidValue;
 }
 
 hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, const WgradPlan &plan, hipStream_t stream) {
@@ -958,12 +966,9 @@ hipError_t launch_step_tail(const StepTail &t, hipStream_t stream) {
     blocks += 1;
   }
   p.vis = t.vis;
-  p.vis_channels = 1;
-  if (t.vis.v0) {   // as many channels side by side as the grid has left
-    const long left = (kMaxGrid - blocks) / kStatBlocks;
-    if (left > 1) p.vis_channels = (int)(t.vis.C < left ? t.vis.C : left);
+  if (t.vis.scratch) {
     p.start[jobs++] = blocks;
-    blocks += kStatBlocks * p.vis_channels;
+    blocks += 1;
   }
   if (blocks == 0) return hipSuccess;
   for (int j = jobs; j < StepTail::kMaxGemm + StepTail::kMaxReduce + StepTail::kMaxColsum + 3; ++j) p.start[j] = blocks;

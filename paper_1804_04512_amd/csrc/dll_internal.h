@@ -159,8 +159,9 @@ bool wgrad_fewch_shape(int C, int H, int W, int K, int R, int S, int pad, int po
 bool wgrad_fewch_applies(const WgradArgs &a, const WgradPlan &plan);
 hipError_t launch_wgrad_fewch(const WgradArgs &a, const WgradPlan &plan, hipStream_t stream);
 hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &plan, hipStream_t stream);
-// Two unpooled identity layers' filter gradients of one shape in one launch (the CRBM's two phases).
-hipError_t launch_wgrad_two(const WgradArgs &a, const WgradArgs &b, const WgradPlan &plan, hipStream_t stream);
+// Two unpooled identity layers' filter gradients of one shape in one launch (the CRBM's two phases), and beside them the
+// sums of x - x' of both inputs per channel and slice, visible_stats_scratch_floats floats.
+hipError_t launch_wgrad_two(const WgradArgs &a, const WgradArgs &b, const WgradPlan &plan, float *visible_scratch, hipStream_t stream);
 
 // dw = scale * (sum(pos partials) - sum(neg partials)); optional in-place theta += step * dw.
 struct WgradReduceArgs {
@@ -254,11 +255,7 @@ hipError_t launch_softmax_ce(float *logits, const int *labels, int B, int classe
 hipError_t launch_softmax_prob(float *logits, int B, int classes, float *prob, const float *partial, int split_k, const float *bias,
                                hipStream_t stream);
 
-// CRBM visible statistics from the sums a closing launch left in scratch (visible_stats_scratch_floats floats):
-// dc[ch] = scale * sum(v0 - v1), mse = mean((v0-v1)^2).
 size_t visible_stats_scratch_floats(int N, int C, int HW);
-hipError_t launch_visible_final(int N, int C, int HW, float scale, float *dc, float *mse, float *c_update, float step,
-                                const float *scratch, hipStream_t stream);
 
 hipError_t launch_copy(const float *src, float *dst, size_t count, hipStream_t stream);
 
@@ -285,8 +282,9 @@ struct StepTail {
   GemmArgs gemm[kMaxGemm];   // small products of the weight-gradient form (A contiguous along m, B along n)
   // optional: *loss = sum(rowloss[0 .. rows)) / count (count 0: the number of rows)
   const float *rowloss = nullptr; int rows = 0; float *loss = nullptr; double count = 0.0;
-  // optional: the CRBM's visible sums per channel and slice (launch_visible_final adds them up)
-  struct Visible { const float *v0 = nullptr, *v1 = nullptr; int N = 0, C = 0, HW = 0; float *scratch = nullptr; } vis;
+  // optional: the CRBM's visible statistics from the sums launch_wgrad_two left in scratch: dc[ch] = scale * sum(v0 - v1),
+  // mse = mean((v0 - v1)^2)
+  struct Visible { const float *scratch = nullptr; int N = 0, C = 0, HW = 0; float scale = 1.0f; float *dc = nullptr, *mse = nullptr, *c_update = nullptr; float step = 0.0f; } vis;
 };
 // Whether a product can be a job of the closing launch (operands below 2 GiB, as gemm_is_small asks).
 bool step_tail_takes(const GemmArgs &g);

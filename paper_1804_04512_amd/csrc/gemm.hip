@@ -821,26 +821,6 @@ __global__ __launch_bounds__(kThreads) void softmax_ce_kernel(float *logits, con
   if (tid == 0) rowloss[n] = -(r[label] - m - logf(s));
 }
 
-// One wavefront: a lane per slice (32 sums, 32 sums of squares), added by lane exchanges in double.
-__global__ void visible_stats_final_kernel(const float *scratch, int N, int C, int HW, float scale, float *dc, float *mse,
-                                           float *c_update, float step) {
-  const int lane = threadIdx.x, b = lane & (kStatBlocks - 1);
-  static_assert(kStatBlocks == 32, "half a wavefront per kind of sum");
-  double sq = 0.0;
-  for (int ch = 0; ch < C; ++ch) {
-    double s = (double)scratch[((lane < 32 ? 0 : C) + ch) * kStatBlocks + b];
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) {
-      const float g = (float)(s * (double)scale);
-      if (dc) dc[ch] = g;
-      if (c_update) c_update[ch] += step * g;
-    }
-    sq += s;   // lanes 32 ..: the channel's squares
-  }
-  if (mse && lane == 32) *mse = (float)(sq / ((double)N * C * HW));
-}
-
 __global__ __launch_bounds__(kThreads) void copy_kernel(const float *src, float *dst, size_t count) {
   for (size_t e = (size_t)blockIdx.x * kThreads + threadIdx.x; e < count; e += (size_t)gridDim.x * kThreads) dst[e] = src[e];
 }
@@ -979,13 +959,6 @@ hipError_t launch_softmax_prob(float *logits, int B, int classes, float *prob, c
 }
 
 size_t visible_stats_scratch_floats(int, int C, int) { return (size_t)2 * C * kStatBlocks; }
-
-hipError_t launch_visible_final(int N, int C, int HW, float scale, float *dc, float *mse, float *c_update, float step,
-                                const float *scratch, hipStream_t stream) {
-  hipLaunchKernelGGL(visible_stats_final_kernel, dim3(1), dim3(64), 0, stream, scratch, N, C, HW, scale, dc, mse, c_update,
-                     step);
-  return hipGetLastError();
-}
 
 hipError_t launch_copy(const float *src, float *dst, size_t count, hipStream_t stream) {
   size_t blocks = (count + kThreads - 1) / kThreads;

@@ -76,29 +76,46 @@ __device__ __forceinline__ void mean_block(const float *v, int n, float *out, do
   if (threadIdx.x == 0) *out = (float)(((sh[0] + sh[1]) + (sh[2] + sh[3])) / count);
 }
 
-// The CRBM's visible sums, kStatBlocks workgroups per channel, `channels` of them side by side: scratch[ch][b] = sum over
-// the block's slice of (v0 - v1); scratch[C*32 + ch*32 + b] = sum of squares
+// The CRBM's visible sums, kStatBlocks workgroups per channel: scratch[ch][b] = sum over the block's slice of (v0 - v1);
+// scratch[C*32 + ch*32 + b] = sum of squares.  blk: channel and slice; sh: kSmallThreads floats of LDS.
 constexpr int kStatBlocks = 32;
-__device__ __forceinline__ void visible_block(const float *v0, const float *v1, int N, int C, int HW, float *scratch, int blk, int channels) {
-  __shared__ float sh[kSmallThreads];
-  const int b = blk % kStatBlocks;
+__device__ __forceinline__ void visible_block(const float *v0, const float *v1, int N, int C, int HW, float *scratch, int blk, float *sh) {
+  const int b = blk % kStatBlocks, ch = blk / kStatBlocks;
   const long per = (long)N * HW;
-  for (int ch = blk / kStatBlocks; ch < C; ch += channels) {
-    float s = 0.0f, q = 0.0f;
-    for (long e = (long)b * kSmallThreads + threadIdx.x; e < per; e += (long)kStatBlocks * kSmallThreads) {
-      const long nn = e / HW, r = e - nn * HW;
-      const long o = (nn * C + ch) * HW + r;
-      const float d = v0[o] - v1[o];
-      s += d;
-      q += d * d;
-    }
-    s = block_reduce(s, sh, false);
-    q = block_reduce(q, sh, false);
-    if (threadIdx.x == 0) {
-      scratch[ch * kStatBlocks + b] = s;
-      scratch[(C + ch) * kStatBlocks + b] = q;
-    }
+  float s = 0.0f, q = 0.0f;
+  for (long e = (long)b * kSmallThreads + threadIdx.x; e < per; e += (long)kStatBlocks * kSmallThreads) {
+    const long nn = e / HW, r = e - nn * HW;
+    const long o = (nn * C + ch) * HW + r;
+    const float d = v0[o] - v1[o];
+    s += d;
+    q += d * d;
   }
+  s = block_reduce(s, sh, false);
+  q = block_reduce(q, sh, false);
+  if (threadIdx.x == 0) {
+    scratch[ch * kStatBlocks + b] = s;
+    scratch[(C + ch) * kStatBlocks + b] = q;
+  }
+}
+
+// Their last sums, in one wavefront: a lane per slice (32 sums, 32 sums of squares), added by lane exchanges in double.
+__device__ __forceinline__ void visible_final(const float *scratch, int N, int C, int HW, float scale, float *dc, float *mse, float *c_update,
+                                              float step) {
+  const int lane = threadIdx.x, b = lane & (kStatBlocks - 1);
+  static_assert(kStatBlocks == 32, "half a wavefront per kind of sum");
+  double sq = 0.0;
+  for (int ch = 0; ch < C; ++ch) {
+    double s = (double)scratch[((lane < 32 ? 0 : C) + ch) * kStatBlocks + b];
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0) {
+      const float g = (float)(s * (double)scale);
+      if (dc) dc[ch] = g;
+      if (c_update) c_update[ch] += step * g;
+    }
+    sq += s;   // lanes 32 ..: the channel's squares
+  }
+  if (mse && lane == 32) *mse = (float)(sq / ((double)N * C * HW));
 }
 
 }  // namespace dllk
