@@ -107,20 +107,21 @@ struct TileRegs {
 // Y: the layer output is read (sigmoid, ReLU without flags).  Unpooled layers whose derivative is 1 (the
 // CRBM's statistics among them) have an instance without those registers, four per 16 filters and row pair: two
 // workgroups per CU where there was one (64 x 28 x 28, 40 filters 9x9, both phases: 32 -> 22 us).
-template <int MTF, int NTT, int POOL, int FAST, bool Y>
+// TWO: a second filter gradient (blockIdx.z == 1) and the sums of x - x2 (2) in the same launch.
+template <int MTF, int NTT, int POOL, int FAST, bool Y, bool TWO = false>
 __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_kernel(const WgradParams p) {
   constexpr bool ONE_ROUND = FAST == 2 || FAST == 4, RAGGED = FAST >= 3;
   constexpr int XI = ONE_ROUND ? 1 : NXI, XH = ONE_ROUND ? 1 : NXH;
   extern __shared__ float lds[];
   WgradArgs a = p.a;
-  if constexpr (POOL == 1) {
+  if constexpr (TWO) {
     if (blockIdx.z == 2) {
       for (int blk = blockIdx.y * gridDim.x + blockIdx.x; blk < kStatBlocks * a.C; blk += gridDim.x * gridDim.y)
         visible_block(a.x, p.x2, a.N, a.C, a.H * a.W, p.visible, blk, lds);
       return;
     }
+    if (blockIdx.z != 0) { a.x = p.x2; a.dy = p.dy2; a.partial = p.partial2; }
   }
-  if (blockIdx.z != 0) { a.x = p.x2; a.dy = p.dy2; a.partial = p.partial2; }
   float *xs = lds;                 // [CC][PS]
   float *dzs = xs + p.CC * p.PS;   // [filters of the group][PSZ]
 
@@ -835,9 +836,10 @@ hipError_t launch_wgrad_t(const WgradParams &p, const WgradPlan &plan, Staging h
     return hipGetLastError();
   };
   const bool pooled = p.a.pool == 2, y = reads_output(p.a.act);
-  if (how == Staging::kElements) return launch(wgrad_kernel<MTF, NTT, 1, 0, true>);
+  if (how == Staging::kElements) return p.partial2 ? launch(wgrad_kernel<MTF, NTT, 1, 0, true, true>) : launch(wgrad_kernel<MTF, NTT, 1, 0, true>);
   auto form = [&](auto fastc) {
     constexpr int FAST = decltype(fastc)::value;
+    if (p.partial2) return launch(wgrad_kernel<MTF, NTT, 1, FAST, false, true>);   // unpooled identity layers
     if (pooled) return launch(wgrad_kernel<MTF, NTT, 2, FAST, true>);
     return y ? launch(wgrad_kernel<MTF, NTT, 1, FAST, true>) : launch(wgrad_kernel<MTF, NTT, 1, FAST, false>);
   };
