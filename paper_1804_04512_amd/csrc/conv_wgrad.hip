@@ -236,11 +236,13 @@ __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_k
     const floatx4 v = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, (int)soff, 0));
     return make_float4(v[0], v[1], v[2], v[3]);
   };
+  int in_x = 0, in_y = 0;   // first output column and row of the tile that was loaded last
   auto load_tile = [&](int item) {
     const int tx = item % p.tiles_x;
     const int ty = (item / p.tiles_x) % p.tiles_y;
     const int n = item / (p.tiles_x * p.tiles_y);
     const int oy0 = ty * TH, ox0 = tx * kTileW;
+    in_x = ox0; in_y = oy0;
     const int gy0 = oy0 - a.pad;                                            // image row of the halo tile's first row
     const unsigned xbase = 4u * ((unsigned)(n * a.C + c0) * a.H * a.W);     // bytes to (n, c0, 0, 0)
     const int torg = 4 * (gy0 * a.W + ox0 - a.pad);                         // bytes to the halo tile's first element inside a plane (negative on the top/left edge)
@@ -413,6 +415,11 @@ __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_k
     __syncthreads();   // the previous tile's MFMA reads are done
     if (FAST) store_tile(); else stage_generic(item);
     __syncthreads();
+    if (!FAST) {
+      in_x = item % p.tiles_x * kTileW;
+      in_y = item / p.tiles_x % p.tiles_y * TH;
+    }
+    const int ox0 = in_x, oy0 = in_y;
     if (FAST && item + slots < item_lim) load_tile(item + slots);   // in flight during the MFMA loop
     // ---- MFMA: 4 neighbouring pixels per step.  Operand fragments are double-buffered in
     // registers: the LDS reads of step t+1 are issued before the MFMAs of step t.
@@ -442,8 +449,7 @@ __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_k
       // of its three 8 x 32 tiles; the products of the rest were exact zeros (this kernel, 64 x 28 x 28, 40 filters 9x9, both
       // phases: 23.3 -> 21.0 us; 100 x 12 x 16 x 16, 24 filters 3x3: 12.8 -> 11.6; 8 x 8 maps, 8 filters 5x5: 8.7 -> 7.4).
       // Whole tiles keep their operand reads one step ahead across rows; a narrow one asks for the second row's by itself.
-      const int tx = item % p.tiles_x, ty = (item / p.tiles_x) % p.tiles_y;
-      const int pairs = min(4, (p.Wo - tx * kTileW + 7) >> 3), rows = p.Ho - ty * TH - wave_u * RW;
+      const int pairs = min(4, (p.Wo - ox0 + 7) >> 3), rows = p.Ho - oy0 - wave_u * RW;
       if (rows > 0) load_frags(I0{}, 0, 0);
 #pragma unroll
       for (int rr = 0; rr < RW; ++rr) {
