@@ -403,6 +403,14 @@ dll_status dll_crbm_cd1_step_units(const dll_conv_desc *din, int visible, int hi
   float *h1p = h1_prob ? h1_prob : h1p_ws;
   float *v1p = v1 ? v1 : v1_ws;
   const int hid_act = pmp ? ACT_PMP : ACT_SIGMOID;
+  const float invB = 1.0f / (float)d.N;
+  WgradReduceArgs r;
+  r.pos = part_pos; r.neg = part_neg; r.scale = invB; r.dw = dW; r.db = db;
+  r.C = d.C; r.K = d.K; r.R = d.R; r.S = d.S;
+  if (lr != 0.0f) { r.w_update = W; r.b_update = b_hid; r.step = lr; }
+  // Asked before anything runs: the visible sums' places are counted in 32 bits, which end at four times the channels
+  // that a closing launch holds.
+  if (!crbm_tail_fits(r, plan)) return DLL_ERR_DEVICE;
 
   // positive phase: hidden probabilities (+ the sampled states in the same epilogue)
   ConvEngineArgs f0 = fwd_args(&d, v0, W, b_hid, h0p, nullptr);
@@ -430,11 +438,6 @@ dll_status dll_crbm_cd1_step_units(const dll_conv_desc *din, int visible, int hi
   di.act = DLL_ACT_IDENTITY;
   const WgradArgs pos = wgrad_args(&di, v0, h0p, nullptr, nullptr, part_pos), neg = wgrad_args(&di, v1p, h1p, nullptr, nullptr, part_neg);
   if ((st = dev(launch_wgrad_two(pos, neg, plan, stats, s))) != DLL_OK) return st;
-  const float invB = 1.0f / (float)d.N;
-  WgradReduceArgs r;
-  r.pos = part_pos; r.neg = part_neg; r.scale = invB; r.dw = dW; r.db = db;
-  r.C = d.C; r.K = d.K; r.R = d.R; r.S = d.S;
-  if (lr != 0.0f) { r.w_update = W; r.b_update = b_hid; r.step = lr; }
   StepTail t;   // the reduction and the visible statistics side by side
   t.reduce[0].a = r;
   t.reduce[0].plan = plan;

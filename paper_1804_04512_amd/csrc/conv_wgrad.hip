@@ -668,8 +668,8 @@ inline long reduce_group_stride(const WgradPlan &plan) {
   return (long)plan.nchunks * plan.n_partials * ((long)plan.MTF * plan.NTT * 256);
 }
 inline int reduce_kgroups(const WgradReduceArgs &a, const WgradPlan &plan) { return (a.K + plan.MTF * 16 - 1) / (plan.MTF * 16); }
-inline int reduce_blocks(const WgradReduceArgs &a, const WgradPlan &plan) {
-  return reduce_kgroups(a, plan) * plan.nchunks * plan.MTF * plan.NTT * 16 + (a.K + 15) / 16;
+inline long reduce_blocks(const WgradReduceArgs &a, const WgradPlan &plan) {
+  return (long)reduce_kgroups(a, plan) * plan.nchunks * plan.MTF * plan.NTT * 16 + (a.K + 15) / 16;
 }
 
 // The step's closing kernel: workgroup ranges [start[j], start[j+1]) belong to job j; jobs are the small
@@ -930,10 +930,12 @@ hipError_t launch_wgrad_two(const WgradArgs &a, const WgradArgs &b, const WgradP
 
 hipError_t launch_wgrad_reduce(const WgradReduceArgs &a, const WgradPlan &plan, hipStream_t stream) {
   if ((reinterpret_cast<uintptr_t>(a.pos) & 15u) || (a.neg && (reinterpret_cast<uintptr_t>(a.neg) & 15u))) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(reduce_blocks(a, plan)), dim3(kThreads), 0, stream, a, plan,
+  hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)reduce_blocks(a, plan)), dim3(kThreads), 0, stream, a, plan,
                      reduce_group_stride(plan), reduce_kgroups(a, plan));
   return hipGetLastError();
 }
+
+bool crbm_tail_fits(const WgradReduceArgs &a, const WgradPlan &plan) { return reduce_blocks(a, plan) + 1 <= kMaxGrid; }
 
 bool step_tail_takes(const GemmArgs &g) {
   return g.split_k <= 1 && gemm_is_small(GemmForm::kWeightGrad, g.M, g.N, g.Kdim) && g.a_m == 1 && g.b_n == 1 && g.c_n == 1 && !g.bias && !g.C_ref &&
@@ -962,7 +964,7 @@ hipError_t launch_step_tail(const StepTail &t, hipStream_t stream) {
     p.group_stride[j] = reduce_group_stride(t.reduce[j].plan);
     p.kgroups[j] = reduce_kgroups(a, t.reduce[j].plan);
     p.start[jobs++] = blocks;
-    blocks += reduce_blocks(a, t.reduce[j].plan);
+    blocks += (int)reduce_blocks(a, t.reduce[j].plan);
   }
   for (int j = 0; j < t.n_colsum; ++j) {
     p.colsum[j] = t.colsum[j];

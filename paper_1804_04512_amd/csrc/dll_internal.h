@@ -286,6 +286,9 @@ struct StepTail {
   // mse = mean((v0 - v1)^2)
   struct Visible { const float *scratch = nullptr; int N = 0, C = 0, HW = 0; float scale = 1.0f; float *dc = nullptr, *mse = nullptr, *c_update = nullptr; float step = 0.0f; } vis;
 };
+// Whether a closing launch holds this reduction and the visible statistics (at least two workgroups per input channel, so
+// the CRBM step has 8.4 million channels at most).
+bool crbm_tail_fits(const WgradReduceArgs &a, const WgradPlan &plan);
 // Whether a product can be a job of the closing launch (operands below 2 GiB, as gemm_is_small asks).
 bool step_tail_takes(const GemmArgs &g);
 hipError_t launch_step_tail(const StepTail &t, hipStream_t stream);

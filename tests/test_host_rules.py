@@ -102,6 +102,16 @@ def test_grids_past_what_a_launch_can_have(tmp_path):
     assert [len(f) for f in forward[1:4]] == [1, 1, 2] and forward[2][0][1] == (1 << 24) - 1
 
 
+def test_crbm_step_that_cannot_be_finished_is_not_begun(tmp_path):
+    """A step of more channels than its closing launch holds is refused before its first launch: the visible sums, which
+    run before the closing launch, would count places past 2^31 (and write there) from 33.5 million channels on."""
+    calls = [["crbm", 1, c, 1, 1, 1, 1, 1, 0] for c in (8_000_000, 9_000_000, 34_000_000, 70_000_000, 2_000_000_000)]
+    got = record(calls, tmp_path)
+    assert got[0][0] == 0 and len(got[0][1]) == 5
+    for call, (status, launches) in zip(calls[1:], got[1:]):
+        assert status == 5 and not launches, (call, status, launches)
+
+
 def test_outputs_over_inputs(tmp_path):
     """A one-layer network's probabilities over its input and an RBM step's reconstruction over the states it starts from:
     nothing writes there while a product still reads (both had come to be written by that product itself)."""
