@@ -428,12 +428,17 @@ __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_k
       static_assert(RW == 2, "dz_row(wave * RW + rr) = dz_row(wave * RW) + dz_row(rr) needs an even first row");
       const float *za = dzs + dz_row<POOL>(wave * RW) + kq;
       const float *xb = xs + (wave * RW) * p.RS + kq;
+      // Taken for new in every tile.  Known to be the same, it had the compiler keep the second row's addresses across tiles
+      // beside the first row's: 4 to 20 registers, which at <2, 9> unpooled and five ragged instances were a wavefront per
+      // SIMD (64 x 16x40x40, 32 filters 3x3, sigmoid: 30.9 us without the checks below, 39.8 with them, 30.4 this way).
+      int row_stride = p.RS;
+      asm volatile("" : "+s"(row_stride));
       auto load_frags = [&](auto bufc, int rr, int cg) {
         constexpr int B_ = decltype(bufc)::value;
 #pragma unroll
         for (int mf = 0; mf < MTF; ++mf) af[B_][mf] = za[fplane[mf] + dz_row<POOL>(rr) + 4 * cg];
 #pragma unroll
-        for (int nt = 0; nt < NTT; ++nt) bf[B_][nt] = xb[tapoff[nt] + rr * p.RS + 4 * cg];
+        for (int nt = 0; nt < NTT; ++nt) bf[B_][nt] = xb[tapoff[nt] + rr * row_stride + 4 * cg];
       };
       auto mfma_frags = [&](auto bufc) {
         constexpr int B_ = decltype(bufc)::value;
@@ -445,9 +450,12 @@ __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_k
       };
       using I0 = std::integral_constant<int, 0>;
       using I1 = std::integral_constant<int, 1>;
-      // The steps that hold outputs: pairs of 4-column groups left of the map's edge, rows above it.  A 20 x 20 map is 1.6
-      // of its three 8 x 32 tiles; the products of the rest were exact zeros (this kernel, 64 x 28 x 28, 40 filters 9x9, both
-      // phases: 23.3 -> 21.0 us; 100 x 12 x 16 x 16, 24 filters 3x3: 12.8 -> 11.6; 8 x 8 maps, 8 filters 5x5: 8.7 -> 7.4).
+      // The steps that hold outputs: pairs of 4-column groups left of the map's edge, rows above it.  A 20 x 20 map takes 1.9
+      // of its three 8 x 32 tiles; the products of the rest add zeros, or NaN where the image is not finite there (this
+      // kernel, 64 x 28 x 28, 40 filters 9x9, both phases: 23.3 -> 21.0 us; 100 x 12 x 16 x 16, 24 filters 3x3: 10.9 -> 9.3).
+      // A check costs about 30 cycles that nothing hides where a SIMD has one wavefront: layers of whole tiles pay up to 3 %
+      // (16 x 3x128x128, 48 filters 7x7: 66.7 -> 68.0 us).  A loop of their own beside this one spilled its accumulators or
+      // took registers that cost a wavefront; this loop rolled, addresses walking along, took 74.2 us there.
       // Whole tiles keep their operand reads one step ahead across rows; a narrow one asks for the second row's by itself.
       const int pairs = min(4, (p.Wo - ox0 + 7) >> 3), rows = p.Ho - oy0 - wave_u * RW;
       if (rows > 0) load_frags(I0{}, 0, 0);

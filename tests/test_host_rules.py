@@ -1,5 +1,8 @@
 """What the library settles on the host before it launches anything: workspace sizes, and which kernel takes a call
 (launches are noted instead of run: no GPU needed)."""
+import re
+import struct
+
 import pytest
 
 from paper_1804_04512_amd import binding as B
@@ -128,6 +131,45 @@ def test_fourier_tile_sizes_have_a_test(tmp_path):
     names = ["".join(l[0] for l in launches) for _, launches in record(calls, tmp_path)]
     want = ["product_kernelILi4ELi8E", "product_inverse_kernelILi2ELi2E"] * 2 + ["product_kernelILi4ELi4E", "product_inverse_kernelILi1ELi1E"]
     assert all(w in n for w, n in zip(want, names)), names
+
+
+def _kernel_resources(path):
+    """Name -> resources of every kernel in a built library, from the notes of the code objects in it."""
+    msgpack = pytest.importorskip("msgpack")
+    data, out = open(path, "rb").read(), {}
+    for m in re.finditer(rb"\x7fELF\x02\x01\x01\x40", data):   # 64 bits, AMD GPU
+        elf = data[m.start():]
+        (table,), (size, count) = struct.unpack_from("<Q", elf, 0x28), struct.unpack_from("<HH", elf, 0x3A)
+        for i in range(count):
+            _, kind, _, _, at, _ = struct.unpack_from("<IIQQQQ", elf, table + i * size)
+            if kind != 7:
+                continue
+            name, body, note = struct.unpack_from("<III", elf, at)
+            if note == 32:
+                start = at + 12 + (name + 3) // 4 * 4
+                for k in msgpack.unpackb(elf[start:start + body], strict_map_key=False)["amdhsa.kernels"]:
+                    out[k[".name"]] = k
+    return out
+
+
+def test_filter_gradient_registers_leave_the_planned_wavefronts():
+    """plan_wgrad sizes its grid by the wavefronts a SIMD has room for beside the registers of the instances with layer
+    output.  Checks in the product loop had taken one from <2, 9> unpooled (a layer there 27 % slower) and from five of
+    the ragged instances."""
+    plan = {1: [[4, 3, 3, 2], [3, 2, 2, 2], [2, 1, 1, 1]], 2: [[5, 4, 3, 3], [4, 3, 2, 2], [3, 2, 2, 2]]}   # [pool][filters / 16 - 1][tap tiles]
+    one_round = {1: [5, 3, 2], 2: [7, 5, 4]}
+    # <filters / 16, tap tiles, pool, staging> that have one less: ragged rows (3) but for one
+    less = {(1, 2, 1, 3), (2, 2, 1, 1), (2, 2, 1, 3), (2, 9, 1, 3), (1, 2, 2, 3), (1, 5, 2, 3), (2, 2, 2, 3), (2, 5, 2, 3), (3, 9, 2, 3)}
+    kernels = _kernel_resources(B.LIB_PATH)
+    for pool in (1, 2):
+        for m in (1, 2, 3):
+            for j, ntt in enumerate((2, 5, 7, 9)):
+                for fast in (1, 2, 3, 4) if ntt == 2 else (1, 3):
+                    name = f"_ZN4dllk12_GLOBAL__N_112wgrad_kernelILi{m}ELi{ntt}ELi{pool}ELi{fast}ELb1ELb0EEEvNS0_11WgradParamsE"
+                    waves = min(8, 512 // ((kernels[name][".vgpr_count"] + 7) // 8 * 8))
+                    want = (plan if fast in (1, 3) else one_round)[pool][m - 1]
+                    want = (want[j] if fast in (1, 3) else want) - ((m, ntt, pool, fast) in less)
+                    assert waves >= want, (name, kernels[name][".vgpr_count"], waves, want)
 
 
 # RBM steps (batch, visible, hidden units): the largest of their kind in the small-product kernels, and the next beyond
