@@ -56,7 +56,7 @@ struct WgradParams {
   // a second filter gradient of the same shape in the same launch (blockIdx.z == 1): the CRBM's negative phase
   const float *x2, *dy2;
   float *partial2;
-  float *visible;          // and the sums of x - x2 per channel and slice (blockIdx.z == 2): small workgroups beside the large ones
+  float *visible;          // and the sums of x - x2 per channel and slice (blockIdx.z >= 2), a workgroup each
   unsigned x_bytes, dy_bytes;   // fast path: tensor sizes (below 2 GiB) for the range-checked loads
 };
 
@@ -107,7 +107,7 @@ struct TileRegs {
 // Y: the layer output is read (sigmoid, ReLU without flags).  Unpooled layers whose derivative is 1 (the
 // CRBM's statistics among them) have an instance without those registers, four per 16 filters and row pair: two
 // workgroups per CU where there was one (64 x 28 x 28, 40 filters 9x9, both phases: 32 -> 22 us).
-// TWO: a second filter gradient (blockIdx.z == 1) and the sums of x - x2 (2) in the same launch.
+// TWO: a second filter gradient (blockIdx.z == 1) and the sums of x - x2 (2 and up) in the same launch.
 template <int MTF, int NTT, int POOL, int FAST, bool Y, bool TWO = false>
 __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_kernel(const WgradParams p) {
   constexpr bool ONE_ROUND = FAST == 2 || FAST == 4, RAGGED = FAST >= 3;
@@ -115,9 +115,9 @@ __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_k
   extern __shared__ float lds[];
   WgradArgs a = p.a;
   if constexpr (TWO) {
-    if (blockIdx.z == 2) {
-      for (int blk = blockIdx.y * gridDim.x + blockIdx.x; blk < kStatBlocks * a.C; blk += gridDim.x * gridDim.y)
-        visible_block(a.x, p.x2, a.N, a.C, a.H * a.W, p.visible, blk, lds);
+    if (blockIdx.z >= 2) {
+      const int blk = ((int)(blockIdx.z - 2) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+      if (blk < kStatBlocks * a.C) visible_block(a.x, p.x2, a.N, a.C, a.H * a.W, p.visible, blk, lds);
       return;
     }
     if (blockIdx.z != 0) { a.x = p.x2; a.dy = p.dy2; a.partial = p.partial2; }
@@ -844,7 +844,14 @@ enum class Staging { kElements, kVectors, kRagged };
 
 template <int MTF, int NTT>
 hipError_t launch_wgrad_t(const WgradParams &p, const WgradPlan &plan, Staging how, hipStream_t stream) {
-  dim3 grid((unsigned)(plan.G * plan.nchunks), (unsigned)p.kgroups, p.visible ? 3 : (p.partial2 ? 2 : 1));
+  dim3 grid((unsigned)(plan.G * plan.nchunks), (unsigned)p.kgroups, 1);
+  if (p.partial2) {
+    // The visible sums get planes enough for a workgroup each: G follows the image tiles, of which a small batch has few.
+    // Walked in turn by one plane, 512 sums on 16 workgroups held the launch up (CRBM step at 8 x 16x16x16, 8 filters
+    // 3x3: 63 us, 47 this way; 1 x 64x16x16: 271, 111).  nchunks >= C / 16 keeps this below 515 planes.
+    const long plane = (long)grid.x * grid.y;
+    grid.z = (unsigned)(2 + ((long)kStatBlocks * p.a.C + plane - 1) / plane);
+  }
   auto launch = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, dim3(kThreads), plan.lds_bytes, stream, p);
     return hipGetLastError();
@@ -885,7 +892,7 @@ hipError_t launch_direct(const WgradArgs &a, const WgradArgs *b, const WgradPlan
   WgradParams p;
   p.a = a;
   p.x2 = b ? b->x : nullptr; p.dy2 = b ? b->dy : nullptr; p.partial2 = b ? b->partial : nullptr;
-  p.visible = b ? visible_scratch : nullptr;
+  p.visible = visible_scratch;
   p.Ho = a.H + 2 * a.pad - a.R + 1;
   p.Wo = a.W + 2 * a.pad - a.S + 1;
   p.CC = plan.CC;
@@ -932,7 +939,7 @@ hipError_t launch_wgrad(const WgradArgs &a, const WgradPlan &plan, hipStream_t s
 
 hipError_t launch_wgrad_two(const WgradArgs &a, const WgradArgs &b, const WgradPlan &plan, float *visible_scratch, hipStream_t stream) {
   const bool alike = a.act == ACT_IDENTITY && b.act == ACT_IDENTITY && a.pool == 1 && b.pool == 1 && a.N == b.N && a.C == b.C && a.H == b.H &&
-                     a.W == b.W && a.K == b.K && a.R == b.R && a.S == b.S && a.pad == b.pad && a.partial && b.partial;
+                     a.W == b.W && a.K == b.K && a.R == b.R && a.S == b.S && a.pad == b.pad && a.partial && b.partial && visible_scratch;
   return alike ? launch_direct(a, &b, plan, visible_scratch, stream) : hipErrorInvalidValue;
 }
 

@@ -77,11 +77,16 @@ __device__ __forceinline__ void mean_block(const float *v, int n, float *out, do
 }
 
 // The CRBM's visible sums, kStatBlocks workgroups per channel: scratch[ch][b] = sum over the block's slice of (v0 - v1);
-// scratch[C*32 + ch*32 + b] = sum of squares.  blk: channel and slice; sh: kSmallThreads floats of LDS.
+// scratch[C*32 + ch*32 + b] = sum of squares.  blk: channel and slice; sh: kSmallThreads floats of LDS.  Small batches fill
+// the first slices only; the others' sums are zero without a reduction.
 constexpr int kStatBlocks = 32;
 __device__ __forceinline__ void visible_block(const float *v0, const float *v1, int N, int C, int HW, float *scratch, int blk, float *sh) {
   const int b = blk % kStatBlocks, ch = blk / kStatBlocks;
   const long per = (long)N * HW;
+  if ((long)b * kSmallThreads >= per) {   // uniform
+    if (threadIdx.x == 0) scratch[ch * kStatBlocks + b] = scratch[(C + ch) * kStatBlocks + b] = 0.0f;
+    return;
+  }
   float s = 0.0f, q = 0.0f;
   for (long e = (long)b * kSmallThreads + threadIdx.x; e < per; e += (long)kStatBlocks * kSmallThreads) {
     const long nn = e / HW, r = e - nn * HW;

@@ -96,7 +96,7 @@ def test_grids_past_what_a_launch_can_have(tmp_path):
              ["fft", 16_000_000, 4, 2, 2, 2, 2, 2, 0, "identity", 1],     # 32 million inverse transforms, or 8 million of 2 x 2
              ["fft", 2, 4096, 2, 2, 4095, 2, 2, 0, "identity", 1],        # as many transforms as fit
              ["fft", 2, 4095, 2, 2, 4096, 2, 2, 0, "identity", 1],        # one operand after the other
-             ["crbm", 1, 600_000, 2, 2, 1, 1, 1, 0],                      # 19 million visible sums
+             ["crbm", 1, 600_000, 2, 2, 1, 1, 1, 0],                      # 19 million visible sums, on 512 planes
              ["rbm", 1, 400_000_000, 1]]                                  # 25 million column sums
     got = record(calls, tmp_path)
     for call, (status, launches) in zip(calls, got):
@@ -113,6 +113,19 @@ def test_crbm_step_that_cannot_be_finished_is_not_begun(tmp_path):
     assert got[0][0] == 0 and len(got[0][1]) == 5
     for call, (status, launches) in zip(calls[1:], got[1:]):
         assert status == 5 and not launches, (call, status, launches)
+
+
+def test_crbm_step_launches(tmp_path):
+    """Five launches; both phases' filter gradients in one, on two planes of workgroups, and a workgroup for each of the 32
+    visible sums per channel on the planes behind them, however few tiles the images have (they were walked in turn by one
+    plane of as many workgroups as a filter gradient has)."""
+    calls = [["crbm", 64, 1, 28, 28, 40, 9, 9, 0], ["crbm", 8, 16, 16, 16, 8, 3, 3, 0], ["crbm", 1, 64, 16, 16, 8, 3, 3, 1],
+             ["crbm", 1, 3, 16, 17, 33, 5, 5, 0], ["crbm", 2, 16, 20, 20, 9, 9, 1, 0], ["crbm", 1, 8_000_000, 1, 1, 1, 1, 1, 0]]
+    for call, (status, launches) in zip(calls, record(calls, tmp_path)):
+        assert status == 0 and len(launches) == 5, (call, launches)
+        name, x, y, z, _ = launches[3]
+        assert "wgrad_kernel" in name and name.split("EEEv")[0].endswith("Lb1") and "step_tail_kernelILb0E" in launches[4][0], (call, launches)
+        assert 32 * call[2] <= x * y * (z - 2) < 32 * call[2] + x * y, (call, launches)
 
 
 def test_outputs_over_inputs(tmp_path):
