@@ -185,6 +185,21 @@ def test_filter_gradient_registers_leave_the_planned_wavefronts():
                     assert waves >= want, (name, kernels[name][".vgpr_count"], waves, want)
 
 
+def test_map_edge_lists_reach_the_instances(tmp_path):
+    """test_gpu_wgrad_edges.py: every staging form and number of tap tiles, pooled and not, with and without the layer
+    output; whole rows and ragged ones with two gradients in one launch."""
+    import test_gpu_wgrad_edges as E
+    fields = lambda c: [c.N, c.C, c.H, c.W, c.K, c.R, c.S, c.pad, c.act, c.pool]
+    got = record([["wgrad", *fields(c)] for c in E.LAYERS] + [["crbm", *fields(c)[:8]] for c in E.CRBM], tmp_path)
+    names = [next(l[0] for l in launches if "wgrad_kernel" in l[0]) for status, launches in got if status == 0]
+    assert len(names) == len(got)
+    seen = {tuple(map(int, re.search(r"wgrad_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELb(\d)ELb(\d)E", n).groups()))[1:] for n in names}
+    want = {(2, pool, fast, y, 0) for fast in (2, 4) for pool, y in ((1, 0), (1, 1), (2, 1))}
+    want |= {(ntt, pool, fast, y, 0) for ntt in (5, 7, 9) for fast in (1, 3) for pool, y in ((1, 0), (1, 1), (2, 1))}
+    want |= {(9, 1, 0, 1, 0), (2, 1, 2, 0, 1), (2, 1, 4, 0, 1), (7, 1, 1, 0, 1), (9, 1, 1, 0, 1), (5, 1, 3, 0, 1), (9, 1, 3, 0, 1), (9, 1, 0, 1, 1)}
+    assert want <= seen, sorted(want - seen)
+
+
 # RBM steps (batch, visible, hidden units): the largest of their kind in the small-product kernels, and the next beyond
 LINES = [((64, 1024, 4096), (64, 1024, 4100)), ((128, 1024, 1536), (128, 1024, 1540)), ((512, 1024, 1024), (516, 1024, 1024)),
          ((127, 1024, 4124), (127, 1024, 4132)), ((129, 2048, 4064), (129, 2048, 4068)), ((513, 1025, 2041), (513, 1025, 2045))]
