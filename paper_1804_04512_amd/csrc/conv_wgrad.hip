@@ -453,9 +453,12 @@ __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_k
       // The steps that hold outputs: pairs of 4-column groups left of the map's edge, rows above it.  A 20 x 20 map takes 1.9
       // of its three 8 x 32 tiles; the products of the rest add zeros, or NaN where the image is not finite there (this
       // kernel, 64 x 28 x 28, 40 filters 9x9, both phases: 23.3 -> 21.0 us; 100 x 12 x 16 x 16, 24 filters 3x3: 10.9 -> 9.3).
-      // A check costs about 30 cycles that nothing hides where a SIMD has one wavefront: layers of whole tiles pay up to 3 %
-      // (16 x 3x128x128, 48 filters 7x7: 66.7 -> 68.0 us).  A loop of their own beside this one spilled its accumulators or
-      // took registers that cost a wavefront; this loop rolled, addresses walking along, took 74.2 us there.
+      // A check costs about 30 cycles that nothing hides where a SIMD has one wavefront: layers with little to leave out pay
+      // up to 4 % (16 x 3x128x128, 48 filters 7x7: 66.7 -> 68.0 us).  Of 300 random layers 203 are more than 1 % faster than
+      // without the checks (up to 49 %), 27 more than 1 % slower, one of them by 16 % (90 x 1x58x44, 19 filters 7x7, pooled:
+      // 29.7 -> 34.6; its grid is larger than what is resident, and tiles of unequal length deal it out worse).  A loop for
+      // whole tiles beside this one spilled its accumulators or took registers that cost a wavefront; this loop rolled, its
+      // addresses walking along, took 74.2 us where it takes 68.0.
       // Whole tiles keep their operand reads one step ahead across rows; a narrow one asks for the second row's by itself.
       const int pairs = min(4, (p.Wo - ox0 + 7) >> 3), rows = p.Ho - oy0 - wave_u * RW;
       if (rows > 0) load_frags(I0{}, 0, 0);
@@ -798,8 +801,9 @@ bool plan_wgrad(int N, int C, int H, int W, int K, int R, int S, int pad, int po
   long resident = (long)(chip().lds_bytes / plan->lds_bytes);
   // waves per SIMD that the registers of the instances with layer output and whole rows (vector + accumulator, from
   // the compiler's resource report) leave room for; a grid beyond it queues workgroups behind resident ones.  The
-  // instances without layer output fit one more at <3, 2>, <3, 5> and <3, 7> unpooled, some ragged ones one less: the
-  // grid, on which the partial sums' layout and order depend, is the same for all of a shape's instances.
+  // instances without layer output fit one more at <3, 2>, <3, 5> and <3, 7> unpooled, some ragged ones and <2, 2> unpooled
+  // with several staging rounds one less: the grid, on which the partial sums' layout and order depend, is the same for all
+  // of a shape's instances.
   static const int kByRegs[2][3][4] = {
       // NTT =  2  5  7  9     (pooled staging)
       {{5, 4, 3, 3}, {4, 3, 2, 2}, {3, 2, 2, 2}},
