@@ -107,7 +107,8 @@ struct TileRegs {
 // Y: the layer output is read (sigmoid, ReLU without flags).  Unpooled layers whose derivative is 1 (the
 // CRBM's statistics among them) have an instance without those registers, four per 16 filters and row pair: two
 // workgroups per CU where there was one (64 x 28 x 28, 40 filters 9x9, both phases: 32 -> 22 us).
-// TWO: a second filter gradient (blockIdx.z == 1) and the sums of x - x2 (2 and up) in the same launch.
+// TWO: a second filter gradient (blockIdx.z == 1) and the sums of x - x2 (2 and up) in the same launch.  An instance of its
+// own also for element-wise staging (tall filters, tensors past 2 GiB): shared, single gradients lost 1 to 2 % there.
 template <int MTF, int NTT, int POOL, int FAST, bool Y, bool TWO = false>
 __global__ __launch_bounds__(kThreads, Y || MTF * NTT > 21 ? 1 : 2) void wgrad_kernel(const WgradParams p) {
   constexpr bool ONE_ROUND = FAST == 2 || FAST == 4, RAGGED = FAST >= 3;
